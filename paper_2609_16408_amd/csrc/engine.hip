@@ -51,7 +51,12 @@ struct rpa_ctx {
   double* psi64 = nullptr;
   double* eps_d = nullptr;
   std::vector<double> eps_h;
-  double* Vax[3] = {nullptr, nullptr, nullptr};   // per-axis eigenbasis [grid][mode]
+  // per-axis eigenbases: padded forward and inverse matrices of the fused
+  // transforms, or [grid][mode] for grids beyond them
+  bool fused = false;
+  double* Vax[3] = {nullptr, nullptr, nullptr};
+  double* Tf[3] = {nullptr, nullptr, nullptr};
+  double* Ti[3] = {nullptr, nullptr, nullptr};
   double* s_half = nullptr;
   double* s_full = nullptr;
   StencilCoef<double> c64;
@@ -262,11 +267,18 @@ void drop_graphs(rpa_ctx* h);
 rpa_status coulomb(rpa_ctx* h, int power, int B, const double* in, double* out, hipStream_t s) {
   const size_t bytes = (size_t)B * h->N * sizeof(double);
   ENSURE(h, h->tmpA, bytes);
-  ENSURE(h, h->vtmp, bytes);
   double* a = P<double>(h->tmpA);
-  double* b = P<double>(h->vtmp);
   const int* n = h->n;
   const double* sc = power == 1 ? h->s_half : h->s_full;
+  if (h->fused) {
+    // y and z forward; x forward, scale, x inverse (in place); y and z inverse
+    HIPCHK(h, launch_planes(in, a, (long long)B * n[0], n[1], n[2], n[1], n[2], h->Tf[1], h->Tf[2], s));
+    HIPCHK(h, launch_cols_scale(a, a, B, n[0], n[1] * n[2], h->Tf[0], h->Ti[0], sc, s));
+    HIPCHK(h, launch_planes(a, out, (long long)B * n[0], n[1], n[2], n[1], n[2], h->Ti[1], h->Ti[2], s));
+    return RPA_OK;
+  }
+  ENSURE(h, h->vtmp, bytes);
+  double* b = P<double>(h->vtmp);
   // forward: modes = V^T along each axis
   HIPCHK(h, launch_axis(in, a, B, n[0], n[1], n[2], 0, n[0], h->Vax[0], true, nullptr, s));
   HIPCHK(h, launch_axis(a, b, B, n[0], n[1], n[2], 1, n[1], h->Vax[1], true, nullptr, s));
@@ -549,6 +561,8 @@ rpa_status end_stats(rpa_ctx* h, hipStream_t s, rpa_stats* st, double t0, long l
   return RPA_OK;
 }
 
+// Per-axis interpolation matrices of (kind, stride): padded for the fused
+// transforms, else row-major (n_fine x n_coarse).
 rpa_status interp_setup(rpa_ctx* h, int kind, int g, hipStream_t s) {
   if (h->interp_kind == kind && h->interp_stride == g) return RPA_OK;
   std::vector<double> all;
@@ -557,8 +571,14 @@ rpa_status interp_setup(rpa_ctx* h, int kind, int g, hipStream_t s) {
     std::vector<double> M;
     interp_matrix(kind, h->n[d], g, M);
     off[d] = all.size();
-    all.insert(all.end(), M.begin(), M.end());
+    if (h->fused) {
+      all.resize(off[d] + transform_elems(h->n[d], h->n[d] / g));
+      pad_k_major(M.data(), h->n[d], h->n[d] / g, false, all.data() + off[d]);
+    } else {
+      all.insert(all.end(), M.begin(), M.end());
+    }
   }
+  h->interp_kind = -1;     // the old matrices are overwritten below
   ENSURE(h, h->interp_m, all.size() * sizeof(double));
   HIPCHK(h, hipMemcpyAsync(h->interp_m.p, all.data(), all.size() * sizeof(double),
                            hipMemcpyHostToDevice, s));
@@ -572,7 +592,6 @@ rpa_status interp_setup(rpa_ctx* h, int kind, int g, hipStream_t s) {
 rpa_status do_interpolate(rpa_ctx* h, int kind, int g, int nf, const double* coarse, double* fine,
                           hipStream_t s) {
   const int* n = h->n;
-  const long long Nc = h->N / ((long long)g * g * g);
   if (g == 1) {
     HIPCHK(h, hipMemcpyAsync(fine, coarse, (size_t)nf * h->N * sizeof(double),
                              hipMemcpyDeviceToDevice, s));
@@ -582,15 +601,21 @@ rpa_status do_interpolate(rpa_ctx* h, int kind, int g, int nf, const double* coa
   if (st != RPA_OK) return st;
   const int nc[3] = {n[0] / g, n[1] / g, n[2] / g};
   ENSURE(h, h->tmpA, (size_t)nf * n[0] * nc[1] * nc[2] * sizeof(double));
-  ENSURE(h, h->vtmp, (size_t)nf * n[0] * n[1] * nc[2] * sizeof(double));
   const double* M = P<double>(h->interp_m);
+  if (h->fused) {
+    // x on the coarse planes, then y and z of every fine plane
+    HIPCHK(h, launch_cols(coarse, P<double>(h->tmpA), nf, nc[0], n[0], nc[1] * nc[2], M + h->interp_dims[0], s));
+    HIPCHK(h, launch_planes(P<double>(h->tmpA), fine, (long long)nf * n[0], nc[1], nc[2], n[1], n[2],
+                            M + h->interp_dims[1], M + h->interp_dims[2], s));
+    return RPA_OK;
+  }
+  ENSURE(h, h->vtmp, (size_t)nf * n[0] * n[1] * nc[2] * sizeof(double));
   HIPCHK(h, launch_axis(coarse, P<double>(h->tmpA), nf, nc[0], nc[1], nc[2], 0, n[0],
                         M + h->interp_dims[0], false, nullptr, s));
   HIPCHK(h, launch_axis(P<double>(h->tmpA), P<double>(h->vtmp), nf, n[0], nc[1], nc[2], 1, n[1],
                         M + h->interp_dims[1], false, nullptr, s));
   HIPCHK(h, launch_axis(P<double>(h->vtmp), fine, nf, n[0], n[1], nc[2], 2, n[2],
                         M + h->interp_dims[2], false, nullptr, s));
-  (void)Nc;
   return RPA_OK;
 }
 
@@ -768,7 +793,7 @@ uint64_t lanczos_workspace_bytes(const rpa_setup_params& p, int B, int n_lanczos
   const bool refine = p.precision == RPA_FP32_REFINE;
   // Lanczos basis, start/iteration vectors, recurrence scalars and bookkeeping
   uint64_t bytes = m * b * N * 8 + b * N * 8 + 2 * b * m * 8 + 2 * b * 4 + 4 * b * 8 + 64 + 16;
-  bytes += 2 * b * N * 8;                                   // nu^1/2 transform buffers
+  bytes += (transform_fits(p.n[0], p.n[1], p.n[2]) ? 1 : 2) * b * N * 8;   // nu^1/2 transform buffers
   const uint64_t ngal = nocc + (uint64_t)std::max(0, p.n_extra);
   bytes += b * (uint64_t)gram_chunks((long long)N) * ngal * nocc * 8 + b * ngal * nocc * 16;
   bytes += items * N * 16;                                  // Sternheimer solutions (FP64)
@@ -938,8 +963,13 @@ rpa_status rpa_setup(const rpa_setup_params* p, void* stream, rpa_handle* out) {
       !alloc((void**)&h->eps_d, h->ngal * sizeof(double)) ||
       !alloc((void**)&h->s_half, N * sizeof(double)) || !alloc((void**)&h->s_full, N * sizeof(double)))
     return fail(RPA_E_OOM);
-  for (int d = 0; d < 3; ++d)
-    if (!alloc((void**)&h->Vax[d], (size_t)h->n[d] * h->n[d] * sizeof(double))) return fail(RPA_E_OOM);
+  h->fused = transform_fits(h->n[0], h->n[1], h->n[2]);
+  for (int d = 0; d < 3; ++d) {
+    const size_t padded = transform_elems(h->n[d], h->n[d]) * sizeof(double);
+    if (h->fused ? !alloc((void**)&h->Tf[d], padded) || !alloc((void**)&h->Ti[d], padded)
+                 : !alloc((void**)&h->Vax[d], (size_t)h->n[d] * h->n[d] * sizeof(double)))
+      return fail(RPA_E_OOM);
+  }
   h->eps_h.assign(p->eps, p->eps + h->nocc);
 
   // nonlocal projector layouts
@@ -1048,8 +1078,22 @@ rpa_status rpa_setup(const rpa_setup_params* p, void* stream, rpa_handle* out) {
     e = hipMemcpyAsync(h->eps_d + h->nocc, p->eps_extra, p->n_extra * sizeof(double), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(h->s_half, sh.data(), N * sizeof(double), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(h->s_full, sf.data(), N * sizeof(double), hipMemcpyHostToDevice, s);
-  for (int d = 0; d < 3 && e == hipSuccess; ++d)
-    e = hipMemcpyAsync(h->Vax[d], V[d].data(), V[d].size() * sizeof(double), hipMemcpyHostToDevice, s);
+  std::vector<double> pad[3][2];
+  for (int d = 0; d < 3 && e == hipSuccess; ++d) {
+    const int n = h->n[d];
+    if (!h->fused) {
+      e = hipMemcpyAsync(h->Vax[d], V[d].data(), V[d].size() * sizeof(double), hipMemcpyHostToDevice, s);
+      continue;
+    }
+    // V is [grid][mode]: forward (grid -> mode) is V itself in k-major order, inverse its transpose
+    for (int k = 0; k < 2; ++k) {
+      pad[d][k].resize(transform_elems(n, n));
+      pad_k_major(V[d].data(), n, n, k == 0, pad[d][k].data());
+      if (e == hipSuccess)
+        e = hipMemcpyAsync(k == 0 ? h->Tf[d] : h->Ti[d], pad[d][k].data(), pad[d][k].size() * sizeof(double),
+                           hipMemcpyHostToDevice, s);
+    }
+  }
   for (size_t k = 0; k < nl_up.size() && e == hipSuccess; ++k)
     if (nl_up[k].bytes)
       e = hipMemcpyAsync(nl_up[k].dst, nl_up[k].src, nl_up[k].bytes, hipMemcpyHostToDevice, s);
@@ -1079,7 +1123,7 @@ rpa_status rpa_destroy(rpa_handle h) {
   for (void* m : h->nl_mem) fr(m);
   fr(h->prec_mem);
   fr(h->nlcoef.p);
-  for (int d = 0; d < 3; ++d) fr(h->Vax[d]);
+  for (int d = 0; d < 3; ++d) { fr(h->Vax[d]); fr(h->Tf[d]); fr(h->Ti[d]); }
   DevBuf* bufs[] = {&h->x64, &h->slots, &h->u64, &h->racc, &h->vtmp, &h->tmpA, &h->Q, &h->alpha,
                     &h->beta, &h->mlen, &h->active, &h->order, &h->iters, &h->cycles, &h->status,
                     &h->counter, &h->stats, &h->omega_b, &h->pos_b, &h->idx_b, &h->gpart, &h->G,
@@ -1225,7 +1269,7 @@ ScratchLayout scratch_layout(rpa_ctx* h, int B, bool symmetrized) {
   add(h->omega_b, b * sizeof(double));
   if (symmetrized) {
     add(h->tmpA, b * N * sizeof(double));
-    add(h->vtmp, b * N * sizeof(double));
+    if (!h->fused) add(h->vtmp, b * N * sizeof(double));
   }
   add(h->gpart, b * (size_t)gram_chunks(h->N) * h->ngal * nocc * sizeof(double));
   add(h->G, b * (size_t)h->ngal * nocc * sizeof(double2));
@@ -1670,15 +1714,37 @@ rpa_status rpa_energy_from_coarse(rpa_handle h, int32_t n_omega, const double* w
   ARG_CHECK(kind != RPA_INTERP_NONE || stride == 1, "RPA_INTERP_NONE requires stride 1");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const long long N = h->N;
-  ENSURE(h, h->dhat, (size_t)n_omega * N * sizeof(double));
-  rpa_status r = do_interpolate(h, kind, stride, n_omega, d_coarse, P<double>(h->dhat), s);
-  if (r != RPA_OK) return r;
-  const int nblk = 256;
-  ENSURE(h, h->partials, nblk * sizeof(double) + (size_t)n_omega * sizeof(double));
-  double* wdev = P<double>(h->partials) + nblk;
-  HIPCHK(h, hipMemcpyAsync(wdev, weight, n_omega * sizeof(double), hipMemcpyHostToDevice, s));
-  HIPCHK(h, launch_weighted_sum(P<double>(h->dhat), wdev, n_omega, N, 1.0 / (2.0 * M_PI * h->dV),
-                                e_fine, P<double>(h->partials), nblk, s));
+  const double scale_fine = 1.0 / (2.0 * M_PI * h->dV);
+  int nblk = 256;
+  if (h->fused && stride > 1 && n_omega <= kMaxFieldWeights) {
+    // interpolation is linear: the frequencies are summed on the coarse set
+    // (in the x pass) and one field is interpolated, summed as it is written
+    rpa_status r = interp_setup(h, kind, stride, s);
+    if (r != RPA_OK) return r;
+    const int* n = h->n;
+    const int nc[3] = {n[0] / stride, n[1] / stride, n[2] / stride};
+    const double* M = P<double>(h->interp_m);
+    nblk = n[0];
+    ENSURE(h, h->tmpA, (size_t)n[0] * nc[1] * nc[2] * sizeof(double));
+    ENSURE(h, h->partials, (size_t)nblk * sizeof(double));
+    HIPCHK(h, launch_cols_fields(d_coarse, P<double>(h->tmpA), n_omega, weight, nc[0], n[0], nc[1] * nc[2],
+                                 M + h->interp_dims[0], s));
+    HIPCHK(h, launch_planes_energy(P<double>(h->tmpA), e_fine, n[0], nc[1], nc[2], n[1], n[2],
+                                   M + h->interp_dims[1], M + h->interp_dims[2], scale_fine,
+                                   P<double>(h->partials), s));
+  } else {
+    const double* dhat = d_coarse;
+    if (stride > 1) {
+      ENSURE(h, h->dhat, (size_t)n_omega * N * sizeof(double));
+      rpa_status r = do_interpolate(h, kind, stride, n_omega, d_coarse, P<double>(h->dhat), s);
+      if (r != RPA_OK) return r;
+      dhat = P<double>(h->dhat);
+    }
+    ENSURE(h, h->partials, nblk * sizeof(double) + (size_t)n_omega * sizeof(double));
+    double* wdev = P<double>(h->partials) + nblk;
+    HIPCHK(h, hipMemcpyAsync(wdev, weight, n_omega * sizeof(double), hipMemcpyHostToDevice, s));
+    HIPCHK(h, launch_weighted_sum(dhat, wdev, n_omega, N, scale_fine, e_fine, P<double>(h->partials), nblk, s));
+  }
   std::vector<double> part(nblk);
   HIPCHK(h, hipMemcpyAsync(part.data(), h->partials.p, nblk * sizeof(double), hipMemcpyDeviceToHost, s));
   HIPCHK(h, hipStreamSynchronize(s));

@@ -163,15 +163,45 @@ hipError_t launch_fill_i(int* p, int v, long long n, hipStream_t s);
 hipError_t launch_d2f(const double* a, float* b, long long n, hipStream_t s);
 hipError_t launch_set_onehot(double* q, long long stride, const long long* idx, int B, hipStream_t s);
 
-// out = M applied along `axis` of a batch of 3D arrays.
+// Separable transforms (transform.hip).  The matrices are stored k-major,
+// zero-padded to multiples of 16: W[k * transform_pad(n_out) + o].
+constexpr int kMaxTransformDim = 128;    // largest dimension of the fused transforms
+constexpr int kMaxFieldWeights = 64;     // most fields summed by launch_cols_fields
+inline int transform_pad(int n) { return (n + 15) & ~15; }
+inline size_t transform_elems(int n_out, int n_in) { return (size_t)transform_pad(n_out) * transform_pad(n_in); }
+// dst = M padded; M is (n_out x n_in) row-major, or (n_in x n_out) with trans
+void pad_k_major(const double* M, int n_out, int n_in, bool trans, double* dst);
+bool transform_fits(int d0, int d1, int d2);
+// out[p] (ni x nj) = L^T in[p] (na x nb) R for every plane p, L: na -> ni, R: nb -> nj
+hipError_t launch_planes(const double* in, double* out, long long planes, int na, int nb, int ni, int nj,
+                         const double* L, const double* R, hipStream_t s);
+// the same, written times scale_fine (e_fine nullable), and partials[p] = sum of plane p
+hipError_t launch_planes_energy(const double* in, double* e_fine, long long planes, int na, int nb, int ni, int nj,
+                                const double* L, const double* R, double scale_fine, double* partials,
+                                hipStream_t s);
+// first-axis transform of B arrays (n_in x ncol) -> (n_out x ncol)
+hipError_t launch_cols(const double* in, double* out, int B, int n_in, int n_out, int ncol, const double* A,
+                       hipStream_t s);
+// ... of the one array sum_f w[f] in[f] (w: host)
+hipError_t launch_cols_fields(const double* in, double* out, int n_fields, const double* w, int n_in, int n_out,
+                              int ncol, const double* A, hipStream_t s);
+// forward first-axis transform, times diag[row][column], inverse; in place allowed
+hipError_t launch_cols_scale(const double* in, double* out, int B, int n, int ncol, const double* fwd,
+                             const double* inv, const double* diag, hipStream_t s);
+// the same for planar complex vectors with the diagonal 1 / (kin[row][column] + sigma_b)
+hipError_t launch_cols_kinetic(const double* in, double* out, int nvec, int n, int ncol, const double* fwd,
+                               const double* inv, const double* kin, const double* sig_re, const double* sig_im,
+                               hipStream_t s);
+
+// Per-axis form for larger dimensions: out = M applied along `axis` of a batch of 3D arrays.
 // in dims (B, d0, d1, d2); M is (n_out x n_in) row-major, n_in = d[axis];
 // out dims equal in dims with d[axis] replaced by n_out.  trans: use M^T
 // (then M is (n_in x n_out)).  scale (nullable) multiplies the output
 // elementwise (length = output 3D size, broadcast over the batch).
-hipError_t launch_kin_scale(double* a, const double* kin, const double* sig_re,
-                            const double* sig_im, int B, long long N, hipStream_t s);
 hipError_t launch_axis(const double* in, double* out, int B, int d0, int d1, int d2, int axis,
                        int n_out, const double* M, bool trans, const double* scale, hipStream_t s);
+hipError_t launch_kin_scale(double* a, const double* kin, const double* sig_re,
+                            const double* sig_im, int B, long long N, hipStream_t s);
 
 hipError_t launch_gram(const double* psi, const double* u, int B, int n_occ, int ng, long long N,
                        int n_chunks, double* part, hipStream_t s);

@@ -1,6 +1,5 @@
-// Kernels around the Sternheimer solve: Kronecker-form nu^1/2 and the
-// separable interpolants (per-axis transforms), Galerkin initial guess,
-// density accumulation, Lanczos recurrence with full reorthogonalisation,
+// Kernels around the Sternheimer solve: Galerkin initial guess, density
+// accumulation, Lanczos recurrence with full reorthogonalisation,
 // tridiagonal Gauss quadrature and frequency integration.
 #include "internal.h"
 
@@ -27,67 +26,6 @@ __global__ void k_d2f(const double* __restrict__ a, float* __restrict__ b, long 
 __global__ void k_set_onehot(double* q, long long stride, const long long* idx, int B) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b < B) q[(size_t)b * stride + idx[b]] = 1.0;
-}
-
-// ---------------------------------------------------------------------------
-// Per-axis transform: out[b, ..., i, ...] = sum_k M(i, k) in[b, ..., k, ...]
-__global__ void k_axis(const double* __restrict__ in, double* __restrict__ out, int B, int d0,
-                       int d1, int d2, int axis, int n_out, const double* __restrict__ M,
-                       int trans, const double* __restrict__ scale) {
-  int od0 = d0, od1 = d1, od2 = d2;
-  if (axis == 0) od0 = n_out; else if (axis == 1) od1 = n_out; else od2 = n_out;
-  const long long osz = (long long)od0 * od1 * od2;
-  const long long isz = (long long)d0 * d1 * d2;
-  const long long total = osz * B;
-  const int n_in = axis == 0 ? d0 : (axis == 1 ? d1 : d2);
-  for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t < total;
-       t += (long long)gridDim.x * blockDim.x) {
-    const long long b = t / osz;
-    const long long o = t - b * osz;
-    const int i2 = (int)(o % od2);
-    const long long o01 = o / od2;
-    const int i1 = (int)(o01 % od1);
-    const int i0 = (int)(o01 / od1);
-    const double* src = in + b * isz;
-    long long base, stride;
-    int i;
-    if (axis == 0) { i = i0; base = (long long)i1 * d2 + i2; stride = (long long)d1 * d2; }
-    else if (axis == 1) { i = i1; base = (long long)i0 * d1 * d2 + i2; stride = d2; }
-    else { i = i2; base = ((long long)i0 * d1 + i1) * d2; stride = 1; }
-    double acc = 0.0;
-    if (trans) {
-      for (int k = 0; k < n_in; ++k) acc += M[(long long)k * n_out + i] * src[base + k * stride];
-    } else {
-      const double* row = M + (long long)i * n_in;
-      for (int k = 0; k < n_in; ++k) acc += row[k] * src[base + k * stride];
-    }
-    if (scale) acc *= scale[o];
-    out[t] = acc;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Complex diagonal solve in the eigenbasis of the FD Laplacian, the middle
-// step of the shifted kinetic preconditioner: vector b is stored planar
-// (N real parts, then N imaginary parts) and each mode o is divided by
-// kin[o] + sigma_b, kin >= 0 the kinetic eigenvalue, Re(sigma_b) > 0.
-__global__ void k_kin_scale(double* __restrict__ a, const double* __restrict__ kin,
-                            const double* __restrict__ sig_re, const double* __restrict__ sig_im,
-                            int B, long long N) {
-  const long long total = (long long)B * N;
-  for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t < total;
-       t += (long long)gridDim.x * blockDim.x) {
-    const long long b = t / N;
-    const long long o = t - b * N;
-    double* re = a + b * 2 * N;
-    double* im = re + N;
-    const double dr = kin[o] + sig_re[b];
-    const double di = sig_im[b];
-    const double den = dr * dr + di * di;
-    const double xr = re[o], xi = im[o];
-    re[o] = (xr * dr + xi * di) / den;
-    im[o] = (xi * dr - xr * di) / den;
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -496,22 +434,6 @@ hipError_t launch_set_onehot(double* q, long long stride, const long long* idx, 
   return hipGetLastError();
 }
 
-hipError_t launch_axis(const double* in, double* out, int B, int d0, int d1, int d2, int axis,
-                       int n_out, const double* M, bool trans, const double* scale, hipStream_t s) {
-  long long osz = (long long)d0 * d1 * d2;
-  const int nin = axis == 0 ? d0 : (axis == 1 ? d1 : d2);
-  osz = osz / nin * n_out;
-  hipLaunchKernelGGL(k_axis, dim3(grid_for(osz * B, 256)), dim3(256), 0, s, in, out, B, d0, d1,
-                     d2, axis, n_out, M, trans ? 1 : 0, scale);
-  return hipGetLastError();
-}
-
-hipError_t launch_kin_scale(double* a, const double* kin, const double* sig_re,
-                            const double* sig_im, int B, long long N, hipStream_t s) {
-  hipLaunchKernelGGL(k_kin_scale, dim3(grid_for((long long)B * N, 256)), dim3(256), 0, s, a, kin,
-                     sig_re, sig_im, B, N);
-  return hipGetLastError();
-}
 hipError_t launch_gram(const double* psi, const double* u, int B, int n_occ, int ng, long long N,
                        int n_chunks, double* part, hipStream_t s) {
   const int ntm = (ng + GT - 1) / GT, ntn = (n_occ + GT - 1) / GT;

@@ -1,10 +1,11 @@
 // Shifted kinetic preconditioner (rpa_kinetic_precond_* in rpa.h).
 //
 // M = -1/2 Lap_h + sigma is inverted exactly in the eigenbasis of the FD
-// Laplacian, which factorises per axis: forward transforms along x, y, z
-// (k_axis with the transposed 1D basis), a complex divide by kin + sigma per
-// mode (k_kin_scale), and the inverse transforms.  A plan owns the three 1D
-// bases, the kinetic diagonal and its transform workspaces; it is separate
+// Laplacian, which factorises per axis: y and z forward, then x forward, a
+// complex divide by kin + sigma per mode and x inverse in one kernel, then y
+// and z inverse (transform.hip); one axis per launch on grids beyond
+// kMaxTransformDim.  A plan owns the three 1D bases, the kinetic diagonal and
+// its transform workspaces; it is separate
 // from the problem handle so that applying it leaves the handle untouched.
 // Errors are reported by status only.
 #include "rpa.h"
@@ -16,7 +17,9 @@
 struct rpa_kinetic_precond_s {
   int n[3] = {0, 0, 0};
   long long N = 0;
-  double* V[3] = {nullptr, nullptr, nullptr};  // [grid point][mode], orthonormal
+  bool fused = false;
+  double* V[3] = {nullptr, nullptr, nullptr};  // [grid point][mode], orthonormal (fused: padded, forward)
+  double* VT[3] = {nullptr, nullptr, nullptr}; // fused: padded, inverse
   double* kin = nullptr;                       // -1/2 (lam_x + lam_y + lam_z) per mode
   double* ws[2] = {nullptr, nullptr};          // transform workspaces
   size_t ws_bytes = 0;
@@ -72,6 +75,7 @@ void fourier_basis(int n, double h, const double* w, std::vector<double>& V,
 void release(rpa_kinetic_precond p) {
   if (!p) return;
   for (double* v : p->V) if (v) (void)hipFree(v);
+  for (double* v : p->VT) if (v) (void)hipFree(v);
   for (double* v : p->ws) if (v) (void)hipFree(v);
   if (p->kin) (void)hipFree(p->kin);
   if (p->sig) (void)hipFree(p->sig);
@@ -101,14 +105,27 @@ rpa_status rpa_kinetic_precond_create(const int32_t* n, const double* L, void* s
     for (int j = 0; j < n[1]; ++j)
       for (int k = 0; k < n[2]; ++k)
         kin[((size_t)i * n[1] + j) * n[2] + k] = -0.5 * (lam[0][i] + lam[1][j] + lam[2][k]);
+  p->fused = rpa::transform_fits(n[0], n[1], n[2]);
+  std::vector<double> VT[3];
+  for (int d = 0; d < 3 && p->fused; ++d) {
+    std::vector<double> fwd(rpa::transform_elems(n[d], n[d]));
+    VT[d].resize(fwd.size());
+    rpa::pad_k_major(V[d].data(), n[d], n[d], true, fwd.data());
+    rpa::pad_k_major(V[d].data(), n[d], n[d], false, VT[d].data());
+    V[d].swap(fwd);
+  }
   bool ok = hipMalloc((void**)&p->kin, (size_t)p->N * sizeof(double)) == hipSuccess;
-  for (int d = 0; d < 3 && ok; ++d)
+  for (int d = 0; d < 3 && ok; ++d) {
     ok = hipMalloc((void**)&p->V[d], V[d].size() * sizeof(double)) == hipSuccess;
+    if (ok && p->fused) ok = hipMalloc((void**)&p->VT[d], VT[d].size() * sizeof(double)) == hipSuccess;
+  }
   if (!ok) { (void)hipGetLastError(); release(p); return RPA_E_OOM; }
   hipError_t e = hipMemcpyAsync(p->kin, kin.data(), kin.size() * sizeof(double),
                                 hipMemcpyHostToDevice, s);
   for (int d = 0; d < 3 && e == hipSuccess; ++d)
     e = hipMemcpyAsync(p->V[d], V[d].data(), V[d].size() * sizeof(double), hipMemcpyHostToDevice, s);
+  for (int d = 0; d < 3 && p->fused && e == hipSuccess; ++d)
+    e = hipMemcpyAsync(p->VT[d], VT[d].data(), VT[d].size() * sizeof(double), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host tables go out of scope
   if (e != hipSuccess) { (void)hipGetLastError(); release(p); return RPA_E_HIP; }
   *out = p;
@@ -129,8 +146,8 @@ rpa_status rpa_kinetic_precond_apply(rpa_kinetic_precond p, int32_t nvec, const 
     // hipFree waits for the device, so no earlier apply still uses the old buffers
     for (double*& v : p->ws) { if (v) (void)hipFree(v); v = nullptr; }
     p->ws_bytes = 0;
-    for (double*& v : p->ws)
-      if (hipMalloc((void**)&v, bytes) != hipSuccess) { (void)hipGetLastError(); return RPA_E_OOM; }
+    for (int k = 0; k < (p->fused ? 1 : 2); ++k)
+      if (hipMalloc((void**)&p->ws[k], bytes) != hipSuccess) { (void)hipGetLastError(); return RPA_E_OOM; }
     p->ws_bytes = bytes;
   }
   if (nvec > p->sig_cap) {
@@ -144,11 +161,20 @@ rpa_status rpa_kinetic_precond_apply(rpa_kinetic_precond p, int32_t nvec, const 
     p->sig_cap = nvec;
   }
   double* a = p->ws[0];
-  double* b = p->ws[1];
   const int* n = p->n;
   hipError_t e = hipMemcpyAsync(p->sig, sigma_re, nvec * sizeof(double), hipMemcpyHostToDevice, s);
   if (e == hipSuccess)
     e = hipMemcpyAsync(p->sig + nvec, sigma_im, nvec * sizeof(double), hipMemcpyHostToDevice, s);
+  if (p->fused) {
+    const int yz = n[1] * n[2];
+    if (e == hipSuccess) e = rpa::launch_planes(x, a, (long long)B * n[0], n[1], n[2], n[1], n[2], p->V[1], p->V[2], s);
+    if (e == hipSuccess)
+      e = rpa::launch_cols_kinetic(a, a, nvec, n[0], yz, p->V[0], p->VT[0], p->kin, p->sig, p->sig + nvec, s);
+    if (e == hipSuccess) e = rpa::launch_planes(a, y, (long long)B * n[0], n[1], n[2], n[1], n[2], p->VT[1], p->VT[2], s);
+    if (e != hipSuccess) { (void)hipGetLastError(); return RPA_E_HIP; }
+    return RPA_OK;
+  }
+  double* b = p->ws[1];
   if (e == hipSuccess) e = rpa::launch_axis(x, a, B, n[0], n[1], n[2], 0, n[0], p->V[0], true, nullptr, s);
   if (e == hipSuccess) e = rpa::launch_axis(a, b, B, n[0], n[1], n[2], 1, n[1], p->V[1], true, nullptr, s);
   if (e == hipSuccess) e = rpa::launch_axis(b, a, B, n[0], n[1], n[2], 2, n[2], p->V[2], true, nullptr, s);
