@@ -59,12 +59,27 @@ __global__ void __launch_bounds__(256) k_nl_add(NlArgs nl, long long N, const vo
 bool geom_supported(const Geom& g) { return g.nz + 2 * R <= 128; }
 
 size_t cocg_shmem_bytes(const Geom& g, int block, bool fp32_refine, int n_proj) {
-  return lds_plane_bytes(g, pitch_for(g), fp32_refine) + red_bytes(block) +
+  return lds_plane_bytes(g, pitch_for(g), fp32_refine) + red_bytes(g.prec && g.pc_block ? g.pc_block : block) +
          (size_t)n_proj * sizeof(double2);
+}
+
+void cocg_pc_shape(Geom& g, int block, int n_proj) {
+  // kPcBlock threads keep the memory pipes busy whatever the stencil tile is;
+  // the tile's own workgroup only where the larger reduction buffer would not fit
+  for (const int b : {kPcBlock, block}) {
+    const size_t rest = red_bytes(b) + (size_t)n_proj * sizeof(double2) + 256;
+    const size_t lds = 160 * 1024 > rest ? 160 * 1024 - rest : 0;
+    g.pc_block = b;
+    g.pc_planes32 = pc_planes<float>(g, b, lds);
+    g.pc_planes64 = pc_planes<double>(g, b, lds);
+    if (cocg_shmem_bytes(g, b, true, n_proj) <= 160 * 1024 && cocg_shmem_bytes(g, b, false, n_proj) <= 160 * 1024)
+      return;
+  }
 }
 
 int cocg_blocks_per_cu(const Geom& g, int block, bool fp32_refine, int n_proj) {
   const size_t shmem = cocg_shmem_bytes(g, block, fp32_refine, n_proj);
+  if (g.prec && g.pc_block) block = g.pc_block;
   const int m = tile_mode(g, block);
   int nb = 0;
   const void* fn = n_proj > 0 ? cocg_nl_fn(fp32_refine, m, pitch_for(g), g.prec != 0)
@@ -79,10 +94,8 @@ int cocg_prec_regs(const Geom& g, int block) { return prec_regs(g, block); }
 int cocg_prec_regs_max() { return kPrecRegs; }
 
 long long cocg_slot_bytes(const Geom& g, bool fp32_refine) {
-  // r, q, p_old, p_new (+ the FP32 correction d); preconditioned: + z and a transform buffer
-  const long long extra = g.prec ? 2 : 0;
-  return fp32_refine ? (5LL + extra) * g.N * (long long)sizeof(float2)
-                     : (4LL + extra) * g.N * (long long)sizeof(double2);
+  // r, q, p_old, p_new (+ the FP32 correction d); preconditioned: one p and a transform buffer
+  return fp32_refine ? 5LL * g.N * (long long)sizeof(float2) : 4LL * g.N * (long long)sizeof(double2);
 }
 
 namespace {
@@ -113,6 +126,7 @@ hipError_t launch_ht(const Geom& g, const StencilCoef<T>& cf, const T* v, const 
 
 hipError_t launch_cocg(const CocgArgs& a, bool fp32_refine, int grid, int block, size_t shmem,
                        hipStream_t s) {
+  if (a.prec) block = a.g.pc_block;
   if (a.nl.n_proj > 0) return launch_cocg_nl(a, fp32_refine, grid, block, shmem, s);
   if (a.prec) return launch_cocg_pc(a, fp32_refine, grid, block, shmem, s);
   return launch_cocg_t<0>(a, fp32_refine, grid, block, shmem, s);

@@ -25,6 +25,8 @@
 //    b = -psi_n (.) u is formed on the fly in FP64 and never stored.
 #pragma once
 
+#include <type_traits>
+
 #include "internal.h"
 
 namespace rpa {
@@ -512,9 +514,12 @@ __host__ __device__ inline size_t lds_plane_bytes(const Geom& g, int pitch, bool
   const size_t light = 2 * rows_light * g.nz * sizeof(double2);
   size_t b = main > light ? main : light;
   if (g.prec) {
-    // the preconditioner's planes (FP64 for the FP64 solver, which the FP32
-    // path also launches for the systems it hands over)
-    const size_t pb = prec_lds_bytes(g, fp32_iter ? sizeof(float) : sizeof(double));
+    // the preconditioner's bases and planes (FP64 for the FP64 solver, which
+    // the FP32 path also launches for the systems it hands over); without a
+    // launch shape yet, the bound that decides whether a problem is accepted
+    const size_t elem = fp32_iter ? sizeof(float) : sizeof(double);
+    const int planes = fp32_iter ? g.pc_planes32 : g.pc_planes64;
+    const size_t pb = planes ? pc_lds_bytes(g, elem, planes) : prec_lds_bytes(g, elem);
     b = b > pb ? b : pb;
   }
   return (b + 255) & ~(size_t)255;
@@ -764,6 +769,25 @@ __device__ __forceinline__ void fold_sweep(long long N, double2* x, const float2
   }
 }
 
+// x += d (has_d) + alpha p (p non-null), the sum formed in the iteration's precision
+template <typename T>
+__device__ __forceinline__ void fold_pair(long long N, double2* x, const typename V2<T>::t* d, bool has_d,
+                                          const typename V2<T>::t* p, T ar, T ai) {
+  typedef typename V2<T>::t T2;
+  for (long long i = threadIdx.x; i < N; i += blockDim.x) {
+    T2 e = has_d ? d[i] : zero2<T2>();
+    if (p) {
+      const T2 pv = p[i];
+      e.x += ar * pv.x - ai * pv.y;
+      e.y += ar * pv.y + ai * pv.x;
+    }
+    double2 w = x[i];
+    w.x += (double)e.x;
+    w.y += (double)e.y;
+    x[i] = w;
+  }
+}
+
 __device__ __forceinline__ void zero_sweep(long long N, double2* x) {
   for (long long i = threadIdx.x; i < N; i += blockDim.x) x[i] = make_double2(0.0, 0.0);
 }
@@ -808,7 +832,7 @@ __device__ __forceinline__ void record(const CocgArgs& a, int s, int its, int cy
 
 // ---------------------------------------------------------------------------
 // One system, FP64 throughout.
-template <bool FULL, int HS, int PITCH, bool NL, bool PC>
+template <bool FULL, int HS, int PITCH, bool NL>
 __device__ void solve_fp64(const CocgArgs& a, int s, char* smem, double* red, char* nlc) {
   const Geom& g = a.g;
   const long long N = g.N;
@@ -823,12 +847,6 @@ __device__ void solve_fp64(const CocgArgs& a, int s, char* smem, double* red, ch
   double2* x = a.x64 + (size_t)s * N;
   const double eps = a.eps[n];
   const double om = a.omega[b];
-  // preconditioned COCG: z = M^-1 r is the stencil operand and rho = r^T z
-  constexpr bool pc = PC;
-  double2* z = pc ? ws + 4 * N : r;
-  double2* tt = ws + 5 * N;
-  const double psr = pc ? fmax(a.prec->vbar - eps, a.prec->floor) : 0.0, psi = -om;
-
   double2* coef = reinterpret_cast<double2*>(nlc);
   NlPoint<double> nlp{a.nl.pm_ptr, a.nl.pm_proj, a.nl.pm_v64, coef};
 
@@ -854,15 +872,6 @@ __device__ void solve_fp64(const CocgArgs& a, int s, char* smem, double* red, ch
     zero_sweep(N, x);
   } else {
     const double thr = a.tol * bnorm;
-    if constexpr (PC) {
-      if (rnorm > thr) {
-        double q2[2] = {0.0, 0.0};
-        precond_apply<double>(g, a.prec, r, tt, z, psr, psi, smem, q2[0], q2[1]);
-        block_reduce<2>(q2, red);
-        rho_r = q2[0];
-        rho_i = q2[1];
-      }
-    }
     double br = 0.0, bi = 0.0;
     bool first = true;
     double2* pold = pa;
@@ -870,7 +879,7 @@ __device__ void solve_fp64(const CocgArgs& a, int s, char* smem, double* red, ch
     while (rnorm > thr) {
       if (its >= a.maxit) { status = 1; break; }
       ApplyPol<double> ap;
-      ap.r = z; ap.pold = pold; ap.pnew = pnew; ap.q = q; ap.v = a.v64;
+      ap.r = r; ap.pold = pold; ap.pnew = pnew; ap.q = q; ap.v = a.v64;
       ap.c0 = a.c64.c0; ap.eps = eps; ap.om = om; ap.br = br; ap.bi = bi; ap.first = first;
       ap.mu_re = ap.mu_im = 0.0;
       march<double, FULL, HS, PITCH>(g, a.c64, ap, lds, 0, g.ntiles);
@@ -886,16 +895,6 @@ __device__ void solve_fp64(const CocgArgs& a, int s, char* smem, double* red, ch
       block_reduce<3>(u3, red);
       ++its;
       rnorm = sqrt(u3[0]);
-      if constexpr (PC) {
-        if (rnorm > thr) {
-          double q2[2] = {0.0, 0.0};
-          precond_apply<double>(g, a.prec, r, tt, z, psr, psi, smem, q2[0], q2[1]);
-          block_reduce<2>(q2, red);
-          u3[1] = q2[0];
-          u3[2] = q2[1];
-          if (fabs(u3[1]) + fabs(u3[2]) < 1e-300) { status = 2; break; }
-        }
-      }
       cdiv(u3[1], u3[2], rho_r, rho_i, br, bi);
       rho_r = u3[1]; rho_i = u3[2];
       first = false;
@@ -912,7 +911,7 @@ __device__ void solve_fp64(const CocgArgs& a, int s, char* smem, double* red, ch
 // FP32 correction d is folded into the FP64 solution and the residual is
 // replaced by the true FP64 residual b - A x64.  Convergence is declared on
 // the FP64 residual only.
-template <bool FULL, int HS, int PITCH, bool NL, bool PC>
+template <bool FULL, int HS, int PITCH, bool NL>
 __device__ void solve_refine(const CocgArgs& a, int s, char* smem, double* red, char* nlc) {
   const Geom& g = a.g;
   const long long N = g.N;
@@ -927,12 +926,6 @@ __device__ void solve_refine(const CocgArgs& a, int s, char* smem, double* red, 
   double2* x = a.x64 + (size_t)s * N;
   const double eps = a.eps[n];
   const double om = a.omega[b];
-  // preconditioned COCG: z = M^-1 r is the stencil operand and rho = r^T z
-  constexpr bool pc = PC;
-  float2* z = pc ? ws + 5 * N : r;
-  float2* tt = ws + 6 * N;
-  const float psr = pc ? (float)fmax(a.prec->vbar - eps, a.prec->floor) : 0.f, psi = (float)(-om);
-
   // nonlocal coefficients: FP64 for the residual sweeps, FP32 for the inner
   // iterations (same LDS region, never live at the same time)
   double2* coef64 = reinterpret_cast<double2*>(nlc);
@@ -973,25 +966,16 @@ __device__ void solve_refine(const CocgArgs& a, int s, char* smem, double* red, 
     bool exact_q = false;          // q = A p directly (after a residual replacement)
     float2* pold = pa;
     float2* pnew = pb;
-    if constexpr (PC) {
-      if (rnorm > thr) {
-        double q2[2] = {0.0, 0.0};
-        precond_apply<float>(g, a.prec, r, tt, z, psr, psi, smem, q2[0], q2[1]);
-        block_reduce<2>(q2, red);
-        rho_r = q2[0];
-        rho_i = q2[1];
-      }
-    }
     while (rnorm > thr) {
       if (its >= a.maxit32) { status = 1; break; }
       double m2[2];
-      // the direct form also serves tiles with two halo slots per thread, and
-      // the preconditioned solver: there the recurrence form's larger centre
-      // pipeline is kept in scratch memory
-      if (exact_q || HS == 2 || PC) {
+      // the direct form also serves tiles with two halo slots per thread:
+      // there the recurrence form's larger centre pipeline is kept in scratch
+      // memory
+      if (exact_q || HS == 2) {
         // bound the drift of the q recurrence: one sweep with p formed on load
         ApplyPol<float> ap;
-        ap.r = z; ap.pold = pold; ap.pnew = pnew; ap.q = q; ap.v = a.v32;
+        ap.r = r; ap.pold = pold; ap.pnew = pnew; ap.q = q; ap.v = a.v32;
         ap.c0 = a.c32.c0; ap.eps = (float)eps; ap.om = (float)om; ap.br = (float)br;
         ap.bi = (float)bi; ap.first = first;
         ap.mu_re = ap.mu_im = 0.0;
@@ -1000,7 +984,7 @@ __device__ void solve_refine(const CocgArgs& a, int s, char* smem, double* red, 
         exact_q = false;
       } else {
         RecurPol<float> ap;
-        ap.r = z; ap.pold = pold; ap.pnew = pnew; ap.q = q; ap.v = a.v32;
+        ap.r = r; ap.pold = pold; ap.pnew = pnew; ap.q = q; ap.v = a.v32;
         ap.c0 = a.c32.c0; ap.eps = (float)eps; ap.om = (float)om; ap.br = (float)br;
         ap.bi = (float)bi; ap.first = first;
         ap.mu_re = ap.mu_im = 0.0;
@@ -1051,17 +1035,6 @@ __device__ void solve_refine(const CocgArgs& a, int s, char* smem, double* red, 
         if (rn < 0.5 * best_true) { best_true = rn; no_gain = 0; }
         else if (++no_gain >= 4) { rnorm = rn; status = 1; break; }   // FP32 stagnation
       }
-      if constexpr (PC) {
-        if (rn > thr) {
-          double q2[2] = {0.0, 0.0};
-          precond_apply<float>(g, a.prec, r, tt, z, psr, psi, smem, q2[0], q2[1]);
-          block_reduce<2>(q2, red);
-          rho_nr = q2[0];
-          rho_ni = q2[1];
-          if (!isfinite(rho_nr) || !isfinite(rho_ni)) { failed = true; break; }
-          if (fabs(rho_nr) + fabs(rho_ni) < 1e-300) { status = 2; break; }
-        }
-      }
       cdiv(rho_nr, rho_ni, rho_r, rho_i, br, bi);
       rho_r = rho_nr; rho_i = rho_ni;
       rnorm = rn;
@@ -1076,6 +1049,183 @@ __device__ void solve_refine(const CocgArgs& a, int s, char* smem, double* red, 
     // x64 holds the last folded solution, which the FP64 launch continues from
     if (failed || status != 0 || !(rnorm <= thr)) status = a.fail_list ? 3 : (status ? status : 1);
   }
+  if (threadIdx.x == 0) {
+    record(a, s, its, updates, status);
+    if (status == 3) a.fail_list[atomicAdd(a.fail_count, 1)] = s;
+  }
+}
+
+// One system, preconditioned COCG (passes in precond_impl.h).  FP64: x
+// itself accumulates alpha p.  FP32 (REFINE): reliable updates as above.
+// q = A p follows its recurrence; every kQRefresh iterations or so it is
+// formed afresh from p (q = M p + (V - shift) p, one more application of the
+// basis transforms), at a reliable update in FP32.
+constexpr int kQRefresh = 24;
+
+template <bool REFINE, bool FULL, int HS, int PITCH, bool NL>
+__device__ void solve_pc(const CocgArgs& a, int s, char* smem, double* red, char* nlc) {
+  typedef typename std::conditional<REFINE, float, double>::type T;
+  typedef typename V2<T>::t T2;
+  const Geom& g = a.g;
+  const long long N = g.N;
+  const int b = s / a.n_occ;
+  const int n = s - b * a.n_occ;
+  T2* r = reinterpret_cast<T2*>(a.slot_ws + (size_t)blockIdx.x * a.slot_bytes);
+  T2* q = r + N;
+  T2* p = r + 2 * N;
+  T2* t = r + 3 * N;
+  double2* x = a.x64 + (size_t)s * N;
+  T2* d;                           // alpha p accumulates here
+  if constexpr (REFINE) d = r + 4 * N;
+  else d = x;
+  const double eps = a.eps[n];
+  const double om = a.omega[b];
+  const T sr = (T)fmax(a.prec->vbar - eps, a.prec->floor), si = (T)(-om);
+  double2* coef64 = reinterpret_cast<double2*>(nlc);
+  T2* coef = reinterpret_cast<T2*>(nlc);
+  const int* pm_ptr = a.nl.pm_ptr;
+  const int* pm_proj = a.nl.pm_proj;
+  const T* pm_v = nl_pick<T>(a.nl.pm_v32, a.nl.pm_v64);
+  auto nlp = [&](long long i, T2& qv) {
+    if constexpr (NL) nl_point<T>(pm_ptr, pm_proj, pm_v, coef, i, qv.x, qv.y);
+  };
+  const int maxit = REFINE ? a.maxit32 : a.maxit;
+
+  ResidPol<T, NL> rp;
+  rp.x = x; rp.v = a.v64; rp.psi = a.psi64 + (size_t)n * N; rp.u = a.u64 + (size_t)b * N;
+  rp.r = r; rp.c0 = a.c64.c0; rp.eps = eps; rp.om = om;
+  rp.pm_ptr = a.nl.pm_ptr; rp.pm_proj = a.nl.pm_proj; rp.pm_v = a.nl.pm_v64;
+  rp.coef = coef64;
+
+  int its = 0, updates = 0, status = 0, last_upd = 0, last_q = 0, no_gain = 0;
+  bool failed = false, start = true, resid = true, upd = false, first = true, pend = false;
+  bool dfresh = REFINE, refresh = false;
+  double rnorm = 0.0, thr = 0.0, rmax = 0.0, best_true = 0.0;
+  double rho_r = 0.0, rho_i = 0.0, al_r = 0.0, al_i = 0.0;
+  for (;;) {
+    if (resid) {
+      // r = b - A x in FP64
+      if constexpr (NL) {
+        double d0 = 0.0, d1 = 0.0;
+        nl_project<double, double>(a.nl, x, coef64, d0, d1);
+        __syncthreads();
+      }
+      rp.rr = rp.bb = rp.rho_re = rp.rho_im = 0.0;
+      march_light<double, FULL, HS>(g, a.c64, rp, reinterpret_cast<double2*>(smem), 0, g.ntiles);
+      double w2[2] = {rp.rr, rp.bb};
+      block_reduce<2>(w2, red);
+      rnorm = sqrt(w2[0]);
+      rmax = rnorm;
+      if (start) {
+        const double bnorm = sqrt(w2[1]);
+        if (bnorm == 0.0) {
+          zero_sweep(N, x);
+          rnorm = 0.0;
+          break;
+        }
+        thr = a.tol * bnorm;
+        best_true = rnorm;
+        start = false;
+      } else if (rnorm < 0.5 * best_true) {
+        best_true = rnorm;
+        no_gain = 0;
+      } else if (++no_gain >= 4) {
+        status = 1;                                    // FP32 stagnation
+        break;
+      }
+      if (!(rnorm > thr)) break;
+      resid = false;
+      upd = false;
+      refresh = !first && its - last_q >= kQRefresh;
+      PcCtx<T>(g, *a.prec, smem).stage();
+      __syncthreads();
+    }
+    double rr[1] = {0.0};
+    pc_forward<T>(PcCtx<T>(g, *a.prec, smem), refresh ? p : r, q, t, upd, (T)al_r, (T)al_i, nlp, rr[0]);
+    if (upd) {
+      block_reduce<1>(rr, red);
+      ++its;
+      rnorm = sqrt(rr[0]);
+      if constexpr (REFINE) {
+        if (!isfinite(rnorm)) { failed = true; break; }
+        // reliable update when the recursive residual has dropped by delta, on
+        // apparent convergence, and at least every kMaxGap iterations
+        if ((rnorm < a.inner_tol * rmax && its - last_upd >= kMinGap) || rnorm <= thr ||
+            its - last_upd >= kMaxGap) {
+          fold_pair<T>(N, x, d, !dfresh, p, (T)al_r, (T)al_i);
+          __syncthreads();
+          dfresh = true;
+          pend = false;
+          ++updates;
+          last_upd = its;
+          resid = true;
+          continue;
+        }
+      } else {
+        if (!(rnorm > thr)) break;                     // converged, or NaN
+        if (its - last_q >= kQRefresh) {
+          // p has its last alpha pending; q is stale only for the next beta
+          refresh = true;
+          upd = false;
+          last_q = its;
+          continue;
+        }
+      }
+    } else if (!refresh) {
+      __syncthreads();
+    }
+    if (!refresh && its >= maxit) { status = 1; break; }
+    double q2[2] = {0.0, 0.0};
+    pc_modes<T>(PcCtx<T>(g, *a.prec, smem), *a.prec, t, sr, si, refresh, q2[0], q2[1]);
+    block_reduce<2>(q2, red);
+    PcUpdate<T> u;
+    u.r = r; u.p = p; u.q = q; u.d = d; u.v = nl_pick<T>(a.v32, a.v64);
+    u.shift = (T)(eps + fmax(a.prec->vbar - eps, a.prec->floor));
+    u.ar = (T)al_r; u.ai = (T)al_i;
+    u.first = first; u.pend = pend && !refresh; u.dfresh = dfresh; u.refresh = refresh;
+    u.br = u.bi = 0;
+    if (!refresh) {
+      if (REFINE && (!isfinite(q2[0]) || !isfinite(q2[1]))) { failed = true; break; }
+      if (fabs(q2[0]) + fabs(q2[1]) < 1e-300) { status = 2; break; }
+      if (!first) {
+        double br, bi;
+        cdiv(q2[0], q2[1], rho_r, rho_i, br, bi);
+        u.br = (T)br;
+        u.bi = (T)bi;
+      }
+      rho_r = q2[0];
+      rho_i = q2[1];
+    }
+    double m2[2] = {0.0, 0.0};
+    pc_inverse<T>(PcCtx<T>(g, *a.prec, smem), t, u, m2[0], m2[1]);
+    if (refresh) {
+      refresh = false;
+      last_q = its;
+      continue;
+    }
+    if (pend) dfresh = false;
+    pend = false;
+    first = false;
+    if constexpr (NL) nl_project<T, T>(a.nl, p, coef, m2[0], m2[1]);
+    block_reduce<2>(m2, red);
+    if (REFINE && (!isfinite(m2[0]) || !isfinite(m2[1]))) { failed = true; break; }
+    if (fabs(m2[0]) + fabs(m2[1]) < 1e-300) { status = 2; break; }
+    cdiv(rho_r, rho_i, m2[0], m2[1], al_r, al_i);
+    upd = true;
+    pend = true;
+  }
+  // a correction not in x yet (convergence in FP64, maxit and breakdown exits)
+  if (!failed && (pend || (REFINE && !dfresh))) {
+    __syncthreads();
+    if constexpr (REFINE) fold_pair<T>(N, x, d, !dfresh, pend ? p : nullptr, (T)al_r, (T)al_i);
+    else fold_pair<double>(N, x, nullptr, false, p, al_r, al_i);
+    __syncthreads();
+  }
+  // FP32 not converged (maxit, stagnation, breakdown, non-finite values): x64
+  // holds the last folded solution, which the FP64 launch continues from
+  if (REFINE && (failed || status != 0 || !(rnorm <= thr)))
+    status = a.fail_list ? 3 : (status ? status : 1);
+  if (!REFINE && status == 0 && !(rnorm <= thr)) status = 1;   // NaN residual is not convergence
   if (threadIdx.x == 0) {
     record(a, s, its, updates, status);
     if (status == 3) a.fail_list[atomicAdd(a.fail_count, 1)] = s;
@@ -1111,8 +1261,9 @@ __global__ void __launch_bounds__(kMaxBlock) k_cocg(CocgArgs a) {
     const int b = s / a.n_occ;
     const int live = a.active == nullptr ? 1 : uni(a.active[b]);
     if (live) {
-      if (REFINE) solve_refine<FULL, HS, PITCH, NL, PC>(a, s, smem, red, nlc);
-      else solve_fp64<FULL, HS, PITCH, NL, PC>(a, s, smem, red, nlc);
+      if constexpr (PC) solve_pc<REFINE, FULL, HS, PITCH, NL>(a, s, smem, red, nlc);
+      else if constexpr (REFINE) solve_refine<FULL, HS, PITCH, NL>(a, s, smem, red, nlc);
+      else solve_fp64<FULL, HS, PITCH, NL>(a, s, smem, red, nlc);
     } else if (threadIdx.x == 0) {
       a.out_iters[s] = 0;
       a.out_cycles[s] = 0;

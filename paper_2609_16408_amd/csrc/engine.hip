@@ -61,7 +61,7 @@ struct rpa_ctx {
   double* s_full = nullptr;
   StencilCoef<double> c64;
   StencilCoef<float> c32;
-  Geom geom;
+  Geom geom{};
   int block = 0;
   NlArgs nl{};                       // nonlocal projectors (device layouts)
   PrecArgs prec{};                   // kinetic preconditioner tables (device addresses)
@@ -371,11 +371,17 @@ rpa_status sternheimer_batch(rpa_ctx* h, int B, const std::vector<double>& omega
   HIPCHK(h, launch_fill_i(P<int>(h->counter), 0, 4, s));
   if (refine) ENSURE(h, h->faillist, (size_t)n_items * sizeof(int));
 
+  // with a preconditioner window the plain launch has its own occupancy
   const int bpc = h->slots_per_cu > 0 ? h->slots_per_cu
                                       : cocg_blocks_per_cu(h->geom, h->block, refine, h->nl.n_proj);
-  int grid = std::max(1, std::min(n_items, bpc * h->num_cu));
+  Geom gp = h->geom;
+  gp.prec = 0;
+  const int bpc_p = h->slots_per_cu > 0 || !prec_window(h) ? bpc
+                                                           : cocg_blocks_per_cu(gp, h->block, refine, h->nl.n_proj);
+  const int grid = std::max(1, std::min(n_items, bpc * h->num_cu));
+  const int grid_p = std::max(1, std::min(n_items, bpc_p * h->num_cu));
   const long long sb = cocg_slot_bytes(h->geom, refine);
-  ENSURE(h, h->slots, (size_t)grid * sb);
+  ENSURE(h, h->slots, (size_t)std::max(grid, grid_p) * sb);
 
   CocgArgs a;
   memset(&a, 0, sizeof(a));
@@ -448,10 +454,8 @@ rpa_status sternheimer_batch(rpa_ctx* h, int B, const std::vector<double>& omega
     ap.inner_tol = h->inner_tol;
     ap.g.prec = 0;
     ap.n_items_dev = P<int>(h->counter) + 4;
-    Geom gp = h->geom;
-    gp.prec = 0;
     const size_t shmem_p = cocg_shmem_bytes(gp, h->block, refine, h->nl.n_proj);
-    rl = timed(0, [&] { return launch_cocg(ap, refine, grid, h->block, shmem_p, s); });
+    rl = timed(0, [&] { return launch_cocg(ap, refine, grid_p, h->block, shmem_p, s); });
     if (rl != RPA_OK) return rl;
     CocgArgs aq = a;
     aq.order = P<int>(h->order) + n_items;
@@ -799,7 +803,7 @@ uint64_t lanczos_workspace_bytes(const rpa_setup_params& p, int B, int n_lanczos
   bytes += items * N * 16;                                  // Sternheimer solutions (FP64)
   bytes += items * 4 * (refine ? 6 : 5) + 64 * 4;           // two order lists, counts, status, hand-over list
   bytes += b * N * 8;                                       // accumulated density response
-  Geom g;
+  Geom g{};
   g.nx = p.n[0]; g.ny = p.n[1]; g.nz = p.n[2];
   g.ty = pick_tile_y(p.n[1], p.n[2], p.tile_y);
   if (g.ty <= 0) g.ty = p.n[1];
@@ -807,9 +811,14 @@ uint64_t lanczos_workspace_bytes(const rpa_setup_params& p, int B, int n_lanczos
   g.N = (long long)N;
   g.prec = p.precond != 0;
   const int block = ((g.ty * g.nz + 63) / 64) * 64;
+  if (g.prec) cocg_pc_shape(g, block, std::max(0, p.n_proj));
   int bpc = p.slots_per_cu > 0 ? p.slots_per_cu : 2;
   if (p.slots_per_cu <= 0 && query_occupancy)
     bpc = cocg_blocks_per_cu(g, block, refine, std::max(0, p.n_proj));
+  if (p.slots_per_cu <= 0 && query_occupancy && g.prec && (p.precond_omega_min > 0 || p.precond_omega_max > 0)) {
+    g.prec = 0;
+    bpc = std::max(bpc, cocg_blocks_per_cu(g, block, refine, std::max(0, p.n_proj)));
+  }
   const uint64_t grid = std::max<uint64_t>(1, std::min<uint64_t>(items, (uint64_t)bpc * num_cu));
   bytes += grid * (uint64_t)cocg_slot_bytes(g, refine);
   return bytes;
@@ -857,7 +866,7 @@ rpa_status rpa_setup(const rpa_setup_params* p, void* stream, rpa_handle* out) {
             "no valid tile_y (ty | ny, ty*nz <= 768)");
   ARG_CHECK(ty == ny || ty >= kRadius, "tile_y must be >= 6 unless it covers the plane");
   {
-    Geom gq;
+    Geom gq{};
     gq.nx = p->n[0]; gq.ny = ny; gq.nz = nz; gq.ty = ty; gq.ntiles = ny / ty; gq.N = N;
     gq.prec = p->precond != 0;
     ARG_CHECK(geom_supported(gq), "n[2] must be <= 116");
@@ -921,6 +930,7 @@ rpa_status rpa_setup(const rpa_setup_params* p, void* stream, rpa_handle* out) {
   h->geom.N = N;
   h->geom.prec = p->precond != 0;
   h->block = ((ty * nz + 63) / 64) * 64;
+  if (h->geom.prec) cocg_pc_shape(h->geom, h->block, p->n_proj);
   int dev = 0;
   auto fail = [&](rpa_status st) { rpa_destroy(h); return st; };
   if (hipGetDevice(&dev) != hipSuccess ||
@@ -1256,7 +1266,11 @@ ScratchLayout scratch_layout(rpa_ctx* h, int B, bool symmetrized) {
   const bool refine = h->precision == RPA_FP32_REFINE;
   const int bpc = h->slots_per_cu > 0 ? h->slots_per_cu
                                       : cocg_blocks_per_cu(h->geom, h->block, refine, h->nl.n_proj);
-  const size_t grid = std::max<size_t>(1, std::min<size_t>(items, (size_t)bpc * h->num_cu));
+  Geom gp = h->geom;
+  gp.prec = 0;
+  const int bpc_p = h->slots_per_cu > 0 || !prec_window(h) ? bpc
+                                                           : cocg_blocks_per_cu(gp, h->block, refine, h->nl.n_proj);
+  const size_t grid = std::max<size_t>(1, std::min<size_t>(items, (size_t)std::max(bpc, bpc_p) * h->num_cu));
   auto add = [&](DevBuf& buf, size_t bytes) {
     L.items.push_back({&buf, bytes});
     L.total += (bytes + 255) & ~(size_t)255;
@@ -1810,6 +1824,7 @@ rpa_status rpa_autotune(rpa_handle h, int32_t n_lanczos, int32_t probe_iters,
     Geom gq = h->geom;
     gq.ty = t;
     gq.ntiles = ny / t;
+    gq.pc_block = gq.pc_planes32 = gq.pc_planes64 = 0;   // the acceptance bound
     const int blk = ((t * nz + 63) / 64) * 64;
     if (cocg_shmem_bytes(gq, blk, refine, h->nl.n_proj) > 160 * 1024 ||
         cocg_shmem_bytes(gq, blk, false, h->nl.n_proj) > 160 * 1024)
@@ -1853,6 +1868,7 @@ rpa_status rpa_autotune(rpa_handle h, int32_t n_lanczos, int32_t probe_iters,
     h->geom.ty = t;
     h->geom.ntiles = ny / t;
     h->block = ((t * nz + 63) / 64) * 64;
+    if (h->geom.prec) cocg_pc_shape(h->geom, h->block, h->nl.n_proj);
     const int occ = cocg_blocks_per_cu(h->geom, h->block, refine, h->nl.n_proj);
     for (int slots = 1; slots <= std::min(2, occ); ++slots) {
       h->slots_per_cu = slots;
@@ -1874,6 +1890,7 @@ rpa_status rpa_autotune(rpa_handle h, int32_t n_lanczos, int32_t probe_iters,
   h->geom.ty = best_ty;
   h->geom.ntiles = ny / best_ty;
   h->block = ((best_ty * nz + 63) / 64) * 64;
+  if (h->geom.prec) cocg_pc_shape(h->geom, h->block, h->nl.n_proj);
   h->slots_per_cu = best_slots;
   drop_graphs(h);
   h->warm_B = 0;

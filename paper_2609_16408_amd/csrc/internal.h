@@ -13,6 +13,7 @@ constexpr int kRadius = 6;               // 12th-order central differences
 constexpr int kMaxLanczos = 64;          // largest supported n_lanczos
 constexpr int kMaxLanczosPublic = kMaxLanczos;
 constexpr int kMaxBlock = 768;           // largest stencil/COCG workgroup
+constexpr int kPcBlock = 768;            // workgroup of the preconditioned solver
 constexpr int kMaxProj = 4096;           // projectors (their coefficients live in LDS)
 constexpr int kMaxGroup = 4;             // projectors sharing one support per group
 
@@ -31,7 +32,11 @@ struct Geom {
   int ty;          // rows per tile
   int ntiles;      // ny / ty
   long long N;     // nx*ny*nz
-  int prec;        // 1: the COCG solves are preconditioned (workspaces and LDS grow)
+  int prec;        // 1: the COCG solves are preconditioned (LDS grows)
+  // preconditioned solver (cocg_pc_shape): its workgroup and the planes it
+  // transforms per round, FP32 and FP64; 0 before the shape is chosen
+  int pc_block;
+  int pc_planes32, pc_planes64;
 };
 
 constexpr int kMaxPrecDim = 64;          // largest grid dimension of the in-kernel preconditioner
@@ -145,7 +150,9 @@ size_t cocg_shmem_bytes(const Geom& g, int block, bool fp32_refine, int n_proj);
 int cocg_blocks_per_cu(const Geom& g, int block, bool fp32_refine, int n_proj);
 bool geom_supported(const Geom& g);   // nz + 12 <= 128 (padded LDS rows)
 long long cocg_slot_bytes(const Geom& g, bool fp32_refine);
-// registers per thread the preconditioner's prefetched planes need, and the most it has
+// fill in the preconditioned solver's launch shape for an accepted problem
+void cocg_pc_shape(Geom& g, int block, int n_proj);
+// plane elements per thread of the stencil workgroup, and the most the preconditioner accepts
 int cocg_prec_regs(const Geom& g, int block);
 int cocg_prec_regs_max();
 
