@@ -17,8 +17,11 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(ROOT, "_build")
 LIB_NAME = "librpa_mi355x.so"
 LIB_PATH = os.path.join(PKG, LIB_NAME)
-SOURCES = ["engine.hip", "cocg.hip", "cocg_nl.hip", "cocg_pc.hip", "kernels.hip", "transform.hip", "server.hip",
-           "precond.hip", "block_lanczos.hip"]
+SOURCES = ["engine.hip", "cocg.hip", "kernels.hip", "transform.hip", "server.hip", "precond.hip",
+           "block_lanczos.hip"]
+# the persistent COCG kernels: one object per variant (plain, nonlocal,
+# preconditioned, both) and LDS pitch
+COCG_GROUPS = [(v, pitch) for v in (3, 2, 1, 0) for pitch in (56, 64, 128)]
 ARCH = "gfx950"
 
 
@@ -39,9 +42,9 @@ def common_flags() -> list:
     ]
 
 
-def _compile(src: str, verbose: bool) -> str:
-    obj = os.path.join(BUILD_DIR, os.path.splitext(src)[0] + ".o")
-    cmd = [hipcc(), *common_flags(), "-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(src: str, verbose: bool, name: str = "", defines=()) -> str:
+    obj = os.path.join(BUILD_DIR, (name or os.path.splitext(src)[0]) + ".o")
+    cmd = [hipcc(), *common_flags(), *defines, "-c", os.path.join(CSRC, src), "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
@@ -55,8 +58,10 @@ def _compile(src: str, verbose: bool) -> str:
 def build(verbose: bool = False) -> str:
     """Compile every HIP source and link the shared library; returns its path."""
     os.makedirs(BUILD_DIR, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
-        objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
+    jobs = [("cocg_kernels.hip", f"cocg_v{v}_p{p}", (f"-DRPA_V={v}", f"-DRPA_PITCH={p}")) for v, p in COCG_GROUPS]
+    jobs += [(s, "", ()) for s in SOURCES]
+    with cf.ThreadPoolExecutor(max_workers=max(1, min(16, os.cpu_count() or 1))) as ex:
+        objs = list(ex.map(lambda j: _compile(j[0], verbose, j[1], j[2]), jobs))
     tmp = LIB_PATH + ".tmp"
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp]
     if verbose:

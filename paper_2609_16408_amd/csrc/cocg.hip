@@ -1,15 +1,18 @@
-// Batched Sternheimer COCG launches (kernels in cocg_impl.h), the plain
-// operator application and the nonlocal term of the latter.
+// Batched Sternheimer COCG launches (kernels in cocg_impl.h, compiled by
+// cocg_kernels.hip), the plain operator application and the nonlocal term of the latter.
 #include "cocg_impl.h"
+
+#include <algorithm>
 
 namespace rpa {
 
 namespace {
 
+// Tile blockIdx.x, vector blockIdx.y, planes of segment blockIdx.z.
 template <typename T, int M, int PITCH>
 __global__ void __launch_bounds__(kMaxBlock) k_happly(Geom g, StencilCoef<T> cf, const T* v,
                                                        const double* sr, const double* si,
-                                                       const void* x, void* y) {
+                                                       const void* x, void* y, int seg) {
   extern __shared__ double smem_d[];
   typedef typename V2<T>::t T2;
   constexpr bool FULL = M == 0;
@@ -21,7 +24,8 @@ __global__ void __launch_bounds__(kMaxBlock) k_happly(Geom g, StencilCoef<T> cf,
   p.y = reinterpret_cast<T2*>(y) + base;
   p.v = v; p.c0 = cf.c0;
   p.sr = (T)sr[vec]; p.si = (T)si[vec];
-  march<T, FULL, HS, PITCH>(g, cf, p, reinterpret_cast<T2*>(smem_d), blockIdx.x, blockIdx.x + 1);
+  const int xb = blockIdx.z * seg, xe = min(g.nx, xb + seg);
+  march<T, FULL, HS, PITCH>(g, cf, p, reinterpret_cast<T2*>(smem_d), blockIdx.x, blockIdx.x + 1, xb, xe);
 }
 
 // Nonlocal term of the plain operator application: per vector, the
@@ -56,6 +60,37 @@ __global__ void __launch_bounds__(256) k_nl_add(NlArgs nl, long long N, const vo
 
 }  // namespace
 
+namespace {
+
+int tile_mode(const Geom& g, int block) {
+  if (g.ty == g.ny) return 0;
+  return block >= 2 * R * g.nz ? 1 : 2;
+}
+
+// LDS row pitch.  When a wave spans several rows, a pitch that is a multiple
+// of the 64 banks puts the same columns of all its rows into the same banks:
+// 56 shifts each row by eight elements.  Rows of 45 to 52 points nearly fill a
+// wave and take 64.
+int pitch_for(const Geom& g) { return g.nz + 2 * R <= 56 ? 56 : (g.nz + 2 * R <= 64 ? 64 : 128); }
+
+template <int V>
+CocgKernel cocg_pick_v(const Geom& g, int block, bool refine) {
+  const int m = tile_mode(g, block);
+  switch (pitch_for(g)) {
+    case 56: return cocg_kernel<V, 56>(m, refine);
+    case 64: return cocg_kernel<V, 64>(m, refine);
+    default: return cocg_kernel<V, 128>(m, refine);
+  }
+}
+
+// The persistent kernel for a launch of `block` threads.
+CocgKernel cocg_pick(const Geom& g, int block, bool refine, bool nonlocal) {
+  if (g.prec) return nonlocal ? cocg_pick_v<3>(g, block, refine) : cocg_pick_v<2>(g, block, refine);
+  return nonlocal ? cocg_pick_v<1>(g, block, refine) : cocg_pick_v<0>(g, block, refine);
+}
+
+}  // namespace
+
 bool geom_supported(const Geom& g) { return g.nz + 2 * R <= 128; }
 
 size_t cocg_shmem_bytes(const Geom& g, int block, bool fp32_refine, int n_proj) {
@@ -80,11 +115,8 @@ void cocg_pc_shape(Geom& g, int block, int n_proj) {
 int cocg_blocks_per_cu(const Geom& g, int block, bool fp32_refine, int n_proj) {
   const size_t shmem = cocg_shmem_bytes(g, block, fp32_refine, n_proj);
   if (g.prec && g.pc_block) block = g.pc_block;
-  const int m = tile_mode(g, block);
   int nb = 0;
-  const void* fn = n_proj > 0 ? cocg_nl_fn(fp32_refine, m, pitch_for(g), g.prec != 0)
-                   : g.prec   ? cocg_pc_fn(fp32_refine, m, pitch_for(g))
-                              : cocg_fn_t<0>(fp32_refine, m, pitch_for(g));
+  const void* fn = reinterpret_cast<const void*>(cocg_pick(g, block, fp32_refine, n_proj > 0));
   hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, block, shmem);
   if (e != hipSuccess || nb < 1) return 1;
   return nb;
@@ -94,42 +126,45 @@ int cocg_prec_regs(const Geom& g, int block) { return prec_regs(g, block); }
 int cocg_prec_regs_max() { return kPrecRegs; }
 
 long long cocg_slot_bytes(const Geom& g, bool fp32_refine) {
-  // r, q, p_old, p_new (+ the FP32 correction d); preconditioned: one p and a transform buffer
-  return fp32_refine ? 5LL * g.N * (long long)sizeof(float2) : 4LL * g.N * (long long)sizeof(double2);
+  // r, q, p (+ the FP32 correction d, + the preconditioner's transform buffer)
+  const long long vecs = 3 + (fp32_refine ? 1 : 0) + (g.prec ? 1 : 0);
+  return vecs * g.N * (long long)(fp32_refine ? sizeof(float2) : sizeof(double2));
 }
 
 namespace {
-template <typename T, int M, int P>
-hipError_t launch_h(const Geom& g, const StencilCoef<T>& cf, const T* v, const double* sr,
-                    const double* si, const void* x, void* y, dim3 grid, int block, size_t shmem,
-                    hipStream_t s) {
-  hipLaunchKernelGGL((k_happly<T, M, P>), grid, dim3(block), shmem, s, g, cf, v, sr, si, x, y);
-  return hipGetLastError();
-}
-template <typename T, int M>
-hipError_t launch_hm(const Geom& g, const StencilCoef<T>& cf, const T* v, const double* sr,
-                     const double* si, const void* x, void* y, dim3 grid, int block,
-                     size_t shmem, hipStream_t s) {
-  return pitch_for(g) == 64 ? launch_h<T, M, 64>(g, cf, v, sr, si, x, y, grid, block, shmem, s)
-                            : launch_h<T, M, 128>(g, cf, v, sr, si, x, y, grid, block, shmem, s);
-}
 template <typename T>
-hipError_t launch_ht(const Geom& g, const StencilCoef<T>& cf, const T* v, const double* sr,
-                     const double* si, const void* x, void* y, dim3 grid, int block,
-                     size_t shmem, hipStream_t s) {
+using HapplyKernel = void (*)(Geom, StencilCoef<T>, const T*, const double*, const double*, const void*, void*, int);
+
+template <typename T, int P>
+HapplyKernel<T> happly_kernel(int m) {
+  if (m == 0) return &k_happly<T, 0, P>;
+  if (m == 1) return &k_happly<T, 1, P>;
+  return &k_happly<T, 2, P>;
+}
+
+template <typename T>
+hipError_t launch_ht(const Geom& g, const StencilCoef<T>& cf, const T* v, const double* sr, const double* si,
+                     const void* x, void* y, int nvec, int block, size_t shmem, hipStream_t s) {
+  constexpr int kFill = 512;         // workgroups that fill the chip (two per compute unit)
+  // few workgroups: split the march along x (each segment reads its own 12 halo planes)
+  const long long wgs = (long long)g.ntiles * nvec;
+  const int nseg = (int)std::max<long long>(1, std::min<long long>(g.nx, kFill / wgs));
+  const int seg = (g.nx + nseg - 1) / nseg;
   const int m = tile_mode(g, block);
-  if (m == 0) return launch_hm<T, 0>(g, cf, v, sr, si, x, y, grid, block, shmem, s);
-  if (m == 1) return launch_hm<T, 1>(g, cf, v, sr, si, x, y, grid, block, shmem, s);
-  return launch_hm<T, 2>(g, cf, v, sr, si, x, y, grid, block, shmem, s);
+  const int pitch = pitch_for(g);
+  const HapplyKernel<T> k = pitch == 56   ? happly_kernel<T, 56>(m)
+                            : pitch == 64 ? happly_kernel<T, 64>(m)
+                                          : happly_kernel<T, 128>(m);
+  hipLaunchKernelGGL(k, dim3(g.ntiles, nvec, (g.nx + seg - 1) / seg), dim3(block), shmem, s, g, cf, v, sr, si, x, y, seg);
+  return hipGetLastError();
 }
 }  // namespace
 
 hipError_t launch_cocg(const CocgArgs& a, bool fp32_refine, int grid, int block, size_t shmem,
                        hipStream_t s) {
   if (a.prec) block = a.g.pc_block;
-  if (a.nl.n_proj > 0) return launch_cocg_nl(a, fp32_refine, grid, block, shmem, s);
-  if (a.prec) return launch_cocg_pc(a, fp32_refine, grid, block, shmem, s);
-  return launch_cocg_t<0>(a, fp32_refine, grid, block, shmem, s);
+  hipLaunchKernelGGL(cocg_pick(a.g, block, fp32_refine, a.nl.n_proj > 0), dim3(grid), dim3(block), shmem, s, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_happly(const Geom& g, const StencilCoef<double>& c64, const StencilCoef<float>& c32,
@@ -137,9 +172,8 @@ hipError_t launch_happly(const Geom& g, const StencilCoef<double>& c64, const St
                          const double* shift_im, const void* x, void* y, bool fp32,
                          int block, hipStream_t s) {
   const size_t shmem = cocg_shmem_bytes(g, block, fp32, 0);
-  dim3 grid(g.ntiles, nvec);
-  if (fp32) return launch_ht<float>(g, c32, v32, shift_re, shift_im, x, y, grid, block, shmem, s);
-  return launch_ht<double>(g, c64, v64, shift_re, shift_im, x, y, grid, block, shmem, s);
+  if (fp32) return launch_ht<float>(g, c32, v32, shift_re, shift_im, x, y, nvec, block, shmem, s);
+  return launch_ht<double>(g, c64, v64, shift_re, shift_im, x, y, nvec, block, shmem, s);
 }
 
 hipError_t launch_nl_apply(const NlArgs& nl, long long N, int nvec, const void* x, void* y,

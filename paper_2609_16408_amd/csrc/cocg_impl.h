@@ -13,11 +13,12 @@
 //    plane (plus 6 halo rows on each side in y) sits in LDS, double
 //    buffered, so each step needs a single barrier.  Every vector element is
 //    read from HBM once per sweep (plus the y halo and the periodic x wrap).
-//  * COCG per iteration: sweep A forms p = r + beta p_old on load, writes p
-//    and q = A p and reduces mu = p^T q (p is double buffered because
-//    neighbouring planes and halo rows still need p_old); sweep B updates
-//    x, r and reduces r^T r and ||r||^2.  All reductions are per workgroup in
-//    a fixed order, so results do not depend on scheduling.
+//  * COCG per iteration is three sweeps: p = r + beta p with the solution's
+//    pending alpha p (5 vector passes), the stencil q = A p with mu = p^T q
+//    (about 2.5), r -= alpha q with r^T r and ||r||^2 (3).  The stencil's
+//    operand is one vector that it only reads, so the march carries nothing
+//    but its column and the potential.  All reductions are per workgroup in a
+//    fixed order, so results do not depend on scheduling.
 //  * FP32_REFINE: COCG in FP32 with reliable updates: the FP32 correction is
 //    folded into the FP64 solution and the residual replaced by the FP64
 //    residual r = b - A x (an FP64 stencil sweep) whenever the recursive
@@ -26,6 +27,7 @@
 #pragma once
 
 #include <type_traits>
+#include <utility>
 
 #include "internal.h"
 
@@ -36,6 +38,23 @@ namespace {
 template <typename T> struct V2;
 template <> struct V2<float> { typedef float2 t; };
 template <> struct V2<double> { typedef double2 t; };
+
+// The thread id, opaque to the optimiser: what a pass over the
+// grid derives from it is computed inside that pass.  Hoisted out of the
+// solver's loop instead, the addresses of the preconditioned solver's passes
+// took 571 spilled registers per thread.
+__device__ __forceinline__ int opaque_tid() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
+// Element `off` after the uniform address p (one 32-bit offset register).
+template <typename E>
+__device__ __forceinline__ E& at32(E* p, unsigned off) {
+  typedef typename std::conditional<std::is_const<E>::value, const char, char>::type C;
+  return *reinterpret_cast<E*>(reinterpret_cast<C*>(p) + (unsigned)(off * (unsigned)sizeof(E)));
+}
 
 }  // namespace
 }  // namespace rpa
@@ -67,6 +86,10 @@ __device__ __forceinline__ double uni(double v) {
   const int lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffLL));
   const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
   return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
+__device__ __forceinline__ float uni(float v) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
 // ---------------------------------------------------------------------------
@@ -200,7 +223,17 @@ __device__ __forceinline__ void nl_point(const int* pm_ptr, const int* pm_proj, 
 // row pitch PITCH, padded with R periodic copies on each side in z (and in y
 // when one tile covers the whole plane), so all 24 in-plane neighbour reads
 // are immediate offsets from one per-thread base address.
-template <typename T> struct V2;
+// f(0) ... f(N - 1) with compile-time arguments: register arrays indexed
+// inside never depend on the loop unroller.
+template <class F, int... I>
+__device__ __forceinline__ void static_for_seq(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_seq(f, std::make_integer_sequence<int, N>{});
+}
+#define RPA_INLINE __attribute__((always_inline))
 
 template <typename T, bool FULL, int HS, int PITCH, class Pol, int PPS>
 struct Marcher {
@@ -209,6 +242,7 @@ struct Marcher {
   static constexpr int PF = Pol::kPF;
   static constexpr int U = QN + PF;   // FIFO: planes x-R .. x+R+PF
   static constexpr int PA = PF + 1;   // aux/halo pipelines: planes x .. x+PF
+  static constexpr int NH = FULL ? 0 : HS;
   // The x loop is unrolled by U, so a slot index (phase within the block) of
   // a pipeline of period PA equals x mod PA only if PA divides U
   // (PF in {1, 2, 3, 5} for the 13-plane stencil).
@@ -222,17 +256,15 @@ struct Marcher {
   Pol& pol;
   T2* buf0;            // plane buffers: 2 * PPS of them, bufs apart
   size_t bufs;         // elements per buffer
-  size_t plane;
+  int plane;
   int nx;
-  bool own;
-  int col;            // own column offset in the plane (gy*nz + z)
-  int wbase;          // LDS index of the thread's stencil window (row rc-R, col z)
-  int ci;             // LDS index of the own point
-  int zpl, zpr;       // LDS indices of periodic copies in z (-1: none)
-  int ypl, ypr;       // ... and in y (whole-plane tiles only)
+  int y0n;             // column offset of the tile's first row
+  unsigned col;        // own column offset in the tile
+  int ci;              // LDS index of the own point
+  int edge;            // periodic copies: 1 left z pad, 2 right z pad, 4 / 8 y pads (whole planes)
   bool hv[HS];
-  int hl[HS];         // LDS index of halo points
-  int hcol[HS];       // halo column offsets in the plane
+  int hl[HS];          // LDS index of halo points
+  unsigned hcol[HS];   // halo column offsets in the plane
   T2 fifo[U];
   AuxT ax[PA];
   T2 hq[HS][PA];
@@ -243,109 +275,116 @@ struct Marcher {
   template <int PH>
   __device__ __forceinline__ void put(T2* buf) {
     const T2 c = fifo[(PH + R) % U];
-    if (own) {
-      buf[ci] = c;
-      if (zpl >= 0) buf[zpl] = c;
-      if (zpr >= 0) buf[zpr] = c;
-      if (FULL) {
-        if (ypl >= 0) buf[ypl] = c;
-        if (ypr >= 0) buf[ypr] = c;
-      }
+    buf[ci] = c;
+    if (edge & 1) buf[ci - g.nz] = c;
+    if (edge & 2) buf[ci + g.nz] = c;
+    if (FULL) {
+      if (edge & 4) buf[ci - g.ny * PITCH] = c;
+      if (edge & 8) buf[ci + g.ny * PITCH] = c;
     }
-#pragma unroll
-    for (int h = 0; h < HS; ++h)
-      if (hv[h]) buf[hl[h]] = hq[h][PH % PA];
+    static_for<NH>([&](auto H) RPA_INLINE {
+      if (hv[H]) buf[hl[H]] = hq[H][PH % PA];
+    });
   }
 
   // PPS consecutive planes x, x+1 share one barrier: both are stored into
   // their own buffers of the current set, then both are computed.  TAIL: the
   // block may end inside the pair (only the last block of a march).
   template <int PH, bool TAIL>
-  __device__ __forceinline__ void step(int x) {
+  __device__ __forceinline__ void step(int x, int xe) {
     T2* set = buf0 + (size_t)(((x / PPS) & 1) * PPS) * bufs;
-    const bool second = PPS == 2 && (!TAIL || x + 1 < nx);
+    const bool second = PPS == 2 && (!TAIL || x + 1 < xe);
     put<PH>(set);
     if (second) put<PH + 1>(set + bufs);
     __syncthreads();
-    point<PH>(x, set);
-    if (second) point<PH + 1>(x + 1, set + bufs);
+    __builtin_amdgcn_sched_barrier(0);
+    point<PH>(x, xe, set);
+    __builtin_amdgcn_sched_barrier(0);
+    if (second) point<PH + 1>(x + 1, xe, set + bufs);
+    __builtin_amdgcn_sched_barrier(0);
   }
 
+  // No branch in here: threads without a column of their own repeat the
+  // tile's first one (same values to the same addresses, Pol::own masks the
+  // sums), and the refills past the last plane re-read it.  The loads and
+  // stores share one counter that completes in order, and behind a branch the
+  // compiler has to assume the smaller count: with the store of q in an
+  // if (own) every step waited for the previous step's store.
   template <int PH>
-  __device__ __forceinline__ void point(int x, const T2* buf) {
+  __device__ __forceinline__ void point(int x, int xe, const T2* buf) {
     const T2 c = fifo[(PH + R) % U];
-    if (own) {
-      const T2* w = buf + wbase;
-      T xr = 0, xi = 0, yr = 0, yi = 0, zr = 0, zi = 0;
-#pragma unroll
-      for (int k = 1; k <= R; ++k) {
-        const T2 a = fifo[(PH + R - k) % U];
-        const T2 b = fifo[(PH + R + k) % U];
-        xr += cf.w[k] * (a.x + b.x);
-        xi += cf.w[k] * (a.y + b.y);
-      }
-#pragma unroll
-      for (int k = 1; k <= R; ++k) {
-        const T2 a = w[(R - k) * PITCH + R];
-        const T2 b = w[(R + k) * PITCH + R];
-        yr += cf.w[k] * (a.x + b.x);
-        yi += cf.w[k] * (a.y + b.y);
-      }
-#pragma unroll
-      for (int k = 1; k <= R; ++k) {
-        const T2 a = w[R * PITCH + R - k];
-        const T2 b = w[R * PITCH + R + k];
-        zr += cf.w[k] * (a.x + b.x);
-        zi += cf.w[k] * (a.y + b.y);
-      }
-      const T sx = cf.sx * xr + cf.sy * yr + cf.sz * zr;
-      const T sy = cf.sx * xi + cf.sy * yi + cf.sz * zi;
-      pol.center((size_t)x * plane, col, c, mk2(sx, sy), ax[PH % PA]);
-    }
+    const T2* w = buf + (ci - (R * PITCH + R));
+    T xr = 0, xi = 0, yr = 0, yi = 0, zr = 0, zi = 0;
+    static_for<R>([&](auto K) RPA_INLINE {
+      constexpr int k = K + 1;
+      const T2 a = fifo[(PH + R - k) % U];
+      const T2 b = fifo[(PH + R + k) % U];
+      xr += cf.w[k] * (a.x + b.x);
+      xi += cf.w[k] * (a.y + b.y);
+    });
+    static_for<R>([&](auto K) RPA_INLINE {
+      constexpr int k = K + 1;
+      const T2 a = w[(R - k) * PITCH + R];
+      const T2 b = w[(R + k) * PITCH + R];
+      yr += cf.w[k] * (a.x + b.x);
+      yi += cf.w[k] * (a.y + b.y);
+    });
+    static_for<R>([&](auto K) RPA_INLINE {
+      constexpr int k = K + 1;
+      const T2 a = w[R * PITCH + R - k];
+      const T2 b = w[R * PITCH + R + k];
+      zr += cf.w[k] * (a.x + b.x);
+      zi += cf.w[k] * (a.y + b.y);
+    });
+    const T sx = cf.sx * xr + cf.sy * yr + cf.sz * zr;
+    const T sy = cf.sx * xi + cf.sy * yi + cf.sz * zi;
+    pol.center(x * plane + y0n, col, c, mk2(sx, sy), ax[PH % PA]);
     // refill the pipelines: the FIFO slot of plane x-R takes plane x+R+PF+1,
-    // the aux/halo slot of plane x takes plane x+PF+1.  The loads are issued
-    // unconditionally (past the last plane they re-read plane nx-1, and
-    // threads without a column read valid addresses whose values are never
-    // used): with no branch around them the compiler can count the loads in
-    // flight and wait only for the one a value comes from.
+    // the aux/halo slot of plane x takes plane x+PF+1
     const int xn = x + PF + 1;
-    const int xc = xn < nx ? xn : nx - 1;
-    fifo[PH % U] = pol.load((size_t)wrapx(xc + R, nx) * plane, col);
-    ax[PH % PA] = pol.aux((size_t)xc * plane, col);
-#pragma unroll
-    for (int h = 0; h < HS; ++h) hq[h][PH % PA] = pol.load((size_t)xc * plane, hcol[h]);
+    const int xc = xn < xe ? xn : xe - 1;
+    const int po = xc * plane + y0n, pw = wrapx(xc + R, nx) * plane + y0n;
+    fifo[PH % U] = pol.load(pw, col);
+    ax[PH % PA] = pol.aux(po, col);
+    static_for<NH>([&](auto H) RPA_INLINE { hq[H][PH % PA] = pol.load(po - y0n, hcol[H]); });
   }
 
   // U planes from x; full blocks need no bounds checks between steps
   template <int PH>
-  __device__ __forceinline__ void block_full(int x) {
+  __device__ __forceinline__ void block_full(int x, int xe) {
     if constexpr (PH < U) {
-      step<PH, false>(x);
-      block_full<PH + PPS>(x + PPS);
+      step<PH, false>(x, xe);
+      block_full<PH + PPS>(x + PPS, xe);
     }
   }
 
   template <int PH>
-  __device__ __forceinline__ void block(int x) {
+  __device__ __forceinline__ void block(int x, int xe) {
     if constexpr (PH < U) {
-      if (x < nx) {
-        step<PH, true>(x);
-        block<PH + PPS>(x + PPS);
+      if (x < xe) {
+        step<PH, true>(x, xe);
+        block<PH + PPS>(x + PPS, xe);
       }
     }
   }
 
-  __device__ __forceinline__ void run(int t_begin, int t_end) {
-    const int tid = threadIdx.x;
-    const int ny = g.ny, nz = g.nz, ty = g.ty;
-    own = tid < ty * nz;
-    const int ly = own ? tid / nz : 0;
-    const int z = own ? tid - ly * nz : 0;
-    const int nhalo = FULL ? 0 : 2 * R * nz;
+  // Planes [xb, xe) of tiles [t_begin, t_end).
+  __device__ __forceinline__ void run(int t_begin, int t_end, int xb, int xe) {
+    const int tid = opaque_tid();
+    const int bs = (int)blockDim.x;
+    const int ny = g.ny, nz = g.nz, ty = FULL ? g.ny : g.ty;
+    pol.own = tid < ty * nz;
+    col = pol.own ? tid : 0;
+    const int ly = (int)col / nz, z = (int)col - ly * nz;
+    ci = (ly + R) * PITCH + z + R;
+    // a point is copied into the left pad if it is among the last R of the
+    // row and into the right pad if among the first R (both when nz < 2R)
+    edge = (z >= nz - R ? 1 : 0) | (z < R ? 2 : 0) | (FULL && ly >= ny - R ? 4 : 0) | (FULL && ly < R ? 8 : 0);
+    const int nhalo = 2 * R * nz;
     int hrow[HS], hz[HS];
 #pragma unroll
-    for (int h = 0; h < HS; ++h) {
-      const int hid = tid + h * (int)blockDim.x;
+    for (int h = 0; h < NH; ++h) {
+      const int hid = tid + h * bs;
       hv[h] = hid < nhalo;
       const int hr = hv[h] ? hid / nz : 0;
       hz[h] = hv[h] ? hid - hr * nz : 0;
@@ -354,43 +393,27 @@ struct Marcher {
     }
     for (int t = t_begin; t < t_end; ++t) {
       const int y0 = t * ty;
-      const int gy = y0 + ly;
-      col = gy * nz + z;
-      const int rc = (FULL ? gy : ly) + R;
-      ci = rc * PITCH + z + R;
-      wbase = (rc - R) * PITCH + z;
-      // a point is copied into the left pad if it is among the last R of the
-      // row and into the right pad if among the first R (both when nz < 2R)
-      zpl = z >= nz - R ? rc * PITCH + z + R - nz : -1;
-      zpr = z < R ? rc * PITCH + z + R + nz : -1;
-      ypl = -1;
-      ypr = -1;
-      if (FULL) {
-        ypl = gy >= ny - R ? (gy + R - ny) * PITCH + z + R : -1;
-        ypr = gy < R ? (gy + R + ny) * PITCH + z + R : -1;
-      }
+      y0n = y0 * nz;
 #pragma unroll
-      for (int h = 0; h < HS; ++h) {
+      for (int h = 0; h < NH; ++h) {
         int gr = hrow[h] < R ? y0 - R + hrow[h] : y0 + ty + (hrow[h] - R);
         gr = gr < 0 ? gr + ny : (gr >= ny ? gr - ny : gr);
         hcol[h] = gr * nz + hz[h];
       }
-      // prologue: FIFO slot j holds plane j - R (phase 0); aux/halo slot j plane j
-#pragma unroll
-      for (int j = 0; j < U; ++j) {
-        const int px = ((j - R) % nx + nx) % nx;
-        fifo[j] = own ? pol.load((size_t)px * plane, col) : zero2<T2>();
-      }
-#pragma unroll
-      for (int j = 0; j < PA; ++j) {
-        ax[j] = own ? pol.aux((size_t)j * plane, col) : AuxT();
-#pragma unroll
-        for (int h = 0; h < HS; ++h)
-          hq[h][j] = hv[h] ? pol.load((size_t)j * plane, hcol[h]) : zero2<T2>();
-      }
-      int x = 0;
-      for (; x + U <= nx; x += U) block_full<0>(x);
-      if (x < nx) block<0>(x);
+      // prologue: FIFO slot i holds plane xb + i - R (phase 0); aux/halo slot i plane xb + i
+      static_for<U>([&](auto I) RPA_INLINE {
+        int px = (xb + (I - R)) % nx;          // nx > R: at most one period below
+        px = px < 0 ? px + nx : px;
+        fifo[I] = pol.load(px * plane + y0n, col);
+      });
+      static_for<PA>([&](auto I) RPA_INLINE {
+        const int px = xb + I < xe ? xb + I : xe - 1;
+        ax[I] = pol.aux(px * plane + y0n, col);
+        static_for<NH>([&](auto H) RPA_INLINE { hq[H][I] = pol.load(px * plane, hcol[H]); });
+      });
+      int x = xb;
+      for (; x + U <= xe; x += U) block_full<0>(x, xe);
+      if (x < xe) block<0>(x, xe);
       __syncthreads();
     }
   }
@@ -402,117 +425,21 @@ constexpr int planes_per_step() { return sizeof(T) == 4 ? 2 : 1; }
 
 template <typename T, bool FULL, int HS, int PITCH, class Pol>
 __device__ __forceinline__ void march(const Geom& g, const StencilCoef<T>& cf, Pol& pol,
-                                      typename V2<T>::t* lds, int t_begin, int t_end) {
+                                      typename V2<T>::t* lds, int t_begin, int t_end, int xb, int xe) {
   const int rows = (FULL ? g.ny : g.ty) + 2 * R;
   Marcher<T, FULL, HS, PITCH, Pol, planes_per_step<T>()> m{g, cf, pol};
   m.buf0 = lds;
   m.bufs = (size_t)rows * PITCH;
-  m.plane = (size_t)g.ny * g.nz;
+  m.plane = g.ny * g.nz;
   m.nx = g.nx;
-  m.run(t_begin, t_end);
+  m.run(t_begin, t_end, xb, xe);
 }
 
-// Register-light variant for the occasional FP64 residual sweep: no x queue;
-// the 12 x neighbours are read through the caches (they were read moments
-// before by the neighbouring planes' steps), y/z neighbours from the LDS plane.
-template <typename T, bool FULL, int HS, class Pol>
-__device__ __forceinline__ void march_light(const Geom& g, const StencilCoef<T>& cf, Pol& pol,
-                                            typename V2<T>::t* lds, int t_begin, int t_end) {
-  typedef typename V2<T>::t T2;
-  typedef typename Pol::Aux AuxT;
-  const int tid = threadIdx.x;
-  const int nx = g.nx, ny = g.ny, nz = g.nz, ty = g.ty;
-  const int ncol = ty * nz;
-  const bool own = tid < ncol;
-  const int ly = own ? tid / nz : 0;
-  const int z = own ? tid - ly * nz : 0;
-  const int rows = FULL ? ny : ty + 2 * R;
-  const size_t plane = (size_t)ny * nz;
-  const int nhalo = FULL ? 0 : 2 * R * nz;
-  int hl[HS], hoff_r[HS], hz[HS];
-  bool hv[HS];
-#pragma unroll
-  for (int j = 0; j < HS; ++j) {
-    const int hid = tid + j * (int)blockDim.x;
-    hv[j] = hid < nhalo;
-    const int hr = hv[j] ? hid / nz : 0;
-    hz[j] = hv[j] ? hid - hr * nz : 0;
-    hoff_r[j] = hr;
-    hl[j] = (hr < R ? hr : ty + hr) * nz + hz[j];
-  }
-  for (int t = t_begin; t < t_end; ++t) {
-    const int y0 = t * ty;
-    const int gy = y0 + ly;
-    const size_t col = (size_t)gy * nz + z;
-    int hrowoff[HS];
-#pragma unroll
-    for (int j = 0; j < HS; ++j) {
-      int gr = hoff_r[j] < R ? y0 - R + hoff_r[j] : y0 + ty + (hoff_r[j] - R);
-      gr = gr < 0 ? gr + ny : (gr >= ny ? gr - ny : gr);
-      hrowoff[j] = gr * nz + hz[j];
-    }
-    const int rc = FULL ? gy : ly + R;
-    for (int x = 0; x < nx; ++x) {
-      T2* buf = lds + (x & 1) * rows * nz;
-      const size_t po = (size_t)x * plane;
-      const T2 c = own ? pol.load(po, (int)col) : zero2<T2>();
-      if (own) buf[rc * nz + z] = c;
-#pragma unroll
-      for (int h = 0; h < HS; ++h)
-        if (hv[h]) buf[hl[h]] = pol.load(po, hrowoff[h]);
-      __syncthreads();
-      if (own) {
-        const AuxT axv = pol.aux(po, (int)col);
-        T xr = 0, xi = 0, yr = 0, yi = 0, zr = 0, zi = 0;
-#pragma unroll
-        for (int k = 1; k <= R; ++k) {
-          int xp = x + k, xm = x - k;
-          xp -= xp >= nx ? nx : 0;
-          xm += xm < 0 ? nx : 0;
-          const T2 a = pol.load((size_t)xp * plane, (int)col);
-          const T2 b = pol.load((size_t)xm * plane, (int)col);
-          xr += cf.w[k] * (a.x + b.x);
-          xi += cf.w[k] * (a.y + b.y);
-        }
-#pragma unroll
-        for (int k = 1; k <= R; ++k) {
-          int up = rc + k, dn = rc - k;
-          if (FULL) { up -= up >= ny ? ny : 0; dn += dn < 0 ? ny : 0; }
-          const T2 a = buf[up * nz + z];
-          const T2 b = buf[dn * nz + z];
-          yr += cf.w[k] * (a.x + b.x);
-          yi += cf.w[k] * (a.y + b.y);
-        }
-        const int rz = rc * nz;
-#pragma unroll
-        for (int k = 1; k <= R; ++k) {
-          int zp = z + k, zm = z - k;
-          zp -= zp >= nz ? nz : 0;
-          zm += zm < 0 ? nz : 0;
-          const T2 a = buf[rz + zp];
-          const T2 b = buf[rz + zm];
-          zr += cf.w[k] * (a.x + b.x);
-          zi += cf.w[k] * (a.y + b.y);
-        }
-        const T sx = cf.sx * xr + cf.sy * yr + cf.sz * zr;
-        const T sy = cf.sx * xi + cf.sy * yi + cf.sz * zi;
-        pol.center(po, (int)col, c, mk2(sx, sy), axv);
-      }
-    }
-    __syncthreads();
-  }
-}
-
-// Bytes of LDS used by the plane buffers: the largest of the FIFO march (T of
-// the COCG iterations, padded pitch) and the FP64 light march (unpadded).
+// Bytes of LDS used by the plane buffers of the march (padded pitch): the
+// FP32 form of one tile takes four buffers, the FP64 form two of twice the size.
 __host__ __device__ inline size_t lds_plane_bytes(const Geom& g, int pitch, bool fp32_iter) {
-  const bool full = g.ty == g.ny;
-  const size_t rows_pad = (size_t)(full ? g.ny : g.ty) + 2 * R;
-  const size_t rows_light = full ? (size_t)g.ny : (size_t)g.ty + 2 * R;
-  const size_t main = fp32_iter ? 2 * planes_per_step<float>() * rows_pad * pitch * sizeof(float2)
-                                : 2 * planes_per_step<double>() * rows_pad * pitch * sizeof(double2);
-  const size_t light = 2 * rows_light * g.nz * sizeof(double2);
-  size_t b = main > light ? main : light;
+  const size_t rows_pad = (size_t)(g.ty == g.ny ? g.ny : g.ty) + 2 * R;
+  size_t b = 2 * rows_pad * pitch * sizeof(double2);
   if (g.prec) {
     // the preconditioner's bases and planes (FP64 for the FP64 solver, which
     // the FP32 path also launches for the systems it hands over); without a
@@ -545,116 +472,63 @@ struct ResidPol {
   TI2* r;
   double c0, eps, om;
   double rr, bb, rho_re, rho_im;
+  bool own;                       // set by the march; sums of repeated columns are dropped
   const int* pm_ptr;              // point-major projector entries (NL)
   const int* pm_proj;
   const double* pm_v;
   const double2* coef;            // w_p of x (LDS)
-  static constexpr int kPF = 1;   // runs a few times per solve: keep registers low
-  struct Aux { double v, b; };
-  __device__ double2 load(size_t po, int c) const { return (x + po)[c]; }
-  __device__ Aux aux(size_t po, int c) const {
+  static constexpr int kPF = 1;
+  struct Aux { double v, psi, u; };
+  __device__ double2 load(int po, unsigned c) const { return at32(x + po, c); }
+  __device__ Aux aux(int po, unsigned c) const {
     Aux a;
-    a.v = (v + po)[c];
-    a.b = -(psi + po)[c] * (u + po)[c];
+    a.v = at32(v + po, c);
+    a.psi = at32(psi + po, c);
+    a.u = at32(u + po, c);
     return a;
   }
-  __device__ void center(size_t po, int c, double2 xv, double2 nb, const Aux& ax) {
+  __device__ void center(int po, unsigned c, double2 xv, double2 nb, const Aux& ax) {
     const double a = c0 + ax.v - eps;
     double axr = a * xv.x + om * xv.y + nb.x;
     double axi = a * xv.y - om * xv.x + nb.y;
     if constexpr (NL) nl_point<double>(pm_ptr, pm_proj, pm_v, coef, (long long)po + c, axr, axi);
-    const double bval = ax.b;
+    const double bval = -ax.psi * ax.u;
     const double rx = bval - axr;
     const double ry = -axi;
     TI2 rs; rs.x = (TI)rx; rs.y = (TI)ry;
-    (r + po)[c] = rs;
-    rr += rx * rx + ry * ry;
-    bb += bval * bval;
+    at32(r + po, c) = rs;
     const double sx = (double)rs.x, sy = (double)rs.y;
-    rho_re += sx * sx - sy * sy;
-    rho_im += 2.0 * sx * sy;
+    rr += own ? rx * rx + ry * ry : 0.0;
+    bb += own ? bval * bval : 0.0;
+    rho_re += own ? sx * sx - sy * sy : 0.0;
+    rho_im += own ? 2.0 * sx * sy : 0.0;
   }
 };
 
-// COCG sweep A: p = r + beta p_old (formed on load), q = (H - sigma) p.
+// COCG stencil sweep: q = (H_loc - sigma) p, mu = p^T q.  Nothing is computed
+// from a value as soon as it is loaded, so the loads of later planes stay in
+// flight across steps.
 template <typename T>
 struct ApplyPol {
   typedef typename V2<T>::t T2;
-  const T2* r;
-  const T2* pold;
-  T2* pnew;
+  const T2* p;
   T2* q;
   const T* v;
   T c0, eps, om;
-  T br, bi;
-  bool first;
   double mu_re, mu_im;
-  // FP32: two planes per barrier already give the loads a plane of slack
-  static constexpr int kPF = sizeof(T) == 4 ? 1 : 2;
+  bool own;
+  static constexpr int kPF = 1;
   typedef T Aux;
-  __device__ T aux(size_t po, int c) const { return (v + po)[c]; }
-  __device__ T2 load(size_t po, int c) const {
-    T2 rv = (r + po)[c];
-    if (first) return rv;
-    const T2 pv = (pold + po)[c];
-    rv.x += br * pv.x - bi * pv.y;
-    rv.y += br * pv.y + bi * pv.x;
-    return rv;
-  }
-  __device__ void center(size_t po, int c, T2 pv, T2 nb, const T& vv) {
+  __device__ T aux(int po, unsigned c) const { return at32(v + po, c); }
+  __device__ T2 load(int po, unsigned c) const { return at32(p + po, c); }
+  __device__ void center(int po, unsigned c, T2 pv, T2 nb, const T& vv) {
     const T a = c0 + vv - eps;
     T2 h;
     h.x = a * pv.x + om * pv.y + nb.x;
     h.y = a * pv.y - om * pv.x + nb.y;
-    (pnew + po)[c] = pv;
-    (q + po)[c] = h;
-    mu_re += (double)(pv.x * h.x - pv.y * h.y);
-    mu_im += (double)(pv.x * h.y + pv.y * h.x);
-  }
-};
-
-// COCG sweep A without forming p as planes arrive: the stencil acts on r
-// only, and since A is linear, q = A p = A r + beta q_old with q_old = A p_old;
-// p = r + beta p_old and q are formed at the centre point from p_old and
-// q_old, which come through the centre pipeline like V.  Nothing is computed
-// from a value as soon as it is loaded, so the loads of later planes stay in
-// flight across steps.  q is updated in place (only its centre point is read).
-template <typename T>
-struct RecurPol {
-  typedef typename V2<T>::t T2;
-  const T2* r;
-  const T2* pold;
-  T2* pnew;
-  T2* q;
-  const T* v;
-  T c0, eps, om;
-  T br, bi;
-  bool first;                     // p = r, q = A r (p_old and q_old are not used)
-  double mu_re, mu_im;
-  static constexpr int kPF = 1;
-  struct Aux { T v; T2 p, q; };
-  __device__ Aux aux(size_t po, int c) const {
-    Aux a;
-    a.v = (v + po)[c];
-    a.p = (pold + po)[c];
-    a.q = (q + po)[c];
-    return a;
-  }
-  __device__ T2 load(size_t po, int c) const { return (r + po)[c]; }
-  __device__ void center(size_t po, int c, T2 rv, T2 nb, const Aux& ax) {
-    const T a = c0 + ax.v - eps;
-    T2 w, pv, qv;
-    w.x = a * rv.x + om * rv.y + nb.x;
-    w.y = a * rv.y - om * rv.x + nb.y;
-    pv.x = rv.x + br * ax.p.x - bi * ax.p.y;
-    pv.y = rv.y + br * ax.p.y + bi * ax.p.x;
-    qv.x = w.x + br * ax.q.x - bi * ax.q.y;
-    qv.y = w.y + br * ax.q.y + bi * ax.q.x;
-    if (first) { pv = rv; qv = w; }
-    (pnew + po)[c] = pv;
-    (q + po)[c] = qv;
-    mu_re += (double)(pv.x * qv.x - pv.y * qv.y);
-    mu_im += (double)(pv.x * qv.y + pv.y * qv.x);
+    at32(q + po, c) = h;
+    mu_re += own ? (double)(pv.x * h.x - pv.y * h.y) : 0.0;
+    mu_im += own ? (double)(pv.x * h.y + pv.y * h.x) : 0.0;
   }
 };
 
@@ -667,16 +541,17 @@ struct HPol {
   T2* y;
   const T* v;
   T c0, sr, si;
+  bool own;
   static constexpr int kPF = sizeof(T) == 4 ? 3 : 2;
   typedef T Aux;
-  __device__ T aux(size_t po, int c) const { return (v + po)[c]; }
-  __device__ T2 load(size_t po, int c) const { return (x + po)[c]; }
-  __device__ void center(size_t po, int c, T2 xv, T2 nb, const T& vv) {
+  __device__ T aux(int po, unsigned c) const { return at32(v + po, c); }
+  __device__ T2 load(int po, unsigned c) const { return at32(x + po, c); }
+  __device__ void center(int po, unsigned c, T2 xv, T2 nb, const T& vv) {
     const T a = c0 + vv - sr;
     T2 o;
     o.x = a * xv.x + si * xv.y + nb.x;
     o.y = a * xv.y - si * xv.x + nb.y;
-    (y + po)[c] = o;
+    at32(y + po, c) = o;
   }
 };
 
@@ -692,81 +567,115 @@ struct NlPoint {
   const typename V2<T>::t* coef;
 };
 
-// x (XT) = first ? alpha p : x + alpha p;  r -= alpha q;  returns ||r||^2, r^T r.
-// With a nonlocal term, q holds (H_loc - sigma) p and V_nl p is added here.
-// Four elements per thread per trip, all loads issued before the arithmetic.
-template <typename T, typename XT, bool NL>
-__device__ __forceinline__ void update_sweep(long long N, typename V2<XT>::t* x,
-                                             const typename V2<T>::t* p, typename V2<T>::t* r,
-                                             const typename V2<T>::t* q, T ar, T ai, bool first,
-                                             const NlPoint<T>& nl, double& rr, double& rho_re,
-                                             double& rho_im) {
-  typedef typename V2<T>::t T2;
-  typedef typename V2<XT>::t X2;
-  constexpr int U = 4;
-  const long long st = blockDim.x;
-  long long i0 = threadIdx.x;
-  for (; i0 + (U - 1) * st < N; i0 += U * st) {
-    T2 pv[U], qv[U], rv[U];
-    X2 xv[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const long long i = i0 + u * st;
-      pv[u] = p[i];
-      qv[u] = q[i];
-      rv[u] = r[i];
-      if (!first) xv[u] = x[i];
-    }
-    if constexpr (NL) {
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        nl_point<T>(nl.ptr, nl.proj, nl.v, nl.coef, i0 + u * st, qv[u].x, qv[u].y);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const long long i = i0 + u * st;
-      const T dx = ar * pv[u].x - ai * pv[u].y;
-      const T dy = ar * pv[u].y + ai * pv[u].x;
-      if (first) { xv[u].x = (XT)dx; xv[u].y = (XT)dy; }
-      else { xv[u].x += (XT)dx; xv[u].y += (XT)dy; }
-      x[i] = xv[u];
-      rv[u].x -= ar * qv[u].x - ai * qv[u].y;
-      rv[u].y -= ar * qv[u].y + ai * qv[u].x;
-      r[i] = rv[u];
-      const double sx = (double)rv[u].x, sy = (double)rv[u].y;
-      rr += sx * sx + sy * sy;
-      rho_re += sx * sx - sy * sy;
-      rho_im += 2.0 * sx * sy;
-    }
+// The streaming sweeps take kSweep elements per thread and trip, the next
+// trip's loads issued before this trip's stores: loads and stores complete
+// in order on one counter, so loads issued after stores would wait for them.
+
+constexpr int kSweep = 4;
+
+template <class Load, class Use>
+__device__ __forceinline__ void stream_sweep(int N, Load&& load, Use&& use) {
+  const int trip = kSweep * (int)blockDim.x;
+  const int full = N / trip;               // trips without a bounds check
+  if (full > 0) load(0, 0);
+  int i0 = 0;
+#pragma unroll 1
+  for (int k = 0; k + 2 <= full; k += 2) {
+    load(i0 + trip, 1);
+    use(i0, 0);
+    if (k + 2 < full) load(i0 + 2 * trip, 0);
+    use(i0 + trip, 1);
+    i0 += 2 * trip;
   }
-  for (long long i = i0; i < N; i += st) {
-    const T2 pv = p[i];
-    T2 qv = q[i];
-    T2 rv = r[i];
-    if constexpr (NL) nl_point<T>(nl.ptr, nl.proj, nl.v, nl.coef, i, qv.x, qv.y);
-    const T dx = ar * pv.x - ai * pv.y;
-    const T dy = ar * pv.y + ai * pv.x;
-    X2 xv;
-    if (first) { xv.x = (XT)dx; xv.y = (XT)dy; }
-    else { xv = x[i]; xv.x += (XT)dx; xv.y += (XT)dy; }
-    x[i] = xv;
-    rv.x -= ar * qv.x - ai * qv.y;
-    rv.y -= ar * qv.y + ai * qv.x;
-    r[i] = rv;
-    const double sx = (double)rv.x, sy = (double)rv.y;
-    rr += sx * sx + sy * sy;
-    rho_re += sx * sx - sy * sy;
-    rho_im += 2.0 * sx * sy;
+  if (full & 1) {
+    use(i0, 0);
+    i0 += trip;
   }
 }
 
-__device__ __forceinline__ void fold_sweep(long long N, double2* x, const float2* d) {
-  for (long long i = threadIdx.x; i < N; i += blockDim.x) {
-    double2 a = x[i];
-    const float2 b = d[i];
-    a.x += (double)b.x; a.y += (double)b.y;
-    x[i] = a;
+// r -= alpha (q + V_nl p);  returns ||r||^2, r^T r.
+template <typename T, bool NL>
+__device__ __forceinline__ void residual_sweep(int N, typename V2<T>::t* r, const typename V2<T>::t* q, T ar, T ai,
+                                               const NlPoint<T>& nl, double& rr, double& rho_re, double& rho_im) {
+  typedef typename V2<T>::t T2;
+  const int st = blockDim.x;
+  const unsigned tid = opaque_tid();
+  T2 qv[2][kSweep], rv[2][kSweep];
+  auto one = [&](int i, T2 b, T2 a) RPA_INLINE {
+    if constexpr (NL) nl_point<T>(nl.ptr, nl.proj, nl.v, nl.coef, i + (int)tid, b.x, b.y);
+    a.x -= ar * b.x - ai * b.y;
+    a.y -= ar * b.y + ai * b.x;
+    at32(r + i, tid) = a;
+    const double sx = (double)a.x, sy = (double)a.y;
+    rr += sx * sx + sy * sy;
+    rho_re += sx * sx - sy * sy;
+    rho_im += 2.0 * sx * sy;
+  };
+  stream_sweep(
+      N,
+      [&](int i0, int h) RPA_INLINE {
+#pragma unroll
+        for (int u = 0; u < kSweep; ++u) {
+          qv[h][u] = at32(q + (i0 + u * st), tid);
+          rv[h][u] = at32(r + (i0 + u * st), tid);
+        }
+      },
+      [&](int i0, int h) RPA_INLINE {
+#pragma unroll
+        for (int u = 0; u < kSweep; ++u) one(i0 + u * st, qv[h][u], rv[h][u]);
+      });
+  for (int i = N / (kSweep * st) * (kSweep * st); i + (int)tid < N; i += st) one(i, at32(q + i, tid), at32(r + i, tid));
+}
+
+// x (pend) += alpha p_old (xfresh: x = alpha p_old);  p = first ? r : r + beta p.
+template <typename T>
+__device__ __forceinline__ void direction_sweep(int N, const typename V2<T>::t* r, typename V2<T>::t* p,
+                                                typename V2<T>::t* x, T ar, T ai, T br, T bi, bool first, bool pend,
+                                                bool xfresh) {
+  typedef typename V2<T>::t T2;
+  const int st = blockDim.x;
+  const unsigned tid = opaque_tid();
+  if (first) {
+    for (int i = 0; i + (int)tid < N; i += st) at32(p + i, tid) = at32(r + i, tid);
+    return;
   }
+  if (!pend || xfresh) {
+    // the iteration after a fold: rare, so not pipelined
+    for (int i = 0; i + (int)tid < N; i += st) {
+      T2 a = at32(r + i, tid);
+      const T2 b = at32(p + i, tid);
+      if (pend) at32(x + i, tid) = {ar * b.x - ai * b.y, ar * b.y + ai * b.x};
+      a.x += br * b.x - bi * b.y;
+      a.y += br * b.y + bi * b.x;
+      at32(p + i, tid) = a;
+    }
+    return;
+  }
+  T2 pv[2][kSweep], rv[2][kSweep], xv[2][kSweep];
+  auto one = [&](int i, T2 a, T2 b, T2 c) RPA_INLINE {
+    c.x += ar * b.x - ai * b.y;
+    c.y += ar * b.y + ai * b.x;
+    at32(x + i, tid) = c;
+    a.x += br * b.x - bi * b.y;
+    a.y += br * b.y + bi * b.x;
+    at32(p + i, tid) = a;
+  };
+  stream_sweep(
+      N,
+      [&](int i0, int h) RPA_INLINE {
+#pragma unroll
+        for (int u = 0; u < kSweep; ++u) {
+          rv[h][u] = at32(r + (i0 + u * st), tid);
+          pv[h][u] = at32(p + (i0 + u * st), tid);
+          xv[h][u] = at32(x + (i0 + u * st), tid);
+        }
+      },
+      [&](int i0, int h) RPA_INLINE {
+#pragma unroll
+        for (int u = 0; u < kSweep; ++u) one(i0 + u * st, rv[h][u], pv[h][u], xv[h][u]);
+      });
+  for (int i = N / (kSweep * st) * (kSweep * st); i + (int)tid < N; i += st)
+    one(i, at32(r + i, tid), at32(p + i, tid), at32(x + i, tid));
 }
 
 // x += d (has_d) + alpha p (p non-null), the sum formed in the iteration's precision
@@ -792,12 +701,14 @@ __device__ __forceinline__ void zero_sweep(long long N, double2* x) {
   for (long long i = threadIdx.x; i < N; i += blockDim.x) x[i] = make_double2(0.0, 0.0);
 }
 
-// complex division a / b
+// complex division a / b of uniform values; the quotient is uniform again (in
+// scalar registers: held in vector registers across the sweeps, the solvers'
+// scalars took room that the marches then spilled)
 __device__ __forceinline__ void cdiv(double ar, double ai, double br, double bi, double& cr,
                                      double& ci) {
   const double den = br * br + bi * bi;
-  cr = (ar * br + ai * bi) / den;
-  ci = (ai * br - ar * bi) / den;
+  cr = uni((ar * br + ai * bi) / den);
+  ci = uni((ai * br - ar * bi) / den);
 }
 
 __device__ __forceinline__ void record(const CocgArgs& a, int s, int its, int cycles, int status) {
@@ -831,224 +742,155 @@ __device__ __forceinline__ void record(const CocgArgs& a, int s, int its, int cy
 }
 
 // ---------------------------------------------------------------------------
-// One system, FP64 throughout.
-template <bool FULL, int HS, int PITCH, bool NL>
-__device__ void solve_fp64(const CocgArgs& a, int s, char* smem, double* red, char* nlc) {
-  const Geom& g = a.g;
-  const long long N = g.N;
-  const int b = s / a.n_occ;
-  const int n = s - b * a.n_occ;
-  double2* lds = reinterpret_cast<double2*>(smem);
-  double2* ws = reinterpret_cast<double2*>(a.slot_ws + (size_t)blockIdx.x * a.slot_bytes);
-  double2* r = ws;
-  double2* q = ws + N;
-  double2* pa = ws + 2 * N;
-  double2* pb = ws + 3 * N;
-  double2* x = a.x64 + (size_t)s * N;
-  const double eps = a.eps[n];
-  const double om = a.omega[b];
-  double2* coef = reinterpret_cast<double2*>(nlc);
-  NlPoint<double> nlp{a.nl.pm_ptr, a.nl.pm_proj, a.nl.pm_v64, coef};
-
-  ResidPol<double, NL> rp;
-  rp.x = x; rp.v = a.v64; rp.psi = a.psi64 + (size_t)n * N; rp.u = a.u64 + (size_t)b * N;
-  rp.r = r; rp.c0 = a.c64.c0; rp.eps = eps; rp.om = om;
-  rp.rr = rp.bb = rp.rho_re = rp.rho_im = 0.0;
-  rp.pm_ptr = a.nl.pm_ptr; rp.pm_proj = a.nl.pm_proj; rp.pm_v = a.nl.pm_v64;
-  rp.coef = coef;
-  if constexpr (NL) {
-    double d0 = 0.0, d1 = 0.0;
-    nl_project<double, double>(a.nl, x, coef, d0, d1);
-    __syncthreads();
-  }
-  march_light<double, FULL, HS>(g, a.c64, rp, lds, 0, g.ntiles);
-  double v4[4] = {rp.rr, rp.bb, rp.rho_re, rp.rho_im};
-  block_reduce<4>(v4, red);
-  const double bnorm = sqrt(v4[1]);
-  double rnorm = sqrt(v4[0]);
-  double rho_r = v4[2], rho_i = v4[3];
-  int its = 0, status = 0;
-  if (bnorm == 0.0) {
-    zero_sweep(N, x);
-  } else {
-    const double thr = a.tol * bnorm;
-    double br = 0.0, bi = 0.0;
-    bool first = true;
-    double2* pold = pa;
-    double2* pnew = pb;
-    while (rnorm > thr) {
-      if (its >= a.maxit) { status = 1; break; }
-      ApplyPol<double> ap;
-      ap.r = r; ap.pold = pold; ap.pnew = pnew; ap.q = q; ap.v = a.v64;
-      ap.c0 = a.c64.c0; ap.eps = eps; ap.om = om; ap.br = br; ap.bi = bi; ap.first = first;
-      ap.mu_re = ap.mu_im = 0.0;
-      march<double, FULL, HS, PITCH>(g, a.c64, ap, lds, 0, g.ntiles);
-      double m2[2] = {ap.mu_re, ap.mu_im};
-      if constexpr (NL) nl_project<double, double>(a.nl, pnew, coef, m2[0], m2[1]);
-      block_reduce<2>(m2, red);
-      if (fabs(m2[0]) + fabs(m2[1]) < 1e-300) { status = 2; break; }
-      double al_r, al_i;
-      cdiv(rho_r, rho_i, m2[0], m2[1], al_r, al_i);
-      double rr = 0.0, nr = 0.0, ni = 0.0;
-      update_sweep<double, double, NL>(N, x, pnew, r, q, al_r, al_i, false, nlp, rr, nr, ni);
-      double u3[3] = {rr, nr, ni};
-      block_reduce<3>(u3, red);
-      ++its;
-      rnorm = sqrt(u3[0]);
-      cdiv(u3[1], u3[2], rho_r, rho_i, br, bi);
-      rho_r = u3[1]; rho_i = u3[2];
-      first = false;
-      double2* t = pold; pold = pnew; pnew = t;
-    }
-    if (status == 0 && !(rnorm <= thr)) status = 1;   // NaN residual is not convergence
-  }
-  if (threadIdx.x == 0) record(a, s, its, 0, status);
-}
-
-// One system, FP32 COCG with reliable updates (Sleijpen and van der Vorst,
+// One system by plain COCG.
+// FP64: x itself accumulates alpha p and the recursive residual decides.
+// FP32 (REFINE): COCG with reliable updates (Sleijpen and van der Vorst,
 // 1996): the search direction is kept for the whole solve, while every time
 // the FP32 recursive residual has dropped by the factor delta (inner_tol) the
 // FP32 correction d is folded into the FP64 solution and the residual is
 // replaced by the true FP64 residual b - A x64.  Convergence is declared on
 // the FP64 residual only.
-template <bool FULL, int HS, int PITCH, bool NL>
-__device__ void solve_refine(const CocgArgs& a, int s, char* smem, double* red, char* nlc) {
+template <bool REFINE, bool FULL, int HS, int PITCH, bool NL>
+__device__ __forceinline__ void solve_plain(const CocgArgs& a, int s, char* smem, double* red, char* nlc) {
+  typedef typename std::conditional<REFINE, float, double>::type T;
+  typedef typename V2<T>::t T2;
   const Geom& g = a.g;
-  const long long N = g.N;
+  const int N = (int)g.N;
   const int b = s / a.n_occ;
   const int n = s - b * a.n_occ;
-  float2* ws = reinterpret_cast<float2*>(a.slot_ws + (size_t)blockIdx.x * a.slot_bytes);
-  float2* r = ws;
-  float2* q = ws + N;
-  float2* pa = ws + 2 * N;
-  float2* pb = ws + 3 * N;
-  float2* d = ws + 4 * N;
+  T2* r = reinterpret_cast<T2*>(a.slot_ws + (size_t)blockIdx.x * a.slot_bytes);
+  T2* q = r + N;
+  T2* p = r + 2 * (size_t)N;
   double2* x = a.x64 + (size_t)s * N;
+  T2* d;                           // alpha p accumulates here
+  if constexpr (REFINE) d = r + 3 * (size_t)N;
+  else d = x;
   const double eps = a.eps[n];
   const double om = a.omega[b];
-  // nonlocal coefficients: FP64 for the residual sweeps, FP32 for the inner
-  // iterations (same LDS region, never live at the same time)
-  double2* coef64 = reinterpret_cast<double2*>(nlc);
-  float2* coef32 = reinterpret_cast<float2*>(nlc);
-  NlPoint<float> nlp{a.nl.pm_ptr, a.nl.pm_proj, a.nl.pm_v32, coef32};
+  const int maxit = REFINE ? a.maxit32 : a.maxit;
 
-  ResidPol<float, NL> rp;
+  // nonlocal coefficients: FP64 for the residual sweeps, the iteration's
+  // precision otherwise (same LDS region, never live at the same time)
+  double2* coef64 = reinterpret_cast<double2*>(nlc);
+  T2* coef = reinterpret_cast<T2*>(nlc);
+  const NlPoint<T> nlp{a.nl.pm_ptr, a.nl.pm_proj, nl_pick<T>(a.nl.pm_v32, a.nl.pm_v64), coef};
+
+  ResidPol<T, NL> rp;
   rp.x = x; rp.v = a.v64; rp.psi = a.psi64 + (size_t)n * N; rp.u = a.u64 + (size_t)b * N;
   rp.r = r; rp.c0 = a.c64.c0; rp.eps = eps; rp.om = om;
-  rp.rr = rp.bb = rp.rho_re = rp.rho_im = 0.0;
   rp.pm_ptr = a.nl.pm_ptr; rp.pm_proj = a.nl.pm_proj; rp.pm_v = a.nl.pm_v64;
   rp.coef = coef64;
-  if constexpr (NL) {
-    double d0 = 0.0, d1 = 0.0;
-    nl_project<double, double>(a.nl, x, coef64, d0, d1);
-    __syncthreads();
-  }
-  march_light<double, FULL, HS>(g, a.c64, rp, reinterpret_cast<double2*>(smem), 0, g.ntiles);
-  double v4[4] = {rp.rr, rp.bb, rp.rho_re, rp.rho_im};
-  block_reduce<4>(v4, red);
-  const double bnorm = sqrt(v4[1]);
-  double rnorm = sqrt(v4[0]);      // current residual estimate
-  double rho_r = v4[2], rho_i = v4[3];
-  int its = 0, updates = 0, status = 0;
+
+  int its = 0, updates = 0, status = 0, last_upd = 0, no_gain = 0;
   bool failed = false;             // FP32 iteration produced a non-finite value
-  if (bnorm == 0.0) {
-    zero_sweep(N, x);
-  } else {
-    const double thr = a.tol * bnorm;
-    const double delta = a.inner_tol;
-    double rmax = rnorm;           // true residual at the last update
-    double best_true = rnorm;      // smallest true residual seen
-    int no_gain = 0;               // updates in a row without progress
-    int last_upd = 0;              // iteration of the last update
-    double br = 0.0, bi = 0.0;
-    bool first = true;             // p = r (no previous direction)
-    bool dfresh = true;            // d holds nothing yet
-    bool exact_q = false;          // q = A p directly (after a residual replacement)
-    float2* pold = pa;
-    float2* pnew = pb;
-    while (rnorm > thr) {
-      if (its >= a.maxit32) { status = 1; break; }
-      double m2[2];
-      // the direct form also serves tiles with two halo slots per thread:
-      // there the recurrence form's larger centre pipeline is kept in scratch
-      // memory
-      if (exact_q || HS == 2) {
-        // bound the drift of the q recurrence: one sweep with p formed on load
-        ApplyPol<float> ap;
-        ap.r = r; ap.pold = pold; ap.pnew = pnew; ap.q = q; ap.v = a.v32;
-        ap.c0 = a.c32.c0; ap.eps = (float)eps; ap.om = (float)om; ap.br = (float)br;
-        ap.bi = (float)bi; ap.first = first;
-        ap.mu_re = ap.mu_im = 0.0;
-        march<float, FULL, HS, PITCH>(g, a.c32, ap, reinterpret_cast<float2*>(smem), 0, g.ntiles);
-        m2[0] = ap.mu_re; m2[1] = ap.mu_im;
-        exact_q = false;
-      } else {
-        RecurPol<float> ap;
-        ap.r = r; ap.pold = pold; ap.pnew = pnew; ap.q = q; ap.v = a.v32;
-        ap.c0 = a.c32.c0; ap.eps = (float)eps; ap.om = (float)om; ap.br = (float)br;
-        ap.bi = (float)bi; ap.first = first;
-        ap.mu_re = ap.mu_im = 0.0;
-        march<float, FULL, HS, PITCH>(g, a.c32, ap, reinterpret_cast<float2*>(smem), 0, g.ntiles);
-        m2[0] = ap.mu_re; m2[1] = ap.mu_im;
+  bool start = true, resid = true; // the residual is (re)computed from x
+  bool first = true, pend = false; // no direction yet; alpha p not in d yet
+  bool dfresh = REFINE;            // d holds nothing yet
+  double rnorm = 0.0, thr = 0.0;   // current residual estimate, its target
+  double rmax = 0.0, best_true = 0.0;  // true residual at the last update, smallest seen
+  double rho_r = 0.0, rho_i = 0.0, al_r = 0.0, al_i = 0.0, br = 0.0, bi = 0.0;
+  for (;;) {
+    double rho_nr, rho_ni;
+    if (resid) {
+      // r = b - A x in FP64 (stored rounded to T)
+      if constexpr (NL) {
+        double d0 = 0.0, d1 = 0.0;
+        nl_project<double, double>(a.nl, x, coef64, d0, d1);
+        __syncthreads();
       }
-      if constexpr (NL) nl_project<float, float>(a.nl, pnew, coef32, m2[0], m2[1]);
-      block_reduce<2>(m2, red);
-      if (!isfinite(m2[0]) || !isfinite(m2[1])) { failed = true; break; }
-      if (fabs(m2[0]) + fabs(m2[1]) < 1e-300) { status = 2; break; }
-      double al_r, al_i;
-      cdiv(rho_r, rho_i, m2[0], m2[1], al_r, al_i);
-      double rr = 0.0, nr = 0.0, ni = 0.0;
-      update_sweep<float, float, NL>(N, d, pnew, r, q, (float)al_r, (float)al_i, dfresh, nlp, rr,
-                                     nr, ni);
-      double u3[3] = {rr, nr, ni};
+      rp.rr = rp.bb = rp.rho_re = rp.rho_im = 0.0;
+      march<double, FULL, HS, PITCH>(g, a.c64, rp, reinterpret_cast<double2*>(smem), 0, g.ntiles, 0, g.nx);
+      double w4[4] = {rp.rr, rp.bb, rp.rho_re, rp.rho_im};
+      block_reduce<4>(w4, red);
+      rnorm = uni(sqrt(w4[0]));
+      rho_nr = w4[2];
+      rho_ni = w4[3];
+      rmax = rnorm;
+      resid = false;
+      if (start) {
+        const double bnorm = sqrt(w4[1]);
+        if (bnorm == 0.0) {
+          zero_sweep(N, x);
+          rnorm = 0.0;
+          break;
+        }
+        thr = uni(a.tol * bnorm);
+        best_true = rnorm;
+      } else if (rnorm < 0.5 * best_true) {
+        best_true = rnorm;
+        no_gain = 0;
+      } else if (++no_gain >= 4) {
+        status = 1;                // FP32 stagnation
+        break;
+      }
+    } else {
+      double u3[3] = {0.0, 0.0, 0.0};
+      residual_sweep<T, NL>(N, r, q, uni((T)al_r), uni((T)al_i), nlp, u3[0], u3[1], u3[2]);
       block_reduce<3>(u3, red);
       ++its;
-      dfresh = false;
-      double rn = sqrt(u3[0]);
-      double rho_nr = u3[1], rho_ni = u3[2];
-      if (!isfinite(rn) || !isfinite(rho_nr) || !isfinite(rho_ni)) { failed = true; break; }
-      // reliable update when the recursive residual has dropped by delta, on
-      // apparent convergence, and at least every kMaxGap iterations (an FP32
-      // recursion that stalls above delta * rmax is caught there)
-      if ((rn < delta * rmax && its - last_upd >= kMinGap) || rn <= thr ||
-          its - last_upd >= kMaxGap) {
-        // reliable update: x64 += d; r = b - A x64 in FP64 (stored rounded to FP32)
-        fold_sweep(N, x, d);
-        __syncthreads();
-        dfresh = true;
-        ++updates;
-        last_upd = its;
-        rp.rr = rp.bb = rp.rho_re = rp.rho_im = 0.0;
-        if constexpr (NL) {
-          double d0 = 0.0, d1 = 0.0;
-          nl_project<double, double>(a.nl, x, coef64, d0, d1);
+      rnorm = uni(sqrt(u3[0]));
+      rho_nr = u3[1];
+      rho_ni = u3[2];
+      if constexpr (REFINE) {
+        if (!isfinite(rnorm) || !isfinite(rho_nr) || !isfinite(rho_ni)) { failed = true; break; }
+        // reliable update when the recursive residual has dropped by delta, on
+        // apparent convergence, and at least every kMaxGap iterations (an FP32
+        // recursion that stalls above delta * rmax is caught there)
+        if ((rnorm < a.inner_tol * rmax && its - last_upd >= kMinGap) || rnorm <= thr ||
+            its - last_upd >= kMaxGap) {
+          fold_pair<T>(N, x, d, !dfresh, p, uni((T)al_r), uni((T)al_i));
           __syncthreads();
+          dfresh = true;
+          pend = false;
+          ++updates;
+          last_upd = its;
+          resid = true;
+          continue;
         }
-        march_light<double, FULL, HS>(g, a.c64, rp, reinterpret_cast<double2*>(smem), 0, g.ntiles);
-        double w4[4] = {rp.rr, rp.bb, rp.rho_re, rp.rho_im};
-        block_reduce<4>(w4, red);
-        rn = sqrt(w4[0]);
-        rho_nr = w4[2];
-        rho_ni = w4[3];
-        rmax = rn;
-        exact_q = true;
-        if (rn < 0.5 * best_true) { best_true = rn; no_gain = 0; }
-        else if (++no_gain >= 4) { rnorm = rn; status = 1; break; }   // FP32 stagnation
       }
-      cdiv(rho_nr, rho_ni, rho_r, rho_i, br, bi);
-      rho_r = rho_nr; rho_i = rho_ni;
-      rnorm = rn;
-      first = false;
-      float2* t = pold; pold = pnew; pnew = t;
     }
-    if (!dfresh && !failed) {      // fold a pending correction (maxit / breakdown exits)
-      fold_sweep(N, x, d);
-      __syncthreads();
+    if (!(rnorm > thr)) break;     // converged, or NaN
+    if (!start) cdiv(rho_nr, rho_ni, rho_r, rho_i, br, bi);
+    start = false;
+    rho_r = rho_nr;
+    rho_i = rho_ni;
+    if (its >= maxit) { status = 1; break; }
+    direction_sweep<T>(N, r, p, d, uni((T)al_r), uni((T)al_i), uni((T)br), uni((T)bi), first, pend, dfresh);
+    __syncthreads();
+    if (pend) dfresh = false;
+    pend = false;
+    first = false;
+    ApplyPol<T> ap;
+    ap.p = p; ap.q = q; ap.v = nl_pick<T>(a.v32, a.v64);
+    ap.eps = uni((T)eps); ap.om = uni((T)om);
+    ap.mu_re = ap.mu_im = 0.0;
+    if constexpr (REFINE) {
+      ap.c0 = a.c32.c0;
+      march<T, FULL, HS, PITCH>(g, a.c32, ap, reinterpret_cast<T2*>(smem), 0, g.ntiles, 0, g.nx);
+    } else {
+      ap.c0 = a.c64.c0;
+      march<T, FULL, HS, PITCH>(g, a.c64, ap, reinterpret_cast<T2*>(smem), 0, g.ntiles, 0, g.nx);
     }
-    // not converged in FP32 (maxit, stagnation, breakdown, non-finite values):
-    // x64 holds the last folded solution, which the FP64 launch continues from
-    if (failed || status != 0 || !(rnorm <= thr)) status = a.fail_list ? 3 : (status ? status : 1);
+    double m2[2] = {ap.mu_re, ap.mu_im};
+    if constexpr (NL) nl_project<T, T>(a.nl, p, coef, m2[0], m2[1]);
+    block_reduce<2>(m2, red);
+    if (REFINE && (!isfinite(m2[0]) || !isfinite(m2[1]))) { failed = true; break; }
+    if (fabs(m2[0]) + fabs(m2[1]) < 1e-300) { status = 2; break; }
+    cdiv(rho_r, rho_i, m2[0], m2[1], al_r, al_i);
+    pend = true;
   }
+  // a correction not in x yet (convergence in FP64, maxit and breakdown exits)
+  if (!failed && (pend || (REFINE && !dfresh))) {
+    __syncthreads();
+    if constexpr (REFINE) fold_pair<T>(N, x, d, !dfresh, pend ? p : nullptr, uni((T)al_r), uni((T)al_i));
+    else fold_pair<double>(N, x, nullptr, false, p, al_r, al_i);
+    __syncthreads();
+  }
+  // FP32 not converged (maxit, stagnation, breakdown, non-finite values): x64
+  // holds the last folded solution, which the FP64 launch continues from
+  if (REFINE && (failed || status != 0 || !(rnorm <= thr)))
+    status = a.fail_list ? 3 : (status ? status : 1);
+  if (!REFINE && status == 0 && !(rnorm <= thr)) status = 1;   // NaN residual is not convergence
   if (threadIdx.x == 0) {
     record(a, s, its, updates, status);
     if (status == 3) a.fail_list[atomicAdd(a.fail_count, 1)] = s;
@@ -1063,7 +905,7 @@ __device__ void solve_refine(const CocgArgs& a, int s, char* smem, double* red, 
 constexpr int kQRefresh = 24;
 
 template <bool REFINE, bool FULL, int HS, int PITCH, bool NL>
-__device__ void solve_pc(const CocgArgs& a, int s, char* smem, double* red, char* nlc) {
+__device__ __forceinline__ void solve_pc(const CocgArgs& a, int s, char* smem, double* red, char* nlc) {
   typedef typename std::conditional<REFINE, float, double>::type T;
   typedef typename V2<T>::t T2;
   const Geom& g = a.g;
@@ -1080,7 +922,7 @@ __device__ void solve_pc(const CocgArgs& a, int s, char* smem, double* red, char
   else d = x;
   const double eps = a.eps[n];
   const double om = a.omega[b];
-  const T sr = (T)fmax(a.prec->vbar - eps, a.prec->floor), si = (T)(-om);
+  const T sr = uni((T)fmax(a.prec->vbar - eps, a.prec->floor)), si = uni((T)(-om));
   double2* coef64 = reinterpret_cast<double2*>(nlc);
   T2* coef = reinterpret_cast<T2*>(nlc);
   const int* pm_ptr = a.nl.pm_ptr;
@@ -1111,10 +953,10 @@ __device__ void solve_pc(const CocgArgs& a, int s, char* smem, double* red, char
         __syncthreads();
       }
       rp.rr = rp.bb = rp.rho_re = rp.rho_im = 0.0;
-      march_light<double, FULL, HS>(g, a.c64, rp, reinterpret_cast<double2*>(smem), 0, g.ntiles);
+      march<double, FULL, HS, PITCH>(g, a.c64, rp, reinterpret_cast<double2*>(smem), 0, g.ntiles, 0, g.nx);
       double w2[2] = {rp.rr, rp.bb};
       block_reduce<2>(w2, red);
-      rnorm = sqrt(w2[0]);
+      rnorm = uni(sqrt(w2[0]));
       rmax = rnorm;
       if (start) {
         const double bnorm = sqrt(w2[1]);
@@ -1123,7 +965,7 @@ __device__ void solve_pc(const CocgArgs& a, int s, char* smem, double* red, char
           rnorm = 0.0;
           break;
         }
-        thr = a.tol * bnorm;
+        thr = uni(a.tol * bnorm);
         best_true = rnorm;
         start = false;
       } else if (rnorm < 0.5 * best_true) {
@@ -1141,18 +983,18 @@ __device__ void solve_pc(const CocgArgs& a, int s, char* smem, double* red, char
       __syncthreads();
     }
     double rr[1] = {0.0};
-    pc_forward<T>(PcCtx<T>(g, *a.prec, smem), refresh ? p : r, q, t, upd, (T)al_r, (T)al_i, nlp, rr[0]);
+    pc_forward<T>(PcCtx<T>(g, *a.prec, smem), refresh ? p : r, q, t, upd, uni((T)al_r), uni((T)al_i), nlp, rr[0]);
     if (upd) {
       block_reduce<1>(rr, red);
       ++its;
-      rnorm = sqrt(rr[0]);
+      rnorm = uni(sqrt(rr[0]));
       if constexpr (REFINE) {
         if (!isfinite(rnorm)) { failed = true; break; }
         // reliable update when the recursive residual has dropped by delta, on
         // apparent convergence, and at least every kMaxGap iterations
         if ((rnorm < a.inner_tol * rmax && its - last_upd >= kMinGap) || rnorm <= thr ||
             its - last_upd >= kMaxGap) {
-          fold_pair<T>(N, x, d, !dfresh, p, (T)al_r, (T)al_i);
+          fold_pair<T>(N, x, d, !dfresh, p, uni((T)al_r), uni((T)al_i));
           __syncthreads();
           dfresh = true;
           pend = false;
@@ -1180,8 +1022,8 @@ __device__ void solve_pc(const CocgArgs& a, int s, char* smem, double* red, char
     block_reduce<2>(q2, red);
     PcUpdate<T> u;
     u.r = r; u.p = p; u.q = q; u.d = d; u.v = nl_pick<T>(a.v32, a.v64);
-    u.shift = (T)(eps + fmax(a.prec->vbar - eps, a.prec->floor));
-    u.ar = (T)al_r; u.ai = (T)al_i;
+    u.shift = uni((T)(eps + fmax(a.prec->vbar - eps, a.prec->floor)));
+    u.ar = uni((T)al_r); u.ai = uni((T)al_i);
     u.first = first; u.pend = pend && !refresh; u.dfresh = dfresh; u.refresh = refresh;
     u.br = u.bi = 0;
     if (!refresh) {
@@ -1190,8 +1032,8 @@ __device__ void solve_pc(const CocgArgs& a, int s, char* smem, double* red, char
       if (!first) {
         double br, bi;
         cdiv(q2[0], q2[1], rho_r, rho_i, br, bi);
-        u.br = (T)br;
-        u.bi = (T)bi;
+        u.br = uni((T)br);
+        u.bi = uni((T)bi);
       }
       rho_r = q2[0];
       rho_i = q2[1];
@@ -1217,7 +1059,7 @@ __device__ void solve_pc(const CocgArgs& a, int s, char* smem, double* red, char
   // a correction not in x yet (convergence in FP64, maxit and breakdown exits)
   if (!failed && (pend || (REFINE && !dfresh))) {
     __syncthreads();
-    if constexpr (REFINE) fold_pair<T>(N, x, d, !dfresh, pend ? p : nullptr, (T)al_r, (T)al_i);
+    if constexpr (REFINE) fold_pair<T>(N, x, d, !dfresh, pend ? p : nullptr, uni((T)al_r), uni((T)al_i));
     else fold_pair<double>(N, x, nullptr, false, p, al_r, al_i);
     __syncthreads();
   }
@@ -1234,16 +1076,18 @@ __device__ void solve_pc(const CocgArgs& a, int s, char* smem, double* red, char
 
 // M: 0 = tile covers the whole plane, 1 = y halo with one slot per thread,
 // 2 = y halo with two slots per thread.  PITCH: LDS row pitch (>= nz + 2R).
-// NL: with the nonlocal projector term (a separate kernel, so the
-// projector-free kernels carry none of its code or registers).
-// V: bit 0 = nonlocal projector term, bit 1 = preconditioned solves.
+// V: bit 0 = nonlocal projector term (separate kernels, so the projector-free
+// ones carry none of its code or registers), bit 1 = preconditioned solves.
 template <bool REFINE, int M, int PITCH, int V>
 __global__ void __launch_bounds__(kMaxBlock) k_cocg(CocgArgs a) {
   constexpr bool NL = (V & 1) != 0;
   constexpr bool PC = (V & 2) != 0;
   constexpr bool FULL = M == 0;
   constexpr int HS = M == 2 ? 2 : 1;
-  extern __shared__ double smem_d[];
+  // 16-byte accesses need the alignment: behind s_item the buffer would start
+  // at 8, where each ds_read_b128 took 54 cycles of the LDS instead of 8 (the
+  // FP64 stencil sweep of a 24^3 system 165 us instead of 30)
+  extern __shared__ __attribute__((aligned(256))) double smem_d[];
   char* smem = reinterpret_cast<char*>(smem_d);
   const Geom& g = a.g;
   double* red = reinterpret_cast<double*>(smem + lds_plane_bytes(g, PITCH, REFINE));
@@ -1262,8 +1106,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_cocg(CocgArgs a) {
     const int live = a.active == nullptr ? 1 : uni(a.active[b]);
     if (live) {
       if constexpr (PC) solve_pc<REFINE, FULL, HS, PITCH, NL>(a, s, smem, red, nlc);
-      else if constexpr (REFINE) solve_refine<FULL, HS, PITCH, NL>(a, s, smem, red, nlc);
-      else solve_fp64<FULL, HS, PITCH, NL>(a, s, smem, red, nlc);
+      else solve_plain<REFINE, FULL, HS, PITCH, NL>(a, s, smem, red, nlc);
     } else if (threadIdx.x == 0) {
       a.out_iters[s] = 0;
       a.out_cycles[s] = 0;
@@ -1274,54 +1117,6 @@ __global__ void __launch_bounds__(kMaxBlock) k_cocg(CocgArgs a) {
     item = uni(s_item);
     __syncthreads();
   }
-}
-
-int tile_mode(const Geom& g, int block) {
-  if (g.ty == g.ny) return 0;
-  return block >= 2 * R * g.nz ? 1 : 2;
-}
-int pitch_for(const Geom& g) { return g.nz + 2 * R <= 64 ? 64 : 128; }
-
-template <bool REFINE, int M, int V>
-const void* cocg_fn_p(int pitch) {
-  return pitch == 64 ? reinterpret_cast<const void*>(&k_cocg<REFINE, M, 64, V>)
-                     : reinterpret_cast<const void*>(&k_cocg<REFINE, M, 128, V>);
-}
-template <int V>
-const void* cocg_fn_t(bool refine, int m, int pitch) {
-  if (refine) {
-    if (m == 0) return cocg_fn_p<true, 0, V>(pitch);
-    if (m == 1) return cocg_fn_p<true, 1, V>(pitch);
-    return cocg_fn_p<true, 2, V>(pitch);
-  }
-  if (m == 0) return cocg_fn_p<false, 0, V>(pitch);
-  if (m == 1) return cocg_fn_p<false, 1, V>(pitch);
-  return cocg_fn_p<false, 2, V>(pitch);
-}
-
-template <bool REFINE, int M, int P, int V>
-hipError_t launch_c(const CocgArgs& a, int grid, int block, size_t shmem, hipStream_t s) {
-  hipLaunchKernelGGL((k_cocg<REFINE, M, P, V>), dim3(grid), dim3(block), shmem, s, a);
-  return hipGetLastError();
-}
-template <bool REFINE, int M, int V>
-hipError_t launch_cm(const CocgArgs& a, int pitch, int grid, int block, size_t shmem, hipStream_t s) {
-  return pitch == 64 ? launch_c<REFINE, M, 64, V>(a, grid, block, shmem, s)
-                     : launch_c<REFINE, M, 128, V>(a, grid, block, shmem, s);
-}
-template <int V>
-hipError_t launch_cocg_t(const CocgArgs& a, bool fp32_refine, int grid, int block, size_t shmem,
-                         hipStream_t s) {
-  const int m = tile_mode(a.g, block);
-  const int pitch = pitch_for(a.g);
-  if (fp32_refine) {
-    if (m == 0) return launch_cm<true, 0, V>(a, pitch, grid, block, shmem, s);
-    if (m == 1) return launch_cm<true, 1, V>(a, pitch, grid, block, shmem, s);
-    return launch_cm<true, 2, V>(a, pitch, grid, block, shmem, s);
-  }
-  if (m == 0) return launch_cm<false, 0, V>(a, pitch, grid, block, shmem, s);
-  if (m == 1) return launch_cm<false, 1, V>(a, pitch, grid, block, shmem, s);
-  return launch_cm<false, 2, V>(a, pitch, grid, block, shmem, s);
 }
 
 }  // namespace

@@ -135,17 +135,17 @@ int pick_tile_y(int ny, int nz, int requested);
 uint64_t lanczos_workspace_bytes(const rpa_setup_params& p, int B, int n_lanczos, int num_cu,
                                  bool query_occupancy);
 
+// The persistent kernel of variant V (bit 0: nonlocal term, bit 1:
+// preconditioned) and LDS row pitch PITCH for tile mode m (0: the tile is the
+// whole plane, 1 / 2: y halo with one / two slots per thread); one
+// translation unit per (V, PITCH), cocg_kernels.hip.
+typedef void (*CocgKernel)(CocgArgs);
+template <int V, int PITCH>
+CocgKernel cocg_kernel(int m, bool refine);
+
 // Launchers (return hipError_t of the launch).
 hipError_t launch_cocg(const CocgArgs& a, bool fp32_refine, int grid, int block, size_t shmem,
                        hipStream_t s);
-// the kernels with the nonlocal term (separate translation unit)
-hipError_t launch_cocg_nl(const CocgArgs& a, bool fp32_refine, int grid, int block, size_t shmem,
-                          hipStream_t s);
-const void* cocg_nl_fn(bool fp32_refine, int tile_mode, int pitch, bool prec);
-// the preconditioned kernels without a nonlocal term (separate translation unit)
-hipError_t launch_cocg_pc(const CocgArgs& a, bool fp32_refine, int grid, int block, size_t shmem,
-                          hipStream_t s);
-const void* cocg_pc_fn(bool fp32_refine, int tile_mode, int pitch);
 size_t cocg_shmem_bytes(const Geom& g, int block, bool fp32_refine, int n_proj);
 int cocg_blocks_per_cu(const Geom& g, int block, bool fp32_refine, int n_proj);
 bool geom_supported(const Geom& g);   // nz + 12 <= 128 (padded LDS rows)

@@ -108,15 +108,6 @@ int pc_planes(const Geom& g, int block, size_t lds) {
   return p < 1 ? 1 : p;
 }
 
-// The thread id, opaque to the optimiser: what a pass derives from it is
-// computed inside that pass.  Hoisted out of the solver's loop instead, the
-// passes' addresses took 571 spilled registers per thread.
-__device__ __forceinline__ int opaque_tid() {
-  int t = threadIdx.x;
-  asm volatile("" : "+v"(t));
-  return t;
-}
-
 template <typename T>
 struct PcCtx {
   typedef typename V2<T>::t T2;
@@ -196,13 +187,6 @@ struct PcCtx {
     return 2 * p * slab + (row - p * g.ny) * kPcLd + (e - row * g.nz);
   }
 };
-
-// Element `off` after the uniform address p (one 32-bit offset register).
-template <typename E>
-__device__ __forceinline__ E& at32(E* p, unsigned off) {
-  typedef typename std::conditional<std::is_const<E>::value, const char, char>::type C;
-  return *reinterpret_cast<E*>(reinterpret_cast<C*>(p) + (unsigned)(off * (unsigned)sizeof(E)));
-}
 
 // One wave: 16 columns (tile c) of L^T X R for the LDS plane at X, rows by
 // rows of 16 through epi(row tile, re, im).
