@@ -56,6 +56,27 @@ __device__ __forceinline__ E& at32(E* p, unsigned off) {
   return *reinterpret_cast<E*>(reinterpret_cast<C*>(p) + (unsigned)(off * (unsigned)sizeof(E)));
 }
 
+// Buffer access to element `off` bytes after the uniform address p: one
+// descriptor in scalar registers and one 32-bit offset per lane.  Through
+// plain pointers every array of a march took a 64-bit address in vector
+// registers and a 64-bit add per access.
+template <typename E>
+__device__ __forceinline__ E buf_load(const E* p, unsigned off) {
+  const __amdgpu_buffer_rsrc_t d =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<E*>(p), 0, 0xffffffffu, 0x00027000);
+  if constexpr (sizeof(E) == 4) return __builtin_bit_cast(E, __builtin_amdgcn_raw_buffer_load_b32(d, off, 0, 0));
+  else if constexpr (sizeof(E) == 8) return __builtin_bit_cast(E, __builtin_amdgcn_raw_buffer_load_b64(d, off, 0, 0));
+  else return __builtin_bit_cast(E, __builtin_amdgcn_raw_buffer_load_b128(d, off, 0, 0));
+}
+typedef unsigned buf_u2 __attribute__((ext_vector_type(2)));
+typedef unsigned buf_u4 __attribute__((ext_vector_type(4)));
+template <typename E>
+__device__ __forceinline__ void buf_store(E* p, unsigned off, const E& v) {
+  const __amdgpu_buffer_rsrc_t d = __builtin_amdgcn_make_buffer_rsrc(p, 0, 0xffffffffu, 0x00027000);
+  if constexpr (sizeof(E) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(buf_u2, v), d, off, 0, 0);
+  else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(buf_u4, v), d, off, 0, 0);
+}
+
 }  // namespace
 }  // namespace rpa
 
@@ -479,12 +500,12 @@ struct ResidPol {
   const double2* coef;            // w_p of x (LDS)
   static constexpr int kPF = 1;
   struct Aux { double v, psi, u; };
-  __device__ double2 load(int po, unsigned c) const { return at32(x + po, c); }
+  __device__ double2 load(int po, unsigned c) const { return buf_load(x + po, c * (unsigned)sizeof(*x)); }
   __device__ Aux aux(int po, unsigned c) const {
     Aux a;
-    a.v = at32(v + po, c);
-    a.psi = at32(psi + po, c);
-    a.u = at32(u + po, c);
+    a.v = buf_load(v + po, c * (unsigned)sizeof(*v));
+    a.psi = buf_load(psi + po, c * (unsigned)sizeof(*psi));
+    a.u = buf_load(u + po, c * (unsigned)sizeof(*u));
     return a;
   }
   __device__ void center(int po, unsigned c, double2 xv, double2 nb, const Aux& ax) {
@@ -496,7 +517,7 @@ struct ResidPol {
     const double rx = bval - axr;
     const double ry = -axi;
     TI2 rs; rs.x = (TI)rx; rs.y = (TI)ry;
-    at32(r + po, c) = rs;
+    buf_store(r + po, c * (unsigned)sizeof(rs), rs);
     const double sx = (double)rs.x, sy = (double)rs.y;
     rr += own ? rx * rx + ry * ry : 0.0;
     bb += own ? bval * bval : 0.0;
@@ -519,14 +540,14 @@ struct ApplyPol {
   bool own;
   static constexpr int kPF = 1;
   typedef T Aux;
-  __device__ T aux(int po, unsigned c) const { return at32(v + po, c); }
-  __device__ T2 load(int po, unsigned c) const { return at32(p + po, c); }
+  __device__ T aux(int po, unsigned c) const { return buf_load(v + po, c * (unsigned)sizeof(*v)); }
+  __device__ T2 load(int po, unsigned c) const { return buf_load(p + po, c * (unsigned)sizeof(*p)); }
   __device__ void center(int po, unsigned c, T2 pv, T2 nb, const T& vv) {
     const T a = c0 + vv - eps;
     T2 h;
     h.x = a * pv.x + om * pv.y + nb.x;
     h.y = a * pv.y - om * pv.x + nb.y;
-    at32(q + po, c) = h;
+    buf_store(q + po, c * (unsigned)sizeof(h), h);
     mu_re += own ? (double)(pv.x * h.x - pv.y * h.y) : 0.0;
     mu_im += own ? (double)(pv.x * h.y + pv.y * h.x) : 0.0;
   }
@@ -544,14 +565,14 @@ struct HPol {
   bool own;
   static constexpr int kPF = sizeof(T) == 4 ? 3 : 2;
   typedef T Aux;
-  __device__ T aux(int po, unsigned c) const { return at32(v + po, c); }
-  __device__ T2 load(int po, unsigned c) const { return at32(x + po, c); }
+  __device__ T aux(int po, unsigned c) const { return buf_load(v + po, c * (unsigned)sizeof(*v)); }
+  __device__ T2 load(int po, unsigned c) const { return buf_load(x + po, c * (unsigned)sizeof(*x)); }
   __device__ void center(int po, unsigned c, T2 xv, T2 nb, const T& vv) {
     const T a = c0 + vv - sr;
     T2 o;
     o.x = a * xv.x + si * xv.y + nb.x;
     o.y = a * xv.y - si * xv.x + nb.y;
-    at32(y + po, c) = o;
+    buf_store(y + po, c * (unsigned)sizeof(o), o);
   }
 };
 
