@@ -8,11 +8,20 @@ namespace rpa {
 
 namespace {
 
-// Tile blockIdx.x, vector blockIdx.y, planes of segment blockIdx.z.
+// Shifts that travel with the launch (n = 0: they are in device memory).
+struct HapplyShifts {
+  int n;
+  double re[kMaxFieldWeights], im[kMaxFieldWeights];
+};
+
+// Tile blockIdx.x, vector blockIdx.y, planes of segment blockIdx.z.  FP32: at
+// most 80 registers, so that two workgroups of a 768-thread tile share a
+// compute unit and one loads while the other computes (512 vectors of 48^3:
+// 305 us with one workgroup, 270 with two; 193 at the rate of a copy).
 template <typename T, int M, int PITCH>
-__global__ void __launch_bounds__(kMaxBlock) k_happly(Geom g, StencilCoef<T> cf, const T* v,
+__global__ void __launch_bounds__(kMaxBlock, sizeof(T) == 4 ? 6 : 1) k_happly(Geom g, StencilCoef<T> cf, const T* v,
                                                        const double* sr, const double* si,
-                                                       const void* x, void* y, int seg) {
+                                                       const void* x, void* y, int seg, HapplyShifts sh) {
   extern __shared__ double smem_d[];
   typedef typename V2<T>::t T2;
   constexpr bool FULL = M == 0;
@@ -23,7 +32,8 @@ __global__ void __launch_bounds__(kMaxBlock) k_happly(Geom g, StencilCoef<T> cf,
   p.x = reinterpret_cast<const T2*>(x) + base;
   p.y = reinterpret_cast<T2*>(y) + base;
   p.v = v; p.c0 = cf.c0;
-  p.sr = (T)sr[vec]; p.si = (T)si[vec];
+  p.sr = (T)(sh.n ? sh.re[vec] : sr[vec]);
+  p.si = (T)(sh.n ? sh.im[vec] : si[vec]);
   const int xb = blockIdx.z * seg, xe = min(g.nx, xb + seg);
   march<T, FULL, HS, PITCH>(g, cf, p, reinterpret_cast<T2*>(smem_d), blockIdx.x, blockIdx.x + 1, xb, xe);
 }
@@ -133,7 +143,8 @@ long long cocg_slot_bytes(const Geom& g, bool fp32_refine) {
 
 namespace {
 template <typename T>
-using HapplyKernel = void (*)(Geom, StencilCoef<T>, const T*, const double*, const double*, const void*, void*, int);
+using HapplyKernel = void (*)(Geom, StencilCoef<T>, const T*, const double*, const double*, const void*, void*, int,
+                              HapplyShifts);
 
 template <typename T, int P>
 HapplyKernel<T> happly_kernel(int m) {
@@ -144,7 +155,7 @@ HapplyKernel<T> happly_kernel(int m) {
 
 template <typename T>
 hipError_t launch_ht(const Geom& g, const StencilCoef<T>& cf, const T* v, const double* sr, const double* si,
-                     const void* x, void* y, int nvec, int block, size_t shmem, hipStream_t s) {
+                     const HapplyShifts& sh, const void* x, void* y, int nvec, int block, size_t shmem, hipStream_t s) {
   constexpr int kFill = 512;         // workgroups that fill the chip (two per compute unit)
   // few workgroups: split the march along x (each segment reads its own 12 halo planes)
   const long long wgs = (long long)g.ntiles * nvec;
@@ -155,7 +166,8 @@ hipError_t launch_ht(const Geom& g, const StencilCoef<T>& cf, const T* v, const 
   const HapplyKernel<T> k = pitch == 56   ? happly_kernel<T, 56>(m)
                             : pitch == 64 ? happly_kernel<T, 64>(m)
                                           : happly_kernel<T, 128>(m);
-  hipLaunchKernelGGL(k, dim3(g.ntiles, nvec, (g.nx + seg - 1) / seg), dim3(block), shmem, s, g, cf, v, sr, si, x, y, seg);
+  hipLaunchKernelGGL(k, dim3(g.ntiles, nvec, (g.nx + seg - 1) / seg), dim3(block), shmem, s, g, cf, v, sr, si, x, y, seg,
+                     sh);
   return hipGetLastError();
 }
 }  // namespace
@@ -169,11 +181,21 @@ hipError_t launch_cocg(const CocgArgs& a, bool fp32_refine, int grid, int block,
 
 hipError_t launch_happly(const Geom& g, const StencilCoef<double>& c64, const StencilCoef<float>& c32,
                          const double* v64, const float* v32, int nvec, const double* shift_re,
-                         const double* shift_im, const void* x, void* y, bool fp32,
+                         const double* shift_im, bool host_shifts, const void* x, void* y, bool fp32,
                          int block, hipStream_t s) {
   const size_t shmem = cocg_shmem_bytes(g, block, fp32, 0);
-  if (fp32) return launch_ht<float>(g, c32, v32, shift_re, shift_im, x, y, nvec, block, shmem, s);
-  return launch_ht<double>(g, c64, v64, shift_re, shift_im, x, y, nvec, block, shmem, s);
+  HapplyShifts sh{};
+  if (host_shifts) {
+    if (nvec > kMaxFieldWeights) return hipErrorInvalidValue;
+    sh.n = nvec;
+    for (int v = 0; v < nvec; ++v) {
+      sh.re[v] = shift_re[v];
+      sh.im[v] = shift_im[v];
+    }
+    shift_re = shift_im = nullptr;
+  }
+  if (fp32) return launch_ht<float>(g, c32, v32, shift_re, shift_im, sh, x, y, nvec, block, shmem, s);
+  return launch_ht<double>(g, c64, v64, shift_re, shift_im, sh, x, y, nvec, block, shmem, s);
 }
 
 hipError_t launch_nl_apply(const NlArgs& nl, long long N, int nvec, const void* x, void* y,

@@ -101,6 +101,7 @@ struct rpa_ctx {
   struct GraphEntry { hipGraph_t g; hipGraphExec_t e; unsigned epoch; };
   std::vector<std::pair<std::pair<int, int>, GraphEntry>> graphs;
   DevBuf dres;
+  double* host_sums = nullptr;       // pinned: per-plane sums the energy kernel writes to the host
   std::vector<int> order_h;
   int counts_h[2] = {0, 0};          // host staging of the two list lengths
   std::vector<hipEvent_t> evs;   // COCG launch timing events of the current call
@@ -942,6 +943,11 @@ rpa_status rpa_setup(const rpa_setup_params* p, void* stream, rpa_handle* out) {
   if (hipEventCreate(&h->ev0) != hipSuccess || hipEventCreate(&h->ev1) != hipSuccess)
     return fail(set_err(RPA_E_HIP, "hipEventCreate failed"));
 
+  if (hipHostMalloc((void**)&h->host_sums, kMaxTransformDim * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(set_err(RPA_E_OOM, "hipHostMalloc failed in setup"));
+  }
+
   // FD coefficients
   double w[kRadius + 1];
   fd_weights(kRadius, w);
@@ -1143,6 +1149,7 @@ rpa_status rpa_destroy(rpa_handle h) {
   drop_graphs(h);
   if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
   fr(h->dres.p);
+  if (h->host_sums) (void)hipHostFree(h->host_sums);
   for (hipEvent_t e : h->evs) (void)hipEventDestroy(e);
   if (h->ev0) (void)hipEventDestroy(h->ev0);
   if (h->ev1) (void)hipEventDestroy(h->ev1);
@@ -1181,13 +1188,18 @@ rpa_status rpa_hamiltonian_apply(rpa_handle h, int32_t nvec, const double* shift
   ARG_CHECK(shift_re && shift_im && x && y, "null pointer");
   ARG_CHECK(precision == RPA_FP64 || precision == RPA_FP32_REFINE, "bad precision");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  ENSURE(h, h->shifts, 2 * (size_t)nvec * sizeof(double));
-  HIPCHK(h, hipMemcpyAsync(h->shifts.p, shift_re, nvec * sizeof(double), hipMemcpyHostToDevice, s));
-  HIPCHK(h, hipMemcpyAsync(P<double>(h->shifts) + nvec, shift_im, nvec * sizeof(double),
-                           hipMemcpyHostToDevice, s));
+  // a few shifts travel with the launch, more go through device memory
+  const bool host_shifts = nvec <= kMaxFieldWeights;
+  if (!host_shifts) {
+    ENSURE(h, h->shifts, 2 * (size_t)nvec * sizeof(double));
+    HIPCHK(h, hipMemcpyAsync(h->shifts.p, shift_re, nvec * sizeof(double), hipMemcpyHostToDevice, s));
+    HIPCHK(h, hipMemcpyAsync(P<double>(h->shifts) + nvec, shift_im, nvec * sizeof(double),
+                             hipMemcpyHostToDevice, s));
+  }
   HIPCHK(h, hipEventRecord(h->ev0, s));
-  HIPCHK(h, launch_happly(h->geom, h->c64, h->c32, h->v64, h->v32, nvec, P<double>(h->shifts),
-                          P<double>(h->shifts) + nvec, x, y, precision == RPA_FP32_REFINE,
+  HIPCHK(h, launch_happly(h->geom, h->c64, h->c32, h->v64, h->v32, nvec,
+                          host_shifts ? shift_re : P<double>(h->shifts),
+                          host_shifts ? shift_im : P<double>(h->shifts) + nvec, host_shifts, x, y, precision == RPA_FP32_REFINE,
                           h->block, s));
   HIPCHK(h, hipEventRecord(h->ev1, s));
   if (h->nl.n_proj > 0) {
@@ -1729,7 +1741,6 @@ rpa_status rpa_energy_from_coarse(rpa_handle h, int32_t n_omega, const double* w
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const long long N = h->N;
   const double scale_fine = 1.0 / (2.0 * M_PI * h->dV);
-  int nblk = 256;
   if (h->fused && stride > 1 && n_omega <= kMaxFieldWeights) {
     // interpolation is linear: the frequencies are summed on the coarse set
     // (in the x pass) and one field is interpolated, summed as it is written
@@ -1738,27 +1749,30 @@ rpa_status rpa_energy_from_coarse(rpa_handle h, int32_t n_omega, const double* w
     const int* n = h->n;
     const int nc[3] = {n[0] / stride, n[1] / stride, n[2] / stride};
     const double* M = P<double>(h->interp_m);
-    nblk = n[0];
+    const int nblk = n[0];
     ENSURE(h, h->tmpA, (size_t)n[0] * nc[1] * nc[2] * sizeof(double));
-    ENSURE(h, h->partials, (size_t)nblk * sizeof(double));
     HIPCHK(h, launch_cols_fields(d_coarse, P<double>(h->tmpA), n_omega, weight, nc[0], n[0], nc[1] * nc[2],
                                  M + h->interp_dims[0], s));
     HIPCHK(h, launch_planes_energy(P<double>(h->tmpA), e_fine, n[0], nc[1], nc[2], n[1], n[2],
-                                   M + h->interp_dims[1], M + h->interp_dims[2], scale_fine,
-                                   P<double>(h->partials), s));
-  } else {
-    const double* dhat = d_coarse;
-    if (stride > 1) {
-      ENSURE(h, h->dhat, (size_t)n_omega * N * sizeof(double));
-      rpa_status r = do_interpolate(h, kind, stride, n_omega, d_coarse, P<double>(h->dhat), s);
-      if (r != RPA_OK) return r;
-      dhat = P<double>(h->dhat);
-    }
-    ENSURE(h, h->partials, nblk * sizeof(double) + (size_t)n_omega * sizeof(double));
-    double* wdev = P<double>(h->partials) + nblk;
-    HIPCHK(h, hipMemcpyAsync(wdev, weight, n_omega * sizeof(double), hipMemcpyHostToDevice, s));
-    HIPCHK(h, launch_weighted_sum(dhat, wdev, n_omega, N, scale_fine, e_fine, P<double>(h->partials), nblk, s));
+                                   M + h->interp_dims[1], M + h->interp_dims[2], scale_fine, h->host_sums, s));
+    HIPCHK(h, hipStreamSynchronize(s));
+    double tot = 0.0;
+    for (int i = 0; i < nblk; ++i) tot += h->host_sums[i];
+    *e_c = tot / (2.0 * M_PI);
+    return RPA_OK;
   }
+  const double* dhat = d_coarse;
+  if (stride > 1) {
+    ENSURE(h, h->dhat, (size_t)n_omega * N * sizeof(double));
+    rpa_status r = do_interpolate(h, kind, stride, n_omega, d_coarse, P<double>(h->dhat), s);
+    if (r != RPA_OK) return r;
+    dhat = P<double>(h->dhat);
+  }
+  const int nblk = 256;
+  ENSURE(h, h->partials, nblk * sizeof(double) + (size_t)n_omega * sizeof(double));
+  double* wdev = P<double>(h->partials) + nblk;
+  HIPCHK(h, hipMemcpyAsync(wdev, weight, n_omega * sizeof(double), hipMemcpyHostToDevice, s));
+  HIPCHK(h, launch_weighted_sum(dhat, wdev, n_omega, N, scale_fine, e_fine, P<double>(h->partials), nblk, s));
   std::vector<double> part(nblk);
   HIPCHK(h, hipMemcpyAsync(part.data(), h->partials.p, nblk * sizeof(double), hipMemcpyDeviceToHost, s));
   HIPCHK(h, hipStreamSynchronize(s));

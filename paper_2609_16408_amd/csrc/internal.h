@@ -143,6 +143,8 @@ typedef void (*CocgKernel)(CocgArgs);
 template <int V, int PITCH>
 CocgKernel cocg_kernel(int m, bool refine);
 
+constexpr int kMaxFieldWeights = 64;     // most host values that travel with a launch
+
 // Launchers (return hipError_t of the launch).
 hipError_t launch_cocg(const CocgArgs& a, bool fp32_refine, int grid, int block, size_t shmem,
                        hipStream_t s);
@@ -156,9 +158,10 @@ void cocg_pc_shape(Geom& g, int block, int n_proj);
 int cocg_prec_regs(const Geom& g, int block);
 int cocg_prec_regs_max();
 
+// shifts on the device, or (host_shifts, at most kMaxFieldWeights vectors) on the host
 hipError_t launch_happly(const Geom& g, const StencilCoef<double>& c64, const StencilCoef<float>& c32,
                          const double* v64, const float* v32, int nvec, const double* shift_re,
-                         const double* shift_im, const void* x, void* y, bool fp32,
+                         const double* shift_im, bool host_shifts, const void* x, void* y, bool fp32,
                          int block, hipStream_t s);
 // y[v] += V_nl x[v] for nvec vectors of N points (complex, FP32 or FP64);
 // coef: workspace of nvec * n_proj complex values of that precision.
@@ -173,7 +176,6 @@ hipError_t launch_set_onehot(double* q, long long stride, const long long* idx, 
 // Separable transforms (transform.hip).  The matrices are stored k-major,
 // zero-padded to multiples of 16: W[k * transform_pad(n_out) + o].
 constexpr int kMaxTransformDim = 128;    // largest dimension of the fused transforms
-constexpr int kMaxFieldWeights = 64;     // most fields summed by launch_cols_fields
 inline int transform_pad(int n) { return (n + 15) & ~15; }
 inline size_t transform_elems(int n_out, int n_in) { return (size_t)transform_pad(n_out) * transform_pad(n_in); }
 // dst = M padded; M is (n_out x n_in) row-major, or (n_in x n_out) with trans
@@ -195,10 +197,11 @@ hipError_t launch_cols_fields(const double* in, double* out, int n_fields, const
 // forward first-axis transform, times diag[row][column], inverse; in place allowed
 hipError_t launch_cols_scale(const double* in, double* out, int B, int n, int ncol, const double* fwd,
                              const double* inv, const double* diag, hipStream_t s);
-// the same for planar complex vectors with the diagonal 1 / (kin[row][column] + sigma_b)
+// the same for planar complex vectors with the diagonal 1 / (kin[row][column] + sigma_b);
+// sigma on the device, or (host_sigma, at most kMaxFieldWeights vectors) on the host
 hipError_t launch_cols_kinetic(const double* in, double* out, int nvec, int n, int ncol, const double* fwd,
                                const double* inv, const double* kin, const double* sig_re, const double* sig_im,
-                               hipStream_t s);
+                               bool host_sigma, hipStream_t s);
 
 // Per-axis form for larger dimensions: out = M applied along `axis` of a batch of 3D arrays.
 // in dims (B, d0, d1, d2); M is (n_out x n_in) row-major, n_in = d[axis];

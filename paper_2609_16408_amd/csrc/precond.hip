@@ -150,7 +150,9 @@ rpa_status rpa_kinetic_precond_apply(rpa_kinetic_precond p, int32_t nvec, const 
       if (hipMalloc((void**)&p->ws[k], bytes) != hipSuccess) { (void)hipGetLastError(); return RPA_E_OOM; }
     p->ws_bytes = bytes;
   }
-  if (nvec > p->sig_cap) {
+  // a few shifts travel with the launch, more go through device memory
+  const bool host_sigma = p->fused && nvec <= rpa::kMaxFieldWeights;
+  if (!host_sigma && nvec > p->sig_cap) {
     if (p->sig) (void)hipFree(p->sig);
     p->sig = nullptr;
     p->sig_cap = 0;
@@ -162,14 +164,16 @@ rpa_status rpa_kinetic_precond_apply(rpa_kinetic_precond p, int32_t nvec, const 
   }
   double* a = p->ws[0];
   const int* n = p->n;
-  hipError_t e = hipMemcpyAsync(p->sig, sigma_re, nvec * sizeof(double), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess)
+  hipError_t e = hipSuccess;
+  if (!host_sigma) e = hipMemcpyAsync(p->sig, sigma_re, nvec * sizeof(double), hipMemcpyHostToDevice, s);
+  if (!host_sigma && e == hipSuccess)
     e = hipMemcpyAsync(p->sig + nvec, sigma_im, nvec * sizeof(double), hipMemcpyHostToDevice, s);
   if (p->fused) {
     const int yz = n[1] * n[2];
     if (e == hipSuccess) e = rpa::launch_planes(x, a, (long long)B * n[0], n[1], n[2], n[1], n[2], p->V[1], p->V[2], s);
     if (e == hipSuccess)
-      e = rpa::launch_cols_kinetic(a, a, nvec, n[0], yz, p->V[0], p->VT[0], p->kin, p->sig, p->sig + nvec, s);
+      e = rpa::launch_cols_kinetic(a, a, nvec, n[0], yz, p->V[0], p->VT[0], p->kin,
+                                   host_sigma ? sigma_re : p->sig, host_sigma ? sigma_im : p->sig + nvec, host_sigma, s);
     if (e == hipSuccess) e = rpa::launch_planes(a, y, (long long)B * n[0], n[1], n[2], n[1], n[2], p->VT[1], p->VT[2], s);
     if (e != hipSuccess) { (void)hipGetLastError(); return RPA_E_HIP; }
     return RPA_OK;

@@ -130,10 +130,12 @@ __global__ void __launch_bounds__(512) k_plane(const double* __restrict__ in, do
   }
 }
 
-// Weights of the frequency sum folded into an interpolation's first pass.
-struct FieldWeights {
-  int n;                       // fields summed into one (1 with w[0] = 1: none)
-  double w[kMaxFieldWeights];
+// Small host values that travel with the launch: the weights of the frequency
+// sum folded into an interpolation's first pass (a), or the shifts of a
+// kinetic solve (a + i b).  n = 0: the shifts are in device memory.
+struct ColsArgs {
+  int n;
+  double a[kMaxFieldWeights], b[kMaxFieldWeights];
 };
 
 enum ColsMode {
@@ -153,7 +155,7 @@ __global__ void __launch_bounds__(256) k_cols(const double* __restrict__ in, dou
                                               int n_out, int ncol, const double* __restrict__ A1,
                                               const double* __restrict__ A2, const double* __restrict__ diag,
                                               const double* __restrict__ sig_re,
-                                              const double* __restrict__ sig_im, FieldWeights fw) {
+                                              const double* __restrict__ sig_im, ColsArgs fw) {
   const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
   const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   constexpr int CW = MODE == COLS_KINETIC ? 16 : 16 * NC;   // columns of a wave
@@ -191,7 +193,7 @@ __global__ void __launch_bounds__(256) k_cols(const double* __restrict__ in, dou
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
         const double v = r < n_in && ok[c] ? src[c][f * isz + (size_t)r * ncol] : 0.0;
-        if constexpr (MODE == COLS_FIELDS) x[c][q] += fw.w[f] * v;
+        if constexpr (MODE == COLS_FIELDS) x[c][q] += fw.a[f] * v;
         else x[c][q] = v;
       }
     }
@@ -237,8 +239,8 @@ __global__ void __launch_bounds__(256) k_cols(const double* __restrict__ in, dou
           for (int c = 0; c < NC; ++c)
             t[c][m][v] *= r < n_in ? diag[(size_t)r * ncol + col[c]] : 0.0;
         } else {
-          const double dr = (r < n_in ? diag[(size_t)r * ncol + col[0]] : 0.0) + sig_re[b];
-          const double di = sig_im[b];
+          const double dr = (r < n_in ? diag[(size_t)r * ncol + col[0]] : 0.0) + (fw.n ? fw.a[b] : sig_re[b]);
+          const double di = fw.n ? fw.b[b] : sig_im[b];
           const double den = dr * dr + di * di;
           const double xr = t[0][m][v], xi = t[1][m][v];
           t[0][m][v] = (xr * dr + xi * di) / den;
@@ -369,7 +371,7 @@ hipError_t plane_t(const double* in, double* out, long long planes, int na, int 
 
 template <int NC, int MODE>
 hipError_t cols_t(const double* in, double* out, int B, int n_in, int n_out, int ncol, const double* A1,
-                  const double* A2, const double* diag, const double* sr, const double* si, const FieldWeights& fw,
+                  const double* A2, const double* diag, const double* sr, const double* si, const ColsArgs& fw,
                   hipStream_t s) {
   const int waves = (ncol + (MODE == COLS_KINETIC ? 16 : 16 * NC) - 1) / (MODE == COLS_KINETIC ? 16 : 16 * NC);
   const int wpb = waves < 4 ? waves : 4;
@@ -421,29 +423,39 @@ hipError_t launch_planes_energy(const double* in, double* e_fine, long long plan
 
 hipError_t launch_cols(const double* in, double* out, int B, int n_in, int n_out, int ncol, const double* A,
                        hipStream_t s) {
-  return cols_t<1, COLS_ONCE>(in, out, B, n_in, n_out, ncol, A, nullptr, nullptr, nullptr, nullptr, FieldWeights{}, s);
+  return cols_t<1, COLS_ONCE>(in, out, B, n_in, n_out, ncol, A, nullptr, nullptr, nullptr, nullptr, ColsArgs{}, s);
 }
 
 hipError_t launch_cols_fields(const double* in, double* out, int n_fields, const double* w, int n_in, int n_out,
                               int ncol, const double* A, hipStream_t s) {
   if (n_fields > kMaxFieldWeights) return hipErrorInvalidValue;
-  FieldWeights fw{};
+  ColsArgs fw{};
   fw.n = n_fields;
-  for (int f = 0; f < n_fields; ++f) fw.w[f] = w[f];
+  for (int f = 0; f < n_fields; ++f) fw.a[f] = w[f];
   return cols_t<1, COLS_FIELDS>(in, out, 1, n_in, n_out, ncol, A, nullptr, nullptr, nullptr, nullptr, fw, s);
 }
 
 hipError_t launch_cols_scale(const double* in, double* out, int B, int n, int ncol, const double* fwd,
                              const double* inv, const double* diag, hipStream_t s) {
   if (n <= 80 && (long long)B * ncol >= 32 * 2048)
-    return cols_t<2, COLS_SCALE>(in, out, B, n, n, ncol, fwd, inv, diag, nullptr, nullptr, FieldWeights{}, s);
-  return cols_t<1, COLS_SCALE>(in, out, B, n, n, ncol, fwd, inv, diag, nullptr, nullptr, FieldWeights{}, s);
+    return cols_t<2, COLS_SCALE>(in, out, B, n, n, ncol, fwd, inv, diag, nullptr, nullptr, ColsArgs{}, s);
+  return cols_t<1, COLS_SCALE>(in, out, B, n, n, ncol, fwd, inv, diag, nullptr, nullptr, ColsArgs{}, s);
 }
 
 hipError_t launch_cols_kinetic(const double* in, double* out, int nvec, int n, int ncol, const double* fwd,
                                const double* inv, const double* kin, const double* sig_re, const double* sig_im,
-                               hipStream_t s) {
-  return cols_t<2, COLS_KINETIC>(in, out, nvec, n, n, ncol, fwd, inv, kin, sig_re, sig_im, FieldWeights{}, s);
+                               bool host_sigma, hipStream_t s) {
+  ColsArgs fw{};
+  if (host_sigma) {
+    if (nvec > kMaxFieldWeights) return hipErrorInvalidValue;
+    fw.n = nvec;
+    for (int v = 0; v < nvec; ++v) {
+      fw.a[v] = sig_re[v];
+      fw.b[v] = sig_im[v];
+    }
+    sig_re = sig_im = nullptr;
+  }
+  return cols_t<2, COLS_KINETIC>(in, out, nvec, n, n, ncol, fwd, inv, kin, sig_re, sig_im, fw, s);
 }
 
 void pad_k_major(const double* M, int n_out, int n_in, bool trans, double* dst) {
