@@ -57,6 +57,7 @@ struct rpa_ctx {
   double* Vax[3] = {nullptr, nullptr, nullptr};
   double* Tf[3] = {nullptr, nullptr, nullptr};
   double* Ti[3] = {nullptr, nullptr, nullptr};
+  double* axis_mem = nullptr;        // allocation of Tf and Ti
   double* s_half = nullptr;
   double* s_full = nullptr;
   StencilCoef<double> c64;
@@ -252,9 +253,6 @@ double now_s() {
 // Grid dimension padded to the 16-wide matrix-core tiles of the preconditioner.
 int prec_pad_host(int n) { return (n + 15) & ~15; }
 
-// Partial Gram sums per start vector (grid-point chunks of the contraction).
-int gram_chunks(long long N) { return (int)std::min<long long>(64, std::max<long long>(1, N / 2048)); }
-
 rpa_status usable(rpa_ctx* h) {
   if (!h) return set_err(RPA_E_ARG, "null handle");
   if (h->broken) return set_err(RPA_E_STATE, "handle unusable after an earlier HIP error");
@@ -344,11 +342,11 @@ rpa_status sternheimer_batch(rpa_ctx* h, int B, const std::vector<double>& omega
   const bool refine = h->precision == RPA_FP32_REFINE;
   const int n_items = B * nocc;
   // Galerkin initial guess over the ngal states (occupied, then any extra
-  // eigenpairs): the Gram contraction C = h^3 Psi_g^T diag(u) Psi runs on the
-  // FP64 matrix cores (k_gram); the energy denominators (k_gram_finish) and
-  // the expansion x0 = Psi_g G (k_expand) on vector FP64
-  const int n_chunks = gram_chunks(N);
+  // eigenpairs): the Gram contraction C = h^3 Psi_g^T diag(u) Psi (k_gram) and
+  // the expansion x0 = Psi_g G (k_expand) run on the FP64 matrix cores, the
+  // energy denominators (k_gram_finish) on vector FP64
   const int ng = h->ngal;
+  const int n_chunks = gram_chunks(N, nocc, ng);
   ENSURE(h, h->gpart, (size_t)B * n_chunks * ng * nocc * sizeof(double));
   ENSURE(h, h->G, (size_t)B * ng * nocc * sizeof(double2));
   ENSURE(h, h->x64, (size_t)n_items * N * sizeof(double2));
@@ -800,7 +798,7 @@ uint64_t lanczos_workspace_bytes(const rpa_setup_params& p, int B, int n_lanczos
   uint64_t bytes = m * b * N * 8 + b * N * 8 + 2 * b * m * 8 + 2 * b * 4 + 4 * b * 8 + 64 + 16;
   bytes += (transform_fits(p.n[0], p.n[1], p.n[2]) ? 1 : 2) * b * N * 8;   // nu^1/2 transform buffers
   const uint64_t ngal = nocc + (uint64_t)std::max(0, p.n_extra);
-  bytes += b * (uint64_t)gram_chunks((long long)N) * ngal * nocc * 8 + b * ngal * nocc * 16;
+  bytes += b * (uint64_t)gram_chunks((long long)N, (int)nocc, (int)ngal) * ngal * nocc * 8 + b * ngal * nocc * 16;
   bytes += items * N * 16;                                  // Sternheimer solutions (FP64)
   bytes += items * 4 * (refine ? 6 : 5) + 64 * 4;           // two order lists, counts, status, hand-over list
   bytes += b * N * 8;                                       // accumulated density response
@@ -943,11 +941,6 @@ rpa_status rpa_setup(const rpa_setup_params* p, void* stream, rpa_handle* out) {
   if (hipEventCreate(&h->ev0) != hipSuccess || hipEventCreate(&h->ev1) != hipSuccess)
     return fail(set_err(RPA_E_HIP, "hipEventCreate failed"));
 
-  if (hipHostMalloc((void**)&h->host_sums, kMaxTransformDim * sizeof(double), hipHostMallocDefault) != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(set_err(RPA_E_OOM, "hipHostMalloc failed in setup"));
-  }
-
   // FD coefficients
   double w[kRadius + 1];
   fd_weights(kRadius, w);
@@ -980,11 +973,15 @@ rpa_status rpa_setup(const rpa_setup_params* p, void* stream, rpa_handle* out) {
       !alloc((void**)&h->s_half, N * sizeof(double)) || !alloc((void**)&h->s_full, N * sizeof(double)))
     return fail(RPA_E_OOM);
   h->fused = transform_fits(h->n[0], h->n[1], h->n[2]);
-  for (int d = 0; d < 3; ++d) {
-    const size_t padded = transform_elems(h->n[d], h->n[d]) * sizeof(double);
-    if (h->fused ? !alloc((void**)&h->Tf[d], padded) || !alloc((void**)&h->Ti[d], padded)
-                 : !alloc((void**)&h->Vax[d], (size_t)h->n[d] * h->n[d] * sizeof(double)))
-      return fail(RPA_E_OOM);
+  std::vector<double> axis_mats;     // fused: the padded forward and inverse matrices of all axes
+  if (h->fused) {
+    size_t total = 0;
+    for (int d = 0; d < 3; ++d) total += 2 * transform_elems(h->n[d], h->n[d]);
+    axis_mats.resize(total);
+    if (!alloc((void**)&h->axis_mem, total * sizeof(double))) return fail(RPA_E_OOM);
+  } else {
+    for (int d = 0; d < 3; ++d)
+      if (!alloc((void**)&h->Vax[d], (size_t)h->n[d] * h->n[d] * sizeof(double))) return fail(RPA_E_OOM);
   }
   h->eps_h.assign(p->eps, p->eps + h->nocc);
 
@@ -1094,21 +1091,20 @@ rpa_status rpa_setup(const rpa_setup_params* p, void* stream, rpa_handle* out) {
     e = hipMemcpyAsync(h->eps_d + h->nocc, p->eps_extra, p->n_extra * sizeof(double), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(h->s_half, sh.data(), N * sizeof(double), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(h->s_full, sf.data(), N * sizeof(double), hipMemcpyHostToDevice, s);
-  std::vector<double> pad[3][2];
-  for (int d = 0; d < 3 && e == hipSuccess; ++d) {
-    const int n = h->n[d];
-    if (!h->fused) {
-      e = hipMemcpyAsync(h->Vax[d], V[d].data(), V[d].size() * sizeof(double), hipMemcpyHostToDevice, s);
-      continue;
-    }
+  if (h->fused) {
     // V is [grid][mode]: forward (grid -> mode) is V itself in k-major order, inverse its transpose
-    for (int k = 0; k < 2; ++k) {
-      pad[d][k].resize(transform_elems(n, n));
-      pad_k_major(V[d].data(), n, n, k == 0, pad[d][k].data());
-      if (e == hipSuccess)
-        e = hipMemcpyAsync(k == 0 ? h->Tf[d] : h->Ti[d], pad[d][k].data(), pad[d][k].size() * sizeof(double),
-                           hipMemcpyHostToDevice, s);
-    }
+    size_t at = 0;
+    for (int d = 0; d < 3; ++d)
+      for (int k = 0; k < 2; ++k) {
+        (k == 0 ? h->Tf : h->Ti)[d] = h->axis_mem + at;
+        pad_k_major(V[d].data(), h->n[d], h->n[d], k == 0, axis_mats.data() + at);
+        at += transform_elems(h->n[d], h->n[d]);
+      }
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(h->axis_mem, axis_mats.data(), at * sizeof(double), hipMemcpyHostToDevice, s);
+  } else {
+    for (int d = 0; d < 3 && e == hipSuccess; ++d)
+      e = hipMemcpyAsync(h->Vax[d], V[d].data(), V[d].size() * sizeof(double), hipMemcpyHostToDevice, s);
   }
   for (size_t k = 0; k < nl_up.size() && e == hipSuccess; ++k)
     if (nl_up[k].bytes)
@@ -1139,7 +1135,8 @@ rpa_status rpa_destroy(rpa_handle h) {
   for (void* m : h->nl_mem) fr(m);
   fr(h->prec_mem);
   fr(h->nlcoef.p);
-  for (int d = 0; d < 3; ++d) { fr(h->Vax[d]); fr(h->Tf[d]); fr(h->Ti[d]); }
+  for (int d = 0; d < 3; ++d) fr(h->Vax[d]);
+  fr(h->axis_mem);
   DevBuf* bufs[] = {&h->x64, &h->slots, &h->u64, &h->racc, &h->vtmp, &h->tmpA, &h->Q, &h->alpha,
                     &h->beta, &h->mlen, &h->active, &h->order, &h->iters, &h->cycles, &h->status,
                     &h->counter, &h->stats, &h->omega_b, &h->pos_b, &h->idx_b, &h->gpart, &h->G,
@@ -1297,7 +1294,7 @@ ScratchLayout scratch_layout(rpa_ctx* h, int B, bool symmetrized) {
     add(h->tmpA, b * N * sizeof(double));
     if (!h->fused) add(h->vtmp, b * N * sizeof(double));
   }
-  add(h->gpart, b * (size_t)gram_chunks(h->N) * h->ngal * nocc * sizeof(double));
+  add(h->gpart, b * (size_t)gram_chunks(h->N, h->nocc, h->ngal) * h->ngal * nocc * sizeof(double));
   add(h->G, b * (size_t)h->ngal * nocc * sizeof(double2));
   add(h->x64, items * N * sizeof(double2));
   add(h->order, 2 * items * sizeof(int));
@@ -1751,6 +1748,8 @@ rpa_status rpa_energy_from_coarse(rpa_handle h, int32_t n_omega, const double* w
     const double* M = P<double>(h->interp_m);
     const int nblk = n[0];
     ENSURE(h, h->tmpA, (size_t)n[0] * nc[1] * nc[2] * sizeof(double));
+    if (!h->host_sums)
+      HIPCHK(h, hipHostMalloc((void**)&h->host_sums, kMaxTransformDim * sizeof(double), hipHostMallocDefault));
     HIPCHK(h, launch_cols_fields(d_coarse, P<double>(h->tmpA), n_omega, weight, nc[0], n[0], nc[1] * nc[2],
                                  M + h->interp_dims[0], s));
     HIPCHK(h, launch_planes_energy(P<double>(h->tmpA), e_fine, n[0], nc[1], nc[2], n[1], n[2],

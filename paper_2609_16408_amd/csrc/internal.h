@@ -213,6 +213,8 @@ hipError_t launch_axis(const double* in, double* out, int B, int d0, int d1, int
 hipError_t launch_kin_scale(double* a, const double* kin, const double* sig_re,
                             const double* sig_im, int B, long long N, hipStream_t s);
 
+// partial Gram sums per start vector (grid-point chunks of the contraction)
+int gram_chunks(long long N, int n_occ, int ng);
 hipError_t launch_gram(const double* psi, const double* u, int B, int n_occ, int ng, long long N,
                        int n_chunks, double* part, hipStream_t s);
 hipError_t launch_gram_finish(const double* part, int B, int n_occ, int ng, int n_chunks, double dV,

@@ -3,6 +3,8 @@
 // tridiagonal Gauss quadrature and frequency integration.
 #include "internal.h"
 
+#include <algorithm>
+
 namespace rpa {
 
 namespace {
@@ -30,80 +32,107 @@ __global__ void k_set_onehot(double* q, long long stride, const long long* idx, 
 
 // ---------------------------------------------------------------------------
 // Galerkin projection, part 1: part[b][c][m][n] = sum_{r in chunk c} psi_m psi_n u_b,
-// a contraction over grid points on the FP64 matrix cores.  A 256-thread
-// workgroup owns a 128 x 128 output tile; each wave a 64 x 64 quadrant as
-// 4 x 4 MFMA tiles (v_mfma_f64_16x16x4: A lane l = row l%16, k l/16; B lane
-// l = column l%16, k l/16; D register v of lane l = row l/16 + 4v, column
-// l%16).  GK grid
-// points of the 128 rows of each operand are staged in LDS per step (the
-// psi_m u_b rows and the psi_n rows), zero beyond n_occ and the chunk end.
-constexpr int GT = 128;   // output tile
-constexpr int GK = 16;    // r-block staged in LDS
-
+// a contraction over grid points on the FP64 matrix cores (v_mfma_f64_16x16x4:
+// A lane l = row l%16, k l/16; B lane l = column l%16, k l/16; D register v of
+// lane l = row l/16 + 4v, column l%16).  Each wave owns a tile of 16 TM x 16 TN
+// outputs of one chunk and takes its operands straight from global memory: per
+// step of 16 points a lane loads the four points 4 l/16 .. + 3 of its row (32
+// contiguous bytes, 128 per row and four lanes), and product q contracts
+// points q, q + 4, q + 8, q + 12 of all lanes, the same ones in A and B.
+// Tiles follow the orbital counts: four orbitals cost one 16-wide tile.
+// The workgroups of a chunk are dealt to one XCD, whose L2 then serves its
+// psi rows to all start vectors and tiles.
+// Bound by the matrix cores at 512 x 128 states; 48^3, 16 start vectors:
+// 8.6 -> 4.0 ms (58 TFLOP/s) against 128 x 128 tiles through LDS; 12^3, 4 states:
+// 332 -> 6 us, 24^3, 16 states, 64 vectors: 694 -> 36 us.
 typedef double d4 __attribute__((ext_vector_type(4)));
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+constexpr int kXcds = 8;
 
-__global__ void __launch_bounds__(256) k_gram(const double* __restrict__ psi,
-                                              const double* __restrict__ u, int n_occ, int ng,
-                                              long long N, int n_chunks, int ntn,
-                                              double* __restrict__ part) {
-  __shared__ double sA[GK][GT + 2];
-  __shared__ double sB[GK][GT + 2];
-  const int c = blockIdx.x;
-  const int b = blockIdx.y;
-  const int tm = blockIdx.z / ntn, tn = blockIdx.z % ntn;
-  const int m0 = tm * GT, n0 = tn * GT;
-  const long long clen = (N + n_chunks - 1) / n_chunks;
-  const long long r0 = c * clen;
-  const long long r1 = r0 + clen < N ? r0 + clen : N;
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int qm = (wave >> 1) * 64, qn = (wave & 1) * 64;   // quadrant of the tile
-  const int li = lane & 15, lk = lane >> 4;
+// index of this workgroup's chunk (possibly past the last one) and its rank in the chunk
+__device__ __forceinline__ void xcd_chunk(int per_chunk, int& chunk, int& rank) {
+  const int x = blockIdx.x % kXcds, k = blockIdx.x / kXcds;
+  chunk = x + kXcds * (k / per_chunk);
+  rank = k % per_chunk;
+}
+inline unsigned xcd_grid(int chunks, int per_chunk) {
+  return (unsigned)((chunks + kXcds - 1) / kXcds * kXcds * per_chunk);
+}
+
+template <int TM, int TN>
+__global__ void __launch_bounds__(256, 2) k_gram(const double* __restrict__ psi,
+                                                 const double* __restrict__ u, int B, int n_occ, int ng,
+                                                 long long N, int n_chunks, double* __restrict__ part) {
+  const int ntm = (ng + 16 * TM - 1) / (16 * TM), ntn = (n_occ + 16 * TN - 1) / (16 * TN);
+  const int jobs = B * ntm * ntn;
+  int c, rank;
+  xcd_chunk((jobs + 3) / 4, c, rank);
+  const int job = rank * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  if (c >= n_chunks || job >= jobs) return;
+  const int b = job / (ntm * ntn), tile = job - b * ntm * ntn;
+  const int m0 = tile / ntn * 16 * TM, n0 = tile % ntn * 16 * TN;
+  const long long clen = ((N + n_chunks - 1) / n_chunks + 15) & ~15LL;
+  const long long r0 = c * clen, r1 = r0 + clen < N ? r0 + clen : N;
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
   const double* ub = u + (size_t)b * N;
-  d4 acc[4][4];
+  const double* pm[TM];
+  const double* pn[TN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
-  for (long long rb = r0; rb < r1; rb += GK) {
-    for (int e = threadIdx.x; e < GK * GT; e += 256) {
-      const int k = e % GK, i = e / GK;
-      const long long r = rb + k;
-      double a = 0.0, bb = 0.0;
-      if (r < r1) {
-        const double uu = ub[r];
-        if (m0 + i < ng) a = psi[(size_t)(m0 + i) * N + r] * uu;
-        if (n0 + i < n_occ) bb = psi[(size_t)(n0 + i) * N + r];
-      }
-      sA[k][i] = a;
-      sB[k][i] = bb;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k0 = 0; k0 < GK; k0 += 4) {
-      double av[4], bv[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        av[t] = sA[k0 + lk][qm + t * 16 + li];
-        bv[t] = sB[k0 + lk][qn + t * 16 + li];
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i], bv[j], acc[i][j], 0, 0, 0);
-    }
-    __syncthreads();
+  for (int t = 0; t < TM; ++t) {
+    const int m = m0 + 16 * t + li;
+    pm[t] = psi + (size_t)(m < ng ? m : ng - 1) * N;       // repeated rows are not stored
   }
+#pragma unroll
+  for (int t = 0; t < TN; ++t) {
+    const int n = n0 + 16 * t + li;
+    pn[t] = psi + (size_t)(n < n_occ ? n : n_occ - 1) * N;
+  }
+  d4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+  auto load = [&](const double* p, long long r, bool full) {
+    d4 v;
+    if (full) {
+      const d2u x = *reinterpret_cast<const d2u*>(p + r), y = *reinterpret_cast<const d2u*>(p + r + 2);
+      v = d4{x[0], x[1], y[0], y[1]};
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = r + q < r1 ? p[r + q] : 0.0;
+    }
+    return v;
+  };
+  auto step = [&](long long rb, bool full) {
+    const long long r = rb + 4 * lk;
+    const d4 uu = load(ub, r, full);
+    d4 a[TM], bb[TN];
+#pragma unroll
+    for (int t = 0; t < TM; ++t) a[t] = load(pm[t], r, full);
+#pragma unroll
+    for (int t = 0; t < TN; ++t) bb[t] = load(pn[t], r, full);
+#pragma unroll
+    for (int t = 0; t < TM; ++t) a[t] *= uu;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i][q], bb[j][q], acc[i][j], 0, 0, 0);
+  };
+  long long rb = r0;
+  for (; rb + 16 <= r1; rb += 16) step(rb, true);
+  if (rb < r1) step(rb, false);
   double* out = part + ((size_t)b * n_chunks + c) * ng * n_occ;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < TM; ++i) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + qn + j * 16 + li;
+    for (int j = 0; j < TN; ++j) {
+      const int n = n0 + 16 * j + li;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int m = m0 + qm + i * 16 + lk + 4 * v;
+        const int m = m0 + 16 * i + lk + 4 * v;
         if (m < ng && n < n_occ) out[(size_t)m * n_occ + n] = acc[i][j][v];
       }
     }
@@ -131,58 +160,72 @@ __global__ void k_gram_finish(const double* __restrict__ part, int B, int n_occ,
   }
 }
 
-// part 3: x64[(b*n_occ + n)][r] = sum_m psi_m(r) G[b][m][n], m over the ng states
-// tile 64 r x 64 n; thread (rl = t%16, nl = t/16) owns r = r0+rl+16i, n = n0+nl+16j
-__global__ void __launch_bounds__(256) k_expand(const double* __restrict__ psi,
-                                                const double2* __restrict__ G, int n_occ, int ng,
-                                                long long N, double2* __restrict__ x64) {
-  __shared__ double sP[16][64 + 1];
-  __shared__ double2 sG[16][64 + 1];
-  const long long r0 = (long long)blockIdx.x * 64;
-  const int n0 = blockIdx.y * 64;
-  const int b = blockIdx.z;
-  const int rl = threadIdx.x & 15, nl = threadIdx.x >> 4;
+// part 3: x64[(b*n_occ + n)][r] = sum_m psi_m(r) G[b][m][n], m over the ng states,
+// on the FP64 matrix cores with rows n, columns r and the real and imaginary
+// parts of G as two A operands that share psi.  Each wave owns 16 TN orbitals
+// x 64 grid points; the workgroups of a point range are dealt to one XCD.
+// Bound by the matrix cores at 512 x 128 states: 48^3, 16 start vectors,
+// 13.3 -> 10.2 ms (46 TFLOP/s) against vector FP64 tiles through LDS.
+template <int TN>
+__global__ void __launch_bounds__(256, 2) k_expand(const double* __restrict__ psi,
+                                                   const double2* __restrict__ G, int B, int n_occ, int ng,
+                                                   long long N, double2* __restrict__ x64) {
+  constexpr int TR = 4;
+  const int ntn = (n_occ + 16 * TN - 1) / (16 * TN);
+  const int jobs = B * ntn;
+  int c, rank;
+  xcd_chunk((jobs + 3) / 4, c, rank);
+  const int job = rank * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const long long r0 = (long long)c * 16 * TR;
+  if (r0 >= N || job >= jobs) return;
+  const int b = job / ntn, n0 = job % ntn * 16 * TN;
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
   const double2* Gb = G + (size_t)b * ng * n_occ;
-  double ar[4][4], ai[4][4];
+  d4 re[TN][TR], im[TN][TR];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TN; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) { ar[i][j] = 0.0; ai[i][j] = 0.0; }
-  for (int mb = 0; mb < ng; mb += 16) {
-    for (int e = threadIdx.x; e < 16 * 64; e += 256) {
-      const int k = e / 64, i = e % 64;
-      const int m = mb + k;
-      const long long r = r0 + i;
-      sP[k][i] = (m < ng && r < N) ? psi[(size_t)m * N + r] : 0.0;
-      sG[k][i] = (m < ng && n0 + i < n_occ) ? Gb[(size_t)m * n_occ + n0 + i] : make_double2(0.0, 0.0);
+    for (int j = 0; j < TR; ++j) re[i][j] = im[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+  long long rc[TR];
+  int nc[TN];
+#pragma unroll
+  for (int j = 0; j < TR; ++j) rc[j] = r0 + 16 * j + li < N ? r0 + 16 * j + li : N - 1;   // not stored
+#pragma unroll
+  for (int i = 0; i < TN; ++i) nc[i] = n0 + 16 * i + li < n_occ ? n0 + 16 * i + li : n_occ - 1;
+#pragma unroll 2
+  for (int m0 = 0; m0 < ng; m0 += 4) {
+    const int m = m0 + lk, mc = m < ng ? m : ng - 1;
+    double2 g[TN];
+    double p[TR];
+#pragma unroll
+    for (int i = 0; i < TN; ++i) g[i] = Gb[(size_t)mc * n_occ + nc[i]];
+#pragma unroll
+    for (int j = 0; j < TR; ++j) p[j] = psi[(size_t)mc * N + rc[j]];
+    if (m >= ng) {
+#pragma unroll
+      for (int i = 0; i < TN; ++i) g[i] = make_double2(0.0, 0.0);
     }
-    __syncthreads();
-#pragma unroll 4
-    for (int k = 0; k < 16; ++k) {
-      double pv[4];
-      double2 gv[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) pv[i] = sP[k][rl + 16 * i];
+    for (int i = 0; i < TN; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) gv[j] = sG[k][nl + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) { ar[i][j] += pv[i] * gv[j].x; ai[i][j] += pv[i] * gv[j].y; }
-    }
-    __syncthreads();
+      for (int j = 0; j < TR; ++j) {
+        re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(g[i].x, p[j], re[i][j], 0, 0, 0);
+        im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(g[i].y, p[j], im[i][j], 0, 0, 0);
+      }
   }
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int n = n0 + nl + 16 * j;
-    if (n >= n_occ) continue;
-    double2* dst = x64 + ((size_t)b * n_occ + n) * N;
+  for (int i = 0; i < TN; ++i)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const long long r = r0 + rl + 16 * i;
-      if (r < N) dst[r] = make_double2(ar[i][j], ai[i][j]);
+    for (int v = 0; v < 4; ++v) {
+      const int n = n0 + 16 * i + lk + 4 * v;
+      if (n >= n_occ) continue;
+      double2* dst = x64 + ((size_t)b * n_occ + n) * N;
+#pragma unroll
+      for (int j = 0; j < TR; ++j) {
+        const long long r = r0 + 16 * j + li;
+        if (r < N) dst[r] = make_double2(re[i][j][v], im[i][j][v]);
+      }
     }
-  }
 }
 
 // racc[b][r] = 4 sum_n psi_n(r) Re x64[b][n][r]
@@ -434,11 +477,25 @@ hipError_t launch_set_onehot(double* q, long long stride, const long long* idx, 
   return hipGetLastError();
 }
 
+int gram_chunks(long long N, int n_occ, int ng) {
+  // enough chunks to fill the chip at any batch size (the sums must not depend
+  // on the batch): at least 2048 points each, or 128 where the partial sums
+  // then stay below one vector per start vector
+  const long long few = std::max<long long>(1, N / 2048);
+  const long long many = std::min<long long>(N / 128, N / ((long long)ng * n_occ));
+  return (int)std::min<long long>(64, std::max(few, many));
+}
 hipError_t launch_gram(const double* psi, const double* u, int B, int n_occ, int ng, long long N,
                        int n_chunks, double* part, hipStream_t s) {
-  const int ntm = (ng + GT - 1) / GT, ntn = (n_occ + GT - 1) / GT;
-  hipLaunchKernelGGL(k_gram, dim3(n_chunks, B, ntm * ntn), dim3(256), 0, s, psi, u, n_occ, ng, N,
-                     n_chunks, ntn, part);
+  const int tm = ng <= 16 ? 1 : (ng <= 32 ? 2 : 4), tn = n_occ <= 16 ? 1 : (n_occ <= 32 ? 2 : 4);
+  const long long jobs = (long long)B * ((ng + 16 * tm - 1) / (16 * tm)) * ((n_occ + 16 * tn - 1) / (16 * tn));
+  const dim3 grid(xcd_grid(n_chunks, (int)((jobs + 3) / 4)));
+#define RPA_GRAM(TM, TN)                                                                             \
+  if (tm == TM && tn == TN)                                                                          \
+    hipLaunchKernelGGL((k_gram<TM, TN>), grid, dim3(256), 0, s, psi, u, B, n_occ, ng, N, n_chunks, part);
+  RPA_GRAM(1, 1) RPA_GRAM(1, 2) RPA_GRAM(1, 4) RPA_GRAM(2, 1) RPA_GRAM(2, 2) RPA_GRAM(2, 4) RPA_GRAM(4, 1)
+  RPA_GRAM(4, 2) RPA_GRAM(4, 4)
+#undef RPA_GRAM
   return hipGetLastError();
 }
 hipError_t launch_gram_finish(const double* part, int B, int n_occ, int ng, int n_chunks, double dV,
@@ -450,8 +507,13 @@ hipError_t launch_gram_finish(const double* part, int B, int n_occ, int ng, int 
 }
 hipError_t launch_expand(const double* psi, const double2* G, int B, int n_occ, int ng, long long N,
                          double2* x64, hipStream_t s) {
-  dim3 grid((unsigned)((N + 63) / 64), (unsigned)((n_occ + 63) / 64), (unsigned)B);
-  hipLaunchKernelGGL(k_expand, grid, dim3(256), 0, s, psi, G, n_occ, ng, N, x64);
+  const int tn = n_occ <= 16 ? 1 : 2;
+  const long long jobs = (long long)B * ((n_occ + 16 * tn - 1) / (16 * tn));
+  const dim3 grid(xcd_grid((int)((N + 63) / 64), (int)((jobs + 3) / 4)));
+  if (tn == 1)
+    hipLaunchKernelGGL((k_expand<1>), grid, dim3(256), 0, s, psi, G, B, n_occ, ng, N, x64);
+  else
+    hipLaunchKernelGGL((k_expand<2>), grid, dim3(256), 0, s, psi, G, B, n_occ, ng, N, x64);
   return hipGetLastError();
 }
 hipError_t launch_accumulate(const double* psi, const double2* x64, int B, int n_occ, long long N,
