@@ -172,10 +172,21 @@ hipError_t launch_ht(const Geom& g, const StencilCoef<T>& cf, const T* v, const 
 }
 }  // namespace
 
-hipError_t launch_cocg(const CocgArgs& a, bool fp32_refine, int grid, int block, size_t shmem,
+hipError_t launch_cocg(const CocgArgs& a, bool fp32_refine, int grid, int block, size_t shmem, int num_cu,
                        hipStream_t s) {
   if (a.prec) block = a.g.pc_block;
-  hipLaunchKernelGGL(cocg_pick(a.g, block, fp32_refine, a.nl.n_proj > 0), dim3(grid), dim3(block), shmem, s, a);
+  CocgArgs b = a;
+  if (!a.prec) {
+    // residual elements in the LDS that this many workgroups per compute unit
+    // leave free, in whole trips of the streaming sweeps
+    const int per_cu = std::max(1, (grid + num_cu - 1) / num_cu);
+    const long long free_lds = 160 * 1024 / per_cu - (long long)shmem - 256;
+    const long long trip = (long long)kSweep * block, elem = fp32_refine ? sizeof(float2) : sizeof(double2);
+    const long long n = std::min(a.g.N, std::max(0LL, free_lds) / elem);
+    b.r_lds = (int)(n / trip * trip);
+    shmem += (size_t)b.r_lds * elem;
+  }
+  hipLaunchKernelGGL(cocg_pick(a.g, block, fp32_refine, a.nl.n_proj > 0), dim3(grid), dim3(block), shmem, s, b);
   return hipGetLastError();
 }
 

@@ -17,8 +17,11 @@
 //    pending alpha p (5 vector passes), the stencil q = A p with mu = p^T q
 //    (about 2.5), r -= alpha q with r^T r and ||r||^2 (3).  The stencil's
 //    operand is one vector that it only reads, so the march carries nothing
-//    but its column and the potential.  All reductions are per workgroup in a
-//    fixed order, so results do not depend on scheduling.
+//    but its column and the potential.  The residual's first elements stay in
+//    the LDS that the march leaves free (cells up to 24^3 are bound by the
+//    traffic of all workgroups' vectors through the last-level cache, about
+//    7 TB/s).  All reductions are per workgroup in a fixed order, so results
+//    do not depend on scheduling.
 //  * FP32_REFINE: COCG in FP32 with reliable updates: the FP32 correction is
 //    folded into the FP64 solution and the residual replaced by the FP64
 //    residual r = b - A x (an FP64 stencil sweep) whenever the recursive
@@ -595,11 +598,11 @@ struct NlPoint {
 constexpr int kSweep = 4;
 
 template <class Load, class Use>
-__device__ __forceinline__ void stream_sweep(int N, Load&& load, Use&& use) {
+__device__ __forceinline__ int stream_sweep(int begin, int end, Load&& load, Use&& use) {
   const int trip = kSweep * (int)blockDim.x;
-  const int full = N / trip;               // trips without a bounds check
-  if (full > 0) load(0, 0);
-  int i0 = 0;
+  const int full = (end - begin) / trip;   // trips without a bounds check
+  if (full > 0) load(begin, 0);
+  int i0 = begin;
 #pragma unroll 1
   for (int k = 0; k + 2 <= full; k += 2) {
     load(i0 + trip, 1);
@@ -612,11 +615,22 @@ __device__ __forceinline__ void stream_sweep(int N, Load&& load, Use&& use) {
     use(i0, 0);
     i0 += trip;
   }
+  return i0;                               // first element not done
 }
+
+// The residual of one system: its first `nl` elements (whole trips of the
+// sweeps) live in LDS, the others in global memory.  Only the streaming
+// sweeps touch it, each thread its own elements.
+template <typename T>
+struct SplitVec {
+  typename V2<T>::t* l;
+  typename V2<T>::t* g;
+  int nl;
+};
 
 // r -= alpha (q + V_nl p);  returns ||r||^2, r^T r.
 template <typename T, bool NL>
-__device__ __forceinline__ void residual_sweep(int N, typename V2<T>::t* r, const typename V2<T>::t* q, T ar, T ai,
+__device__ __forceinline__ void residual_sweep(int N, const SplitVec<T>& r, const typename V2<T>::t* q, T ar, T ai,
                                                const NlPoint<T>& nl, double& rr, double& rho_re, double& rho_im) {
   typedef typename V2<T>::t T2;
   const int st = blockDim.x;
@@ -626,48 +640,59 @@ __device__ __forceinline__ void residual_sweep(int N, typename V2<T>::t* r, cons
     if constexpr (NL) nl_point<T>(nl.ptr, nl.proj, nl.v, nl.coef, i + (int)tid, b.x, b.y);
     a.x -= ar * b.x - ai * b.y;
     a.y -= ar * b.y + ai * b.x;
-    at32(r + i, tid) = a;
     const double sx = (double)a.x, sy = (double)a.y;
     rr += sx * sx + sy * sy;
     rho_re += sx * sx - sy * sy;
     rho_im += 2.0 * sx * sy;
+    return a;
   };
-  stream_sweep(
-      N,
+  int i = stream_sweep(
+      0, r.nl,
+      [&](int i0, int h) RPA_INLINE {
+#pragma unroll
+        for (int u = 0; u < kSweep; ++u) qv[h][u] = at32(q + (i0 + u * st), tid);
+      },
+      [&](int i0, int h) RPA_INLINE {
+#pragma unroll
+        for (int u = 0; u < kSweep; ++u) {
+          T2* rl = r.l + (i0 + u * st + (int)tid);
+          *rl = one(i0 + u * st, qv[h][u], *rl);
+        }
+      });
+  i = stream_sweep(
+      i, N,
       [&](int i0, int h) RPA_INLINE {
 #pragma unroll
         for (int u = 0; u < kSweep; ++u) {
           qv[h][u] = at32(q + (i0 + u * st), tid);
-          rv[h][u] = at32(r + (i0 + u * st), tid);
+          rv[h][u] = at32(r.g + (i0 + u * st), tid);
         }
       },
       [&](int i0, int h) RPA_INLINE {
 #pragma unroll
-        for (int u = 0; u < kSweep; ++u) one(i0 + u * st, qv[h][u], rv[h][u]);
+        for (int u = 0; u < kSweep; ++u) at32(r.g + (i0 + u * st), tid) = one(i0 + u * st, qv[h][u], rv[h][u]);
       });
-  for (int i = N / (kSweep * st) * (kSweep * st); i + (int)tid < N; i += st) one(i, at32(q + i, tid), at32(r + i, tid));
+  for (; i + (int)tid < N; i += st) at32(r.g + i, tid) = one(i, at32(q + i, tid), at32(r.g + i, tid));
 }
 
 // x (pend) += alpha p_old (xfresh: x = alpha p_old);  p = first ? r : r + beta p.
 template <typename T>
-__device__ __forceinline__ void direction_sweep(int N, const typename V2<T>::t* r, typename V2<T>::t* p,
+__device__ __forceinline__ void direction_sweep(int N, const SplitVec<T>& r, typename V2<T>::t* p,
                                                 typename V2<T>::t* x, T ar, T ai, T br, T bi, bool first, bool pend,
                                                 bool xfresh) {
   typedef typename V2<T>::t T2;
   const int st = blockDim.x;
   const unsigned tid = opaque_tid();
-  if (first) {
-    for (int i = 0; i + (int)tid < N; i += st) at32(p + i, tid) = at32(r + i, tid);
-    return;
-  }
-  if (!pend || xfresh) {
-    // the iteration after a fold: rare, so not pipelined
+  if (first || !pend || xfresh) {
+    // the first iteration and the one after a fold: rare, so not pipelined
     for (int i = 0; i + (int)tid < N; i += st) {
-      T2 a = at32(r + i, tid);
-      const T2 b = at32(p + i, tid);
-      if (pend) at32(x + i, tid) = {ar * b.x - ai * b.y, ar * b.y + ai * b.x};
-      a.x += br * b.x - bi * b.y;
-      a.y += br * b.y + bi * b.x;
+      T2 a = i < r.nl ? r.l[i + (int)tid] : at32(r.g + i, tid);
+      if (!first) {
+        const T2 b = at32(p + i, tid);
+        if (pend) at32(x + i, tid) = {ar * b.x - ai * b.y, ar * b.y + ai * b.x};
+        a.x += br * b.x - bi * b.y;
+        a.y += br * b.y + bi * b.x;
+      }
       at32(p + i, tid) = a;
     }
     return;
@@ -681,12 +706,25 @@ __device__ __forceinline__ void direction_sweep(int N, const typename V2<T>::t* 
     a.y += br * b.y + bi * b.x;
     at32(p + i, tid) = a;
   };
-  stream_sweep(
-      N,
+  int i = stream_sweep(
+      0, r.nl,
       [&](int i0, int h) RPA_INLINE {
 #pragma unroll
         for (int u = 0; u < kSweep; ++u) {
-          rv[h][u] = at32(r + (i0 + u * st), tid);
+          pv[h][u] = at32(p + (i0 + u * st), tid);
+          xv[h][u] = at32(x + (i0 + u * st), tid);
+        }
+      },
+      [&](int i0, int h) RPA_INLINE {
+#pragma unroll
+        for (int u = 0; u < kSweep; ++u) one(i0 + u * st, r.l[i0 + u * st + (int)tid], pv[h][u], xv[h][u]);
+      });
+  i = stream_sweep(
+      i, N,
+      [&](int i0, int h) RPA_INLINE {
+#pragma unroll
+        for (int u = 0; u < kSweep; ++u) {
+          rv[h][u] = at32(r.g + (i0 + u * st), tid);
           pv[h][u] = at32(p + (i0 + u * st), tid);
           xv[h][u] = at32(x + (i0 + u * st), tid);
         }
@@ -695,8 +733,7 @@ __device__ __forceinline__ void direction_sweep(int N, const typename V2<T>::t* 
 #pragma unroll
         for (int u = 0; u < kSweep; ++u) one(i0 + u * st, rv[h][u], pv[h][u], xv[h][u]);
       });
-  for (int i = N / (kSweep * st) * (kSweep * st); i + (int)tid < N; i += st)
-    one(i, at32(r + i, tid), at32(p + i, tid), at32(x + i, tid));
+  for (; i + (int)tid < N; i += st) one(i, at32(r.g + i, tid), at32(p + i, tid), at32(x + i, tid));
 }
 
 // x += d (has_d) + alpha p (p non-null), the sum formed in the iteration's precision
@@ -786,6 +823,7 @@ __device__ __forceinline__ void solve_plain(const CocgArgs& a, int s, char* smem
   T2* d;                           // alpha p accumulates here
   if constexpr (REFINE) d = r + 3 * (size_t)N;
   else d = x;
+  const SplitVec<T> rs{reinterpret_cast<T2*>(nlc + (size_t)a.nl.n_proj * sizeof(double2)), r, a.r_lds};
   const double eps = a.eps[n];
   const double om = a.omega[b];
   const int maxit = REFINE ? a.maxit32 : a.maxit;
@@ -823,6 +861,7 @@ __device__ __forceinline__ void solve_plain(const CocgArgs& a, int s, char* smem
       march<double, FULL, HS, PITCH>(g, a.c64, rp, reinterpret_cast<double2*>(smem), 0, g.ntiles, 0, g.nx);
       double w4[4] = {rp.rr, rp.bb, rp.rho_re, rp.rho_im};
       block_reduce<4>(w4, red);
+      for (int i = threadIdx.x; i < rs.nl; i += blockDim.x) rs.l[i] = r[i];
       rnorm = uni(sqrt(w4[0]));
       rho_nr = w4[2];
       rho_ni = w4[3];
@@ -846,7 +885,7 @@ __device__ __forceinline__ void solve_plain(const CocgArgs& a, int s, char* smem
       }
     } else {
       double u3[3] = {0.0, 0.0, 0.0};
-      residual_sweep<T, NL>(N, r, q, uni((T)al_r), uni((T)al_i), nlp, u3[0], u3[1], u3[2]);
+      residual_sweep<T, NL>(N, rs, q, uni((T)al_r), uni((T)al_i), nlp, u3[0], u3[1], u3[2]);
       block_reduce<3>(u3, red);
       ++its;
       rnorm = uni(sqrt(u3[0]));
@@ -876,7 +915,7 @@ __device__ __forceinline__ void solve_plain(const CocgArgs& a, int s, char* smem
     rho_r = rho_nr;
     rho_i = rho_ni;
     if (its >= maxit) { status = 1; break; }
-    direction_sweep<T>(N, r, p, d, uni((T)al_r), uni((T)al_i), uni((T)br), uni((T)bi), first, pend, dfresh);
+    direction_sweep<T>(N, rs, p, d, uni((T)al_r), uni((T)al_i), uni((T)br), uni((T)bi), first, pend, dfresh);
     __syncthreads();
     if (pend) dfresh = false;
     pend = false;

@@ -454,19 +454,19 @@ rpa_status sternheimer_batch(rpa_ctx* h, int B, const std::vector<double>& omega
     ap.g.prec = 0;
     ap.n_items_dev = P<int>(h->counter) + 4;
     const size_t shmem_p = cocg_shmem_bytes(gp, h->block, refine, h->nl.n_proj);
-    rl = timed(0, [&] { return launch_cocg(ap, refine, grid_p, h->block, shmem_p, s); });
+    rl = timed(0, [&] { return launch_cocg(ap, refine, grid_p, h->block, shmem_p, h->num_cu, s); });
     if (rl != RPA_OK) return rl;
     CocgArgs aq = a;
     aq.order = P<int>(h->order) + n_items;
     aq.n_items_dev = P<int>(h->counter) + 5;
     aq.counter = P<int>(h->counter) + 3;
-    rl = timed(1, [&] { return launch_cocg(aq, refine, grid, h->block, shmem, s); });
+    rl = timed(1, [&] { return launch_cocg(aq, refine, grid, h->block, shmem, h->num_cu, s); });
   } else {
-    rl = timed(h->prec_dev ? 1 : 0, [&] { return launch_cocg(a, refine, grid, h->block, shmem, s); });
+    rl = timed(h->prec_dev ? 1 : 0, [&] { return launch_cocg(a, refine, grid, h->block, shmem, h->num_cu, s); });
   }
   if (rl != RPA_OK) return rl;
   if (refine) {
-    rl = timed(2, [&] { return launch_cocg(f, false, grid64, h->block, shmem64, s); });
+    rl = timed(2, [&] { return launch_cocg(f, false, grid64, h->block, shmem64, h->num_cu, s); });
     if (rl != RPA_OK) return rl;
   }
   h->last_grid = grid;

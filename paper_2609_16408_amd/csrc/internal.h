@@ -118,6 +118,7 @@ struct CocgArgs {
   unsigned long long* ostats;
   int n_bins;
   const PrecArgs* prec;        // device copy of the preconditioner tables; null: plain COCG
+  int r_lds;                   // elements of the residual kept in LDS (set by launch_cocg)
   int is_followup;             // the FP64 launch that continues systems the FP32 one handed over
 };
 
@@ -146,7 +147,7 @@ CocgKernel cocg_kernel(int m, bool refine);
 constexpr int kMaxFieldWeights = 64;     // most host values that travel with a launch
 
 // Launchers (return hipError_t of the launch).
-hipError_t launch_cocg(const CocgArgs& a, bool fp32_refine, int grid, int block, size_t shmem,
+hipError_t launch_cocg(const CocgArgs& a, bool fp32_refine, int grid, int block, size_t shmem, int num_cu,
                        hipStream_t s);
 size_t cocg_shmem_bytes(const Geom& g, int block, bool fp32_refine, int n_proj);
 int cocg_blocks_per_cu(const Geom& g, int block, bool fp32_refine, int n_proj);
