@@ -959,15 +959,19 @@ __device__ __forceinline__ void solve_plain(const CocgArgs& a, int s, char* smem
 
 // One system, preconditioned COCG (passes in precond_impl.h).  FP64: x
 // itself accumulates alpha p.  FP32 (REFINE): reliable updates as above.
-// q = A p follows its recurrence; every kQRefresh iterations or so it is
-// formed afresh from p (q = M p + (V - shift) p, one more application of the
-// basis transforms), at a reliable update in FP32.
-constexpr int kQRefresh = 24;
+// q = A p follows its recurrence; every QR iterations or so it is formed
+// afresh from p (q = M p + (V - shift) p, one more application of the basis
+// transforms), at a reliable update in FP32.  FP64 takes 8: rounding in the
+// recurrence ends the longest solves early (24^3, tol 1e-10, right-hand sides
+// perturbed by 1e-15: 94 iterations at an unrecurred q and at 8, 91 in half of
+// the runs at 24 or without; true residuals are the same within a percent).
+// FP32 measures its true residual and takes 24.
 
 template <bool REFINE, bool FULL, int HS, int PITCH, bool NL>
 __device__ __forceinline__ void solve_pc(const CocgArgs& a, int s, char* smem, double* red, char* nlc) {
   typedef typename std::conditional<REFINE, float, double>::type T;
   typedef typename V2<T>::t T2;
+  constexpr int QR = REFINE ? 24 : 8;
   const Geom& g = a.g;
   const long long N = g.N;
   const int b = s / a.n_occ;
@@ -1038,7 +1042,7 @@ __device__ __forceinline__ void solve_pc(const CocgArgs& a, int s, char* smem, d
       if (!(rnorm > thr)) break;
       resid = false;
       upd = false;
-      refresh = !first && its - last_q >= kQRefresh;
+      refresh = !first && its - last_q >= QR;
       PcCtx<T>(g, *a.prec, smem).stage();
       __syncthreads();
     }
@@ -1065,7 +1069,7 @@ __device__ __forceinline__ void solve_pc(const CocgArgs& a, int s, char* smem, d
         }
       } else {
         if (!(rnorm > thr)) break;                     // converged, or NaN
-        if (its - last_q >= kQRefresh) {
+        if (its - last_q >= QR) {
           // p has its last alpha pending; q is stale only for the next beta
           refresh = true;
           upd = false;
