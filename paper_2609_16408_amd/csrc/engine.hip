@@ -57,7 +57,7 @@ struct rpa_ctx {
   double* Vax[3] = {nullptr, nullptr, nullptr};
   double* Tf[3] = {nullptr, nullptr, nullptr};
   double* Ti[3] = {nullptr, nullptr, nullptr};
-  double* axis_mem = nullptr;        // allocation of Tf and Ti
+  double* axis_mem = nullptr;        // allocation of Tf, Ti, s_half and s_full
   double* s_half = nullptr;
   double* s_full = nullptr;
   StencilCoef<double> c64;
@@ -969,16 +969,23 @@ rpa_status rpa_setup(const rpa_setup_params* p, void* stream, rpa_handle* out) {
   };
   if (!alloc((void**)&h->v64, N * sizeof(double)) || !alloc((void**)&h->v32, N * sizeof(float)) ||
       !alloc((void**)&h->psi64, (size_t)h->ngal * N * sizeof(double)) ||
-      !alloc((void**)&h->eps_d, h->ngal * sizeof(double)) ||
-      !alloc((void**)&h->s_half, N * sizeof(double)) || !alloc((void**)&h->s_full, N * sizeof(double)))
+      !alloc((void**)&h->eps_d, h->ngal * sizeof(double)))
     return fail(RPA_E_OOM);
   h->fused = transform_fits(h->n[0], h->n[1], h->n[2]);
-  std::vector<double> axis_mats;     // fused: the padded forward and inverse matrices of all axes
+  // one table, one copy (each copy from pageable memory waits about 17 us):
+  // fused, the padded forward and inverse matrices of all axes, then the
+  // Coulomb scales nu^1/2 and nu
+  const size_t scale_len = ((size_t)N + 31) & ~(size_t)31;
+  size_t axis_len = 0;
+  for (int d = 0; d < 3 && h->fused; ++d) axis_len += 2 * transform_elems(h->n[d], h->n[d]);
+  axis_len = (axis_len + 31) & ~(size_t)31;
+  std::vector<double> tables(axis_len + 2 * scale_len, 0.0);
+  if (!alloc((void**)&h->axis_mem, tables.size() * sizeof(double))) return fail(RPA_E_OOM);
+  h->s_half = h->axis_mem + axis_len;
+  h->s_full = h->s_half + scale_len;
   if (h->fused) {
-    size_t total = 0;
-    for (int d = 0; d < 3; ++d) total += 2 * transform_elems(h->n[d], h->n[d]);
-    axis_mats.resize(total);
-    if (!alloc((void**)&h->axis_mem, total * sizeof(double))) return fail(RPA_E_OOM);
+    if (hipHostMalloc((void**)&h->host_sums, kMaxTransformDim * sizeof(double), hipHostMallocDefault) != hipSuccess)
+      return fail(set_err(RPA_E_OOM, "hipHostMalloc failed in setup"));
   } else {
     for (int d = 0; d < 3; ++d)
       if (!alloc((void**)&h->Vax[d], (size_t)h->n[d] * h->n[d] * sizeof(double))) return fail(RPA_E_OOM);
@@ -1071,7 +1078,8 @@ rpa_status rpa_setup(const rpa_setup_params* p, void* stream, rpa_handle* out) {
     memcpy(prec_host.data() + args_off, &h->prec, sizeof(PrecArgs));
     h->prec_dev = reinterpret_cast<const PrecArgs*>(base + args_off);
   }
-  std::vector<double> sh((size_t)N), sf((size_t)N);
+  double* sh = tables.data() + axis_len;
+  double* sf = sh + scale_len;
   for (int i = 0; i < h->n[0]; ++i)
     for (int j = 0; j < h->n[1]; ++j)
       for (int k = 0; k < h->n[2]; ++k) {
@@ -1089,23 +1097,21 @@ rpa_status rpa_setup(const rpa_setup_params* p, void* stream, rpa_handle* out) {
                        hipMemcpyDeviceToDevice, s);
   if (e == hipSuccess && p->n_extra > 0)
     e = hipMemcpyAsync(h->eps_d + h->nocc, p->eps_extra, p->n_extra * sizeof(double), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(h->s_half, sh.data(), N * sizeof(double), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(h->s_full, sf.data(), N * sizeof(double), hipMemcpyHostToDevice, s);
   if (h->fused) {
     // V is [grid][mode]: forward (grid -> mode) is V itself in k-major order, inverse its transpose
     size_t at = 0;
     for (int d = 0; d < 3; ++d)
       for (int k = 0; k < 2; ++k) {
         (k == 0 ? h->Tf : h->Ti)[d] = h->axis_mem + at;
-        pad_k_major(V[d].data(), h->n[d], h->n[d], k == 0, axis_mats.data() + at);
+        pad_k_major(V[d].data(), h->n[d], h->n[d], k == 0, tables.data() + at);
         at += transform_elems(h->n[d], h->n[d]);
       }
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(h->axis_mem, axis_mats.data(), at * sizeof(double), hipMemcpyHostToDevice, s);
   } else {
     for (int d = 0; d < 3 && e == hipSuccess; ++d)
       e = hipMemcpyAsync(h->Vax[d], V[d].data(), V[d].size() * sizeof(double), hipMemcpyHostToDevice, s);
   }
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(h->axis_mem, tables.data(), tables.size() * sizeof(double), hipMemcpyHostToDevice, s);
   for (size_t k = 0; k < nl_up.size() && e == hipSuccess; ++k)
     if (nl_up[k].bytes)
       e = hipMemcpyAsync(nl_up[k].dst, nl_up[k].src, nl_up[k].bytes, hipMemcpyHostToDevice, s);
@@ -1131,7 +1137,7 @@ rpa_status rpa_destroy(rpa_handle h) {
   if (!h) return RPA_OK;
   (void)hipDeviceSynchronize();
   auto fr = [](void* p) { if (p) (void)hipFree(p); };
-  fr(h->v64); fr(h->v32); fr(h->psi64); fr(h->eps_d); fr(h->s_half); fr(h->s_full);
+  fr(h->v64); fr(h->v32); fr(h->psi64); fr(h->eps_d);
   for (void* m : h->nl_mem) fr(m);
   fr(h->prec_mem);
   fr(h->nlcoef.p);
@@ -1748,8 +1754,6 @@ rpa_status rpa_energy_from_coarse(rpa_handle h, int32_t n_omega, const double* w
     const double* M = P<double>(h->interp_m);
     const int nblk = n[0];
     ENSURE(h, h->tmpA, (size_t)n[0] * nc[1] * nc[2] * sizeof(double));
-    if (!h->host_sums)
-      HIPCHK(h, hipHostMalloc((void**)&h->host_sums, kMaxTransformDim * sizeof(double), hipHostMallocDefault));
     HIPCHK(h, launch_cols_fields(d_coarse, P<double>(h->tmpA), n_omega, weight, nc[0], n[0], nc[1] * nc[2],
                                  M + h->interp_dims[0], s));
     HIPCHK(h, launch_planes_energy(P<double>(h->tmpA), e_fine, n[0], nc[1], nc[2], n[1], n[2],

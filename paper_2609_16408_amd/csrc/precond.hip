@@ -11,6 +11,7 @@
 #include "rpa.h"
 #include "internal.h"
 
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -18,6 +19,7 @@ struct rpa_kinetic_precond_s {
   int n[3] = {0, 0, 0};
   long long N = 0;
   bool fused = false;
+  double* mem = nullptr;                       // allocation of V, VT and kin
   double* V[3] = {nullptr, nullptr, nullptr};  // [grid point][mode], orthonormal (fused: padded, forward)
   double* VT[3] = {nullptr, nullptr, nullptr}; // fused: padded, inverse
   double* kin = nullptr;                       // -1/2 (lam_x + lam_y + lam_z) per mode
@@ -74,10 +76,8 @@ void fourier_basis(int n, double h, const double* w, std::vector<double>& V,
 
 void release(rpa_kinetic_precond p) {
   if (!p) return;
-  for (double* v : p->V) if (v) (void)hipFree(v);
-  for (double* v : p->VT) if (v) (void)hipFree(v);
   for (double* v : p->ws) if (v) (void)hipFree(v);
-  if (p->kin) (void)hipFree(p->kin);
+  if (p->mem) (void)hipFree(p->mem);
   if (p->sig) (void)hipFree(p->sig);
   delete p;
 }
@@ -100,32 +100,40 @@ rpa_status rpa_kinetic_precond_create(const int32_t* n, const double* L, void* s
     p->n[d] = n[d];
     fourier_basis(n[d], L[d] / n[d], w, V[d], lam[d]);
   }
-  std::vector<double> kin((size_t)p->N);
+  p->fused = rpa::transform_fits(n[0], n[1], n[2]);
+  // one allocation and one copy: per axis the basis (fused: padded, then its
+  // inverse), then the kinetic diagonal
+  size_t off[3], len[3], total = 0;
+  for (int d = 0; d < 3; ++d) {
+    len[d] = p->fused ? rpa::transform_elems(n[d], n[d]) : (V[d].size() + 31) & ~(size_t)31;
+    off[d] = total;
+    total += (p->fused ? 2 : 1) * len[d];
+  }
+  std::vector<double> host(total + (size_t)p->N, 0.0);
+  for (int d = 0; d < 3; ++d) {
+    if (p->fused) {
+      rpa::pad_k_major(V[d].data(), n[d], n[d], true, host.data() + off[d]);
+      rpa::pad_k_major(V[d].data(), n[d], n[d], false, host.data() + off[d] + len[d]);
+    } else {
+      std::copy(V[d].begin(), V[d].end(), host.begin() + off[d]);
+    }
+  }
+  double* kin = host.data() + total;
   for (int i = 0; i < n[0]; ++i)
     for (int j = 0; j < n[1]; ++j)
       for (int k = 0; k < n[2]; ++k)
         kin[((size_t)i * n[1] + j) * n[2] + k] = -0.5 * (lam[0][i] + lam[1][j] + lam[2][k]);
-  p->fused = rpa::transform_fits(n[0], n[1], n[2]);
-  std::vector<double> VT[3];
-  for (int d = 0; d < 3 && p->fused; ++d) {
-    std::vector<double> fwd(rpa::transform_elems(n[d], n[d]));
-    VT[d].resize(fwd.size());
-    rpa::pad_k_major(V[d].data(), n[d], n[d], true, fwd.data());
-    rpa::pad_k_major(V[d].data(), n[d], n[d], false, VT[d].data());
-    V[d].swap(fwd);
+  if (hipMalloc((void**)&p->mem, host.size() * sizeof(double)) != hipSuccess) {
+    (void)hipGetLastError();
+    release(p);
+    return RPA_E_OOM;
   }
-  bool ok = hipMalloc((void**)&p->kin, (size_t)p->N * sizeof(double)) == hipSuccess;
-  for (int d = 0; d < 3 && ok; ++d) {
-    ok = hipMalloc((void**)&p->V[d], V[d].size() * sizeof(double)) == hipSuccess;
-    if (ok && p->fused) ok = hipMalloc((void**)&p->VT[d], VT[d].size() * sizeof(double)) == hipSuccess;
+  for (int d = 0; d < 3; ++d) {
+    p->V[d] = p->mem + off[d];
+    if (p->fused) p->VT[d] = p->V[d] + len[d];
   }
-  if (!ok) { (void)hipGetLastError(); release(p); return RPA_E_OOM; }
-  hipError_t e = hipMemcpyAsync(p->kin, kin.data(), kin.size() * sizeof(double),
-                                hipMemcpyHostToDevice, s);
-  for (int d = 0; d < 3 && e == hipSuccess; ++d)
-    e = hipMemcpyAsync(p->V[d], V[d].data(), V[d].size() * sizeof(double), hipMemcpyHostToDevice, s);
-  for (int d = 0; d < 3 && p->fused && e == hipSuccess; ++d)
-    e = hipMemcpyAsync(p->VT[d], VT[d].data(), VT[d].size() * sizeof(double), hipMemcpyHostToDevice, s);
+  p->kin = p->mem + total;
+  hipError_t e = hipMemcpyAsync(p->mem, host.data(), host.size() * sizeof(double), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host tables go out of scope
   if (e != hipSuccess) { (void)hipGetLastError(); release(p); return RPA_E_HIP; }
   *out = p;
