@@ -17,7 +17,7 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(ROOT, "_build")
 LIB_NAME = "librpa_mi355x.so"
 LIB_PATH = os.path.join(PKG, LIB_NAME)
-SOURCES = ["engine.hip", "cocg.hip", "kernels.hip", "transform.hip", "server.hip", "precond.hip",
+SOURCES = ["engine.hip", "cocg.hip", "cocg_resident.hip", "kernels.hip", "transform.hip", "server.hip", "precond.hip",
            "block_lanczos.hip"]
 # the persistent COCG kernels: one object per variant (plain, nonlocal,
 # preconditioned, both) and LDS pitch

@@ -174,6 +174,7 @@ hipError_t launch_ht(const Geom& g, const StencilCoef<T>& cf, const T* v, const 
 
 hipError_t launch_cocg(const CocgArgs& a, bool fp32_refine, int grid, int block, size_t shmem, int num_cu,
                        hipStream_t s) {
+  if (launch_cocg_resident(a, fp32_refine, grid, s)) return hipGetLastError();
   if (a.prec) block = a.g.pc_block;
   CocgArgs b = a;
   if (!a.prec) {

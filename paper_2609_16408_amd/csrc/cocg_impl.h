@@ -21,7 +21,11 @@
 //    the LDS that the march leaves free (cells up to 24^3 are bound by the
 //    traffic of all workgroups' vectors through the last-level cache, about
 //    7 TB/s).  All reductions are per workgroup in a fixed order, so results
-//    do not depend on scheduling.
+//    do not depend on scheduling.  Measured against a stencil sweep that forms
+//    p on the fly (two halo'd operands in FP64, A p by recurrence in FP32) and
+//    one update sweep: density of 64 start vectors on 24^3 in FP64 279 -> 99 ms,
+//    chi0 of 64 vectors on 24^3 in FP32 30.1 -> 23.4 ms, the plain launches of
+//    16 start vectors on 48^3 with 128 orbitals 926 -> 760 ms.
 //  * FP32_REFINE: COCG in FP32 with reliable updates: the FP32 correction is
 //    folded into the FP64 solution and the residual replaced by the FP64
 //    residual r = b - A x (an FP64 stencil sweep) whenever the recursive

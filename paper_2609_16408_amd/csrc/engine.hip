@@ -910,8 +910,8 @@ rpa_status rpa_setup(const rpa_setup_params* p, void* stream, rpa_handle* out) {
   // reliable-update factor of the FP32 COCG (residual replaced by the FP64
   // residual each time the recursive one dropped by this factor).  On the
   // Si64 workload 0.01 needs 3.0 updates and 98.3 iterations per solve
-  // against 5.6 and 97.1 at 0.1, and each update costs about five FP32
-  // iterations of time (fold plus FP64 residual sweep): 5% faster overall.
+  // against 5.6 and 97.1 at 0.1, and an update is a fold and an FP64 residual
+  // sweep: 5% faster overall (these figures predate the three-sweep solver).
   // defaults measured on the Si64-like workload: the preconditioned solves,
   // a few dozen iterations each, gain from fewer updates (0.001: 2.3 instead
   // of 2.9 per solve, 3% less kernel time than 0.01); so do the plain ones

@@ -149,6 +149,8 @@ constexpr int kMaxFieldWeights = 64;     // most host values that travel with a 
 // Launchers (return hipError_t of the launch).
 hipError_t launch_cocg(const CocgArgs& a, bool fp32_refine, int grid, int block, size_t shmem, int num_cu,
                        hipStream_t s);
+// the same for systems that the LDS-resident FP64 solver takes; false (nothing launched) for others
+bool launch_cocg_resident(const CocgArgs& a, bool fp32_refine, int grid, hipStream_t s);
 size_t cocg_shmem_bytes(const Geom& g, int block, bool fp32_refine, int n_proj);
 int cocg_blocks_per_cu(const Geom& g, int block, bool fp32_refine, int n_proj);
 bool geom_supported(const Geom& g);   // nz + 12 <= 128 (padded LDS rows)

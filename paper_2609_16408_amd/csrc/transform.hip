@@ -15,7 +15,7 @@
 // k = 4v .. 4v+3, and both contractions of a kernel chain in registers.
 // Measured against one k_axis launch per axis (which re-reads a line of
 // inputs through the caches for every output): nu^1/2 of 64 vectors on 48^3
-// 2226 -> 143 us, M^-1 of 16 complex vectors on 24x24x48 268 -> 49 us.
+// 2226 -> 143 us, M^-1 of 16 complex vectors on 24x24x48 268 -> 44 us.
 #include "internal.h"
 
 namespace rpa {
