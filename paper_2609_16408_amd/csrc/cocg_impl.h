@@ -267,6 +267,9 @@ template <typename T, bool FULL, int HS, int PITCH, class Pol, int PPS>
 struct Marcher {
   typedef typename V2<T>::t T2;
   typedef typename Pol::Aux AuxT;
+  // grid offsets: a whole-plane tile has at most 768 points per plane, and an
+  // axis' dense basis keeps n_x far below the 2.8 million that 32 bits hold
+  typedef typename std::conditional<FULL, int, long long>::type Off;
   static constexpr int PF = Pol::kPF;
   static constexpr int U = QN + PF;   // FIFO: planes x-R .. x+R+PF
   static constexpr int PA = PF + 1;   // aux/halo pipelines: planes x .. x+PF
@@ -366,12 +369,12 @@ struct Marcher {
     });
     const T sx = cf.sx * xr + cf.sy * yr + cf.sz * zr;
     const T sy = cf.sx * xi + cf.sy * yi + cf.sz * zi;
-    pol.center(x * plane + y0n, col, c, mk2(sx, sy), ax[PH % PA]);
+    pol.center((Off)x * plane + y0n, col, c, mk2(sx, sy), ax[PH % PA]);
     // refill the pipelines: the FIFO slot of plane x-R takes plane x+R+PF+1,
     // the aux/halo slot of plane x takes plane x+PF+1
     const int xn = x + PF + 1;
     const int xc = xn < xe ? xn : xe - 1;
-    const int po = xc * plane + y0n, pw = wrapx(xc + R, nx) * plane + y0n;
+    const Off po = (Off)xc * plane + y0n, pw = (Off)wrapx(xc + R, nx) * plane + y0n;
     fifo[PH % U] = pol.load(pw, col);
     ax[PH % PA] = pol.aux(po, col);
     static_for<NH>([&](auto H) RPA_INLINE { hq[H][PH % PA] = pol.load(po - y0n, hcol[H]); });
@@ -432,12 +435,12 @@ struct Marcher {
       static_for<U>([&](auto I) RPA_INLINE {
         int px = (xb + (I - R)) % nx;          // nx > R: at most one period below
         px = px < 0 ? px + nx : px;
-        fifo[I] = pol.load(px * plane + y0n, col);
+        fifo[I] = pol.load((Off)px * plane + y0n, col);
       });
       static_for<PA>([&](auto I) RPA_INLINE {
         const int px = xb + I < xe ? xb + I : xe - 1;
-        ax[I] = pol.aux(px * plane + y0n, col);
-        static_for<NH>([&](auto H) RPA_INLINE { hq[H][I] = pol.load(px * plane, hcol[H]); });
+        ax[I] = pol.aux((Off)px * plane + y0n, col);
+        static_for<NH>([&](auto H) RPA_INLINE { hq[H][I] = pol.load((Off)px * plane, hcol[H]); });
       });
       int x = xb;
       for (; x + U <= xe; x += U) block_full<0>(x, xe);
@@ -507,15 +510,15 @@ struct ResidPol {
   const double2* coef;            // w_p of x (LDS)
   static constexpr int kPF = 1;
   struct Aux { double v, psi, u; };
-  __device__ double2 load(int po, unsigned c) const { return buf_load(x + po, c * (unsigned)sizeof(*x)); }
-  __device__ Aux aux(int po, unsigned c) const {
+  __device__ double2 load(long long po, unsigned c) const { return buf_load(x + po, c * (unsigned)sizeof(*x)); }
+  __device__ Aux aux(long long po, unsigned c) const {
     Aux a;
     a.v = buf_load(v + po, c * (unsigned)sizeof(*v));
     a.psi = buf_load(psi + po, c * (unsigned)sizeof(*psi));
     a.u = buf_load(u + po, c * (unsigned)sizeof(*u));
     return a;
   }
-  __device__ void center(int po, unsigned c, double2 xv, double2 nb, const Aux& ax) {
+  __device__ void center(long long po, unsigned c, double2 xv, double2 nb, const Aux& ax) {
     const double a = c0 + ax.v - eps;
     double axr = a * xv.x + om * xv.y + nb.x;
     double axi = a * xv.y - om * xv.x + nb.y;
@@ -547,9 +550,9 @@ struct ApplyPol {
   bool own;
   static constexpr int kPF = 1;
   typedef T Aux;
-  __device__ T aux(int po, unsigned c) const { return buf_load(v + po, c * (unsigned)sizeof(*v)); }
-  __device__ T2 load(int po, unsigned c) const { return buf_load(p + po, c * (unsigned)sizeof(*p)); }
-  __device__ void center(int po, unsigned c, T2 pv, T2 nb, const T& vv) {
+  __device__ T aux(long long po, unsigned c) const { return buf_load(v + po, c * (unsigned)sizeof(*v)); }
+  __device__ T2 load(long long po, unsigned c) const { return buf_load(p + po, c * (unsigned)sizeof(*p)); }
+  __device__ void center(long long po, unsigned c, T2 pv, T2 nb, const T& vv) {
     const T a = c0 + vv - eps;
     T2 h;
     h.x = a * pv.x + om * pv.y + nb.x;
@@ -572,9 +575,9 @@ struct HPol {
   bool own;
   static constexpr int kPF = sizeof(T) == 4 ? 3 : 2;
   typedef T Aux;
-  __device__ T aux(int po, unsigned c) const { return buf_load(v + po, c * (unsigned)sizeof(*v)); }
-  __device__ T2 load(int po, unsigned c) const { return buf_load(x + po, c * (unsigned)sizeof(*x)); }
-  __device__ void center(int po, unsigned c, T2 xv, T2 nb, const T& vv) {
+  __device__ T aux(long long po, unsigned c) const { return buf_load(v + po, c * (unsigned)sizeof(*v)); }
+  __device__ T2 load(long long po, unsigned c) const { return buf_load(x + po, c * (unsigned)sizeof(*x)); }
+  __device__ void center(long long po, unsigned c, T2 xv, T2 nb, const T& vv) {
     const T a = c0 + vv - sr;
     T2 o;
     o.x = a * xv.x + si * xv.y + nb.x;
@@ -593,6 +596,7 @@ struct NlPoint {
   const int* proj;
   const T* v;
   const typename V2<T>::t* coef;
+  __device__ __forceinline__ NlPoint from(long long i) const { return {ptr ? ptr + i : ptr, proj, v, coef}; }
 };
 
 // The streaming sweeps take kSweep elements per thread and trip, the next
@@ -600,6 +604,20 @@ struct NlPoint {
 // in order on one counter, so loads issued after stores would wait for them.
 
 constexpr int kSweep = 4;
+
+// Within a sweep an element's index is 32 bits; systems that may be longer
+// (not whole-plane tiles) go in blocks of kSweepBlock elements.  64-bit
+// indices cost the sweeps scalar registers (FP64 systems of 24^3 99 -> 102 ms).
+constexpr int kSweepBlock = 1 << 30;
+template <bool FULL, class F>
+__device__ __forceinline__ void sweep_blocks(long long N, F&& f) {
+  if constexpr (FULL) {
+    f(0, (int)N);
+  } else {
+#pragma unroll 1
+    for (long long i = 0; i < N; i += kSweepBlock) f(i, (int)min(N - i, (long long)kSweepBlock));
+  }
+}
 
 template <class Load, class Use>
 __device__ __forceinline__ int stream_sweep(int begin, int end, Load&& load, Use&& use) {
@@ -630,6 +648,7 @@ struct SplitVec {
   typename V2<T>::t* l;
   typename V2<T>::t* g;
   int nl;
+  __device__ __forceinline__ SplitVec from(long long i) const { return {l, g + i, i == 0 ? nl : 0}; }
 };
 
 // r -= alpha (q + V_nl p);  returns ||r||^2, r^T r.
@@ -817,7 +836,7 @@ __device__ __forceinline__ void solve_plain(const CocgArgs& a, int s, char* smem
   typedef typename std::conditional<REFINE, float, double>::type T;
   typedef typename V2<T>::t T2;
   const Geom& g = a.g;
-  const int N = (int)g.N;
+  const long long N = g.N;
   const int b = s / a.n_occ;
   const int n = s - b * a.n_occ;
   T2* r = reinterpret_cast<T2*>(a.slot_ws + (size_t)blockIdx.x * a.slot_bytes);
@@ -889,7 +908,9 @@ __device__ __forceinline__ void solve_plain(const CocgArgs& a, int s, char* smem
       }
     } else {
       double u3[3] = {0.0, 0.0, 0.0};
-      residual_sweep<T, NL>(N, rs, q, uni((T)al_r), uni((T)al_i), nlp, u3[0], u3[1], u3[2]);
+      sweep_blocks<FULL>(N, [&](long long i, int len) RPA_INLINE {
+        residual_sweep<T, NL>(len, rs.from(i), q + i, uni((T)al_r), uni((T)al_i), nlp.from(i), u3[0], u3[1], u3[2]);
+      });
       block_reduce<3>(u3, red);
       ++its;
       rnorm = uni(sqrt(u3[0]));
@@ -919,7 +940,10 @@ __device__ __forceinline__ void solve_plain(const CocgArgs& a, int s, char* smem
     rho_r = rho_nr;
     rho_i = rho_ni;
     if (its >= maxit) { status = 1; break; }
-    direction_sweep<T>(N, rs, p, d, uni((T)al_r), uni((T)al_i), uni((T)br), uni((T)bi), first, pend, dfresh);
+    sweep_blocks<FULL>(N, [&](long long i, int len) RPA_INLINE {
+      direction_sweep<T>(len, rs.from(i), p + i, d + i, uni((T)al_r), uni((T)al_i), uni((T)br), uni((T)bi), first, pend,
+                         dfresh);
+    });
     __syncthreads();
     if (pend) dfresh = false;
     pend = false;
