@@ -141,6 +141,10 @@ long long cocg_slot_bytes(const Geom& g, bool fp32_refine) {
   return vecs * g.N * (long long)(fp32_refine ? sizeof(float2) : sizeof(double2));
 }
 
+size_t cocg_slots_bytes(const Geom& g, bool fp32_refine, int grid) {
+  return (size_t)std::max((long long)grid * cocg_slot_bytes(g, fp32_refine), cocg_slot_bytes(g, false));
+}
+
 namespace {
 template <typename T>
 using HapplyKernel = void (*)(Geom, StencilCoef<T>, const T*, const double*, const double*, const void*, void*, int,

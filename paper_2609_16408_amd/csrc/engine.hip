@@ -380,7 +380,7 @@ rpa_status sternheimer_batch(rpa_ctx* h, int B, const std::vector<double>& omega
   const int grid = std::max(1, std::min(n_items, bpc * h->num_cu));
   const int grid_p = std::max(1, std::min(n_items, bpc_p * h->num_cu));
   const long long sb = cocg_slot_bytes(h->geom, refine);
-  ENSURE(h, h->slots, (size_t)std::max(grid, grid_p) * sb);
+  ENSURE(h, h->slots, cocg_slots_bytes(h->geom, refine, std::max(grid, grid_p)));
 
   CocgArgs a;
   memset(&a, 0, sizeof(a));
@@ -819,7 +819,7 @@ uint64_t lanczos_workspace_bytes(const rpa_setup_params& p, int B, int n_lanczos
     bpc = std::max(bpc, cocg_blocks_per_cu(g, block, refine, std::max(0, p.n_proj)));
   }
   const uint64_t grid = std::max<uint64_t>(1, std::min<uint64_t>(items, (uint64_t)bpc * num_cu));
-  bytes += grid * (uint64_t)cocg_slot_bytes(g, refine);
+  bytes += cocg_slots_bytes(g, refine, (int)grid);
   return bytes;
 }
 
@@ -1309,7 +1309,7 @@ ScratchLayout scratch_layout(rpa_ctx* h, int B, bool symmetrized) {
   add(h->status, items * sizeof(int));
   add(h->counter, 64 * sizeof(int));
   if (refine) add(h->faillist, items * sizeof(int));
-  add(h->slots, grid * (size_t)cocg_slot_bytes(h->geom, refine));
+  add(h->slots, cocg_slots_bytes(h->geom, refine, (int)grid));
   add(h->racc, b * N * sizeof(double));
   return L;
 }

@@ -155,6 +155,9 @@ size_t cocg_shmem_bytes(const Geom& g, int block, bool fp32_refine, int n_proj);
 int cocg_blocks_per_cu(const Geom& g, int block, bool fp32_refine, int n_proj);
 bool geom_supported(const Geom& g);   // nz + 12 <= 128 (padded LDS rows)
 long long cocg_slot_bytes(const Geom& g, bool fp32_refine);
+// bytes of the slots of `grid` workgroups; an FP32 launch's hold the slots of
+// the FP64 launch behind it too, at least one
+size_t cocg_slots_bytes(const Geom& g, bool fp32_refine, int grid);
 // fill in the preconditioned solver's launch shape for an accepted problem
 void cocg_pc_shape(Geom& g, int block, int n_proj);
 // plane elements per thread of the stencil workgroup, and the most the preconditioner accepts

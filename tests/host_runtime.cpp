@@ -1,0 +1,167 @@
+// A stand-in for the HIP runtime, for host tests of the library's bookkeeping
+// without a GPU: allocations are host memory that is recorded, copies copy,
+// and kernels are not run but checked against what they may assume.  The
+// definitions here take the place of the runtime's for the whole process.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "internal.h"
+#include "rpa.h"
+
+namespace {
+
+std::map<char*, size_t> g_mem;      // live device allocations
+size_t g_bytes = 0;                 // their total
+constexpr int kCus = 256;
+int g_occupancy = 2;                // workgroups per compute unit the occupancy query answers
+
+struct Launch {
+  const void* fn;
+  dim3 grid, block;
+  size_t shmem;
+  void** args;
+};
+void (*g_on_launch)(const Launch&) = nullptr;
+
+}  // namespace
+
+extern "C" {
+
+hipError_t hipMalloc(void** p, size_t n) {
+  *p = std::calloc(1, n);
+  if (!*p) return hipErrorOutOfMemory;
+  g_mem[static_cast<char*>(*p)] = n;
+  g_bytes += n;
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+  auto it = g_mem.find(static_cast<char*>(p));
+  if (it == g_mem.end()) std::abort();
+  g_bytes -= it->second;
+  g_mem.erase(it);
+  std::free(p);
+  return hipSuccess;
+}
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+  *p = std::calloc(1, n);
+  return *p ? hipSuccess : hipErrorOutOfMemory;
+}
+hipError_t hipHostFree(void* p) { std::free(p); return hipSuccess; }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
+  std::memcpy(d, s, n);
+  return hipSuccess;
+}
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = kCus; return hipSuccess; }
+hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { *e = nullptr; return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0.f; return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetSymbolAddress(void** p, const void*) { *p = nullptr; return hipErrorInvalidSymbol; }
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) {
+  *n = g_occupancy;
+  return hipSuccess;
+}
+struct { dim3 grid, block; size_t shmem; hipStream_t s; } g_call;
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t shmem, hipStream_t s) {
+  g_call = {grid, block, shmem, s};
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shmem, hipStream_t* s) {
+  *grid = g_call.grid;
+  *block = g_call.block;
+  *shmem = g_call.shmem;
+  *s = g_call.s;
+  return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void* fn, dim3 grid, dim3 block, void** args, size_t shmem, hipStream_t) {
+  if (g_on_launch) g_on_launch(Launch{fn, grid, block, shmem, args});
+  return hipSuccess;
+}
+
+}  // extern "C"
+
+namespace {
+
+int fail(const std::string& what) {
+  std::printf("FAIL %s\n", what.c_str());
+  return 1;
+}
+
+// A problem on a grid of n points with n_occ orbitals (its arrays live as long as the process).
+rpa_setup_params problem(int nx, int ny, int nz, int n_occ, rpa_precision precision, bool precond) {
+  rpa_setup_params p;
+  std::memset(&p, 0, sizeof(p));
+  const int n[3] = {nx, ny, nz};
+  for (int d = 0; d < 3; ++d) {
+    p.n[d] = n[d];
+    p.L[d] = 0.45 * n[d];
+  }
+  const size_t N = (size_t)nx * ny * nz;
+  p.fd_radius = rpa::kRadius;
+  p.n_occ = n_occ;
+  p.v_loc = static_cast<double*>(std::calloc(N, sizeof(double)));
+  p.psi = static_cast<double*>(std::calloc(N * n_occ, sizeof(double)));
+  p.eps = static_cast<double*>(std::calloc(n_occ, sizeof(double)));
+  p.precision = precision;
+  p.stern_tol = 1e-8;
+  p.stern_maxit = 100;
+  p.precond = precond;
+  return p;
+}
+
+// --- slots: the workspaces of every Sternheimer launch lie inside their allocation
+
+bool g_slots_ok = true;
+int g_cocg = 0;
+bool is_cocg(const void* fn) {
+  for (int m = 0; m < 3; ++m)
+    for (int r = 0; r < 2; ++r)
+      for (rpa::CocgKernel k : {rpa::cocg_kernel<0, 56>(m, r), rpa::cocg_kernel<0, 64>(m, r), rpa::cocg_kernel<0, 128>(m, r),
+                                rpa::cocg_kernel<2, 56>(m, r), rpa::cocg_kernel<2, 64>(m, r), rpa::cocg_kernel<2, 128>(m, r)})
+        if (fn == reinterpret_cast<const void*>(k)) return true;
+  return false;
+}
+void check_slots(const Launch& l) {
+  if (!is_cocg(l.fn)) return;
+  const rpa::CocgArgs& a = *static_cast<const rpa::CocgArgs*>(l.args[0]);
+  auto it = g_mem.find(a.slot_ws);
+  const size_t need = (size_t)l.grid.x * a.slot_bytes;
+  ++g_cocg;
+  std::printf("%u workgroups of %lld bytes in %zu\n", l.grid.x, a.slot_bytes, it == g_mem.end() ? 0 : it->second);
+  if (it == g_mem.end() || need > it->second) g_slots_ok = false;
+}
+
+int slots(int nx, int ny, int nz, int n_occ, int nvec, int precision, int precond) {
+  rpa_setup_params p = problem(nx, ny, nz, n_occ, (rpa_precision)precision, precond != 0);
+  rpa_handle h = nullptr;
+  if (rpa_setup(&p, nullptr, &h) != RPA_OK) return fail(rpa_last_error(nullptr));
+  g_on_launch = check_slots;
+  const size_t N = (size_t)nx * ny * nz;
+  std::vector<double> u(nvec * N), x(2 * nvec * n_occ * N);
+  if (rpa_sternheimer_solve(h, 0.5, nvec, u.data(), x.data(), nullptr, nullptr) != RPA_OK)
+    return fail(rpa_last_error(nullptr));
+  rpa_destroy(h);
+  if (g_cocg != (precision == RPA_FP64 ? 1 : 2)) return fail("a launch was not seen");
+  return g_slots_ok ? 0 : fail("workspaces end beyond their allocation");
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const std::string what = argc > 1 ? argv[1] : "";
+  std::vector<int> v;
+  for (int i = 2; i < argc; ++i) v.push_back(std::atoi(argv[i]));
+  int r = 2;
+  if (what == "slots" && v.size() == 7) r = slots(v[0], v[1], v[2], v[3], v[4], v[5], v[6]);
+  if (r == 0) std::printf("ok\n");
+  return r;
+}

@@ -1,0 +1,41 @@
+"""Workspaces, memory accounting and launch shapes, checked on the host: a C++
+program runs the library over a stand-in for the HIP runtime (host_runtime.cpp)
+that records allocations and looks at every launch instead of running it."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_2609_16408_amd")
+FP64, FP32 = 0, 1
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    if shutil.which("g++") is None or not os.path.exists(os.path.join(PKG, "librpa_mi355x.so")):
+        pytest.skip("needs a C++ compiler and the built library")
+    exe = str(tmp_path_factory.mktemp("host") / "host_runtime")
+    cmd = ["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
+           "-I", os.path.join(PKG, "csrc"), os.path.join(ROOT, "tests", "host_runtime.cpp"), "-L", PKG, "-lrpa_mi355x",
+           "-L/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath," + PKG, "-Wl,-rpath,/opt/rocm/lib", "-rdynamic", "-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+
+    def run(*args):
+        p = subprocess.run([exe, *map(str, args)], capture_output=True, text=True, timeout=120)
+        assert p.returncode == 0, (p.returncode, p.stdout, p.stderr)
+        return p.stdout
+
+    return run
+
+
+# one and two systems, where a single FP64 slot may be longer than the FP32 slots
+# together, and many; grids the marching solver takes (whole planes and 12-row tiles)
+@pytest.mark.parametrize("n_occ,nvec", [(1, 1), (1, 2), (2, 1), (3, 20)])
+@pytest.mark.parametrize("precond", [False, True])
+@pytest.mark.parametrize("precision", [FP64, FP32])
+@pytest.mark.parametrize("n", [(26, 27, 28), (13, 24, 48)])
+def test_sternheimer_workspaces_lie_inside_their_allocation(host, n, precision, precond, n_occ, nvec):
+    host("slots", *n, n_occ, nvec, precision, int(precond))
