@@ -815,8 +815,9 @@ uint64_t lanczos_workspace_bytes(const rpa_setup_params& p, int B, int n_lanczos
   if (p.slots_per_cu <= 0 && query_occupancy)
     bpc = cocg_blocks_per_cu(g, block, refine, std::max(0, p.n_proj));
   if (p.slots_per_cu <= 0 && query_occupancy && g.prec && (p.precond_omega_min > 0 || p.precond_omega_max > 0)) {
-    g.prec = 0;
-    bpc = std::max(bpc, cocg_blocks_per_cu(g, block, refine, std::max(0, p.n_proj)));
+    Geom gp = g;             // the plain launch; the slots are those of the preconditioned one
+    gp.prec = 0;
+    bpc = std::max(bpc, cocg_blocks_per_cu(gp, block, refine, std::max(0, p.n_proj)));
   }
   const uint64_t grid = std::max<uint64_t>(1, std::min<uint64_t>(items, (uint64_t)bpc * num_cu));
   bytes += cocg_slots_bytes(g, refine, (int)grid);

@@ -39,3 +39,11 @@ def host(tmp_path_factory):
 @pytest.mark.parametrize("n", [(26, 27, 28), (13, 24, 48)])
 def test_sternheimer_workspaces_lie_inside_their_allocation(host, n, precision, precond, n_occ, nvec):
     host("slots", *n, n_occ, nvec, precision, int(precond))
+
+
+# one system, fewer systems than workgroups, and more
+@pytest.mark.parametrize("n_occ,n_pts", [(1, 1), (2, 9), (16, 40)])
+@pytest.mark.parametrize("window", [False, True])
+@pytest.mark.parametrize("precision", [FP64, FP32])
+def test_counted_workspace_is_what_a_job_allocates(host, precision, window, n_occ, n_pts):
+    host("workspace", 24, 24, 20, n_occ, n_pts, 3, precision, int(window))
