@@ -787,6 +787,44 @@ int pick_tile_y(int ny, int nz, int requested) {
   return 0;
 }
 
+// Elements of a handle's axis table: the padded forward and inverse matrices
+// of the fused transforms (none beyond them), then twice scale_len for the
+// Coulomb scales.
+struct AxisTable {
+  bool fused;
+  size_t axis_len, scale_len;
+  explicit AxisTable(const int32_t* n) : fused(transform_fits(n[0], n[1], n[2])), axis_len(0) {
+    scale_len = ((size_t)n[0] * n[1] * n[2] + 31) & ~(size_t)31;
+    for (int d = 0; d < 3 && fused; ++d) axis_len += 2 * transform_elems(n[d], n[d]);
+    axis_len = (axis_len + 31) & ~(size_t)31;
+  }
+  size_t bytes() const { return (axis_len + 2 * scale_len) * sizeof(double); }
+};
+
+uint64_t setup_bytes(const rpa_setup_params& p) {
+  const uint64_t N = (uint64_t)p.n[0] * p.n[1] * p.n[2];
+  const uint64_t ngal = (uint64_t)std::max(0, p.n_occ) + (uint64_t)std::max(0, p.n_extra);
+  uint64_t bytes = N * (sizeof(double) + sizeof(float)) + ngal * (N + 1) * sizeof(double);   // V, psi, eps
+  const AxisTable at(p.n);
+  bytes += at.bytes();
+  for (int d = 0; d < 3 && !at.fused; ++d) bytes += (uint64_t)p.n[d] * p.n[d] * sizeof(double);
+  if (p.precond) {
+    auto r = [](uint64_t b) { return (b + 255) & ~(uint64_t)255; };
+    bytes += r(sizeof(PrecArgs));
+    for (int d = 0; d < 3; ++d) {
+      const uint64_t Pd = prec_pad_host(p.n[d]), P2 = Pd * Pd;
+      bytes += 2 * r(P2 * sizeof(float)) + r(Pd * sizeof(float)) + 2 * r(P2 * sizeof(double)) + r(Pd * sizeof(double));
+    }
+  }
+  if (p.n_proj > 0) {
+    // both layouts: indices, FP32 and FP64 values, point pointers, groups
+    const uint64_t nnz = (uint64_t)p.proj_ptr[p.n_proj];
+    bytes += 2 * std::max<uint64_t>(1, nnz) * (sizeof(int) + sizeof(float) + sizeof(double)) + (N + 1) * sizeof(int) +
+             (uint64_t)p.n_proj * (sizeof(int4) + sizeof(int) + sizeof(double));
+  }
+  return bytes;
+}
+
 uint64_t lanczos_workspace_bytes(const rpa_setup_params& p, int B, int n_lanczos, int num_cu,
                                  bool query_occupancy) {
   const uint64_t N = (uint64_t)p.n[0] * p.n[1] * p.n[2];
@@ -972,16 +1010,14 @@ rpa_status rpa_setup(const rpa_setup_params* p, void* stream, rpa_handle* out) {
       !alloc((void**)&h->psi64, (size_t)h->ngal * N * sizeof(double)) ||
       !alloc((void**)&h->eps_d, h->ngal * sizeof(double)))
     return fail(RPA_E_OOM);
-  h->fused = transform_fits(h->n[0], h->n[1], h->n[2]);
+  const AxisTable at_size(p->n);
+  h->fused = at_size.fused;
   // one table, one copy (each copy from pageable memory waits about 17 us):
   // fused, the padded forward and inverse matrices of all axes, then the
   // Coulomb scales nu^1/2 and nu
-  const size_t scale_len = ((size_t)N + 31) & ~(size_t)31;
-  size_t axis_len = 0;
-  for (int d = 0; d < 3 && h->fused; ++d) axis_len += 2 * transform_elems(h->n[d], h->n[d]);
-  axis_len = (axis_len + 31) & ~(size_t)31;
+  const size_t axis_len = at_size.axis_len, scale_len = at_size.scale_len;
   std::vector<double> tables(axis_len + 2 * scale_len, 0.0);
-  if (!alloc((void**)&h->axis_mem, tables.size() * sizeof(double))) return fail(RPA_E_OOM);
+  if (!alloc((void**)&h->axis_mem, at_size.bytes())) return fail(RPA_E_OOM);
   h->s_half = h->axis_mem + axis_len;
   h->s_full = h->s_half + scale_len;
   if (h->fused) {

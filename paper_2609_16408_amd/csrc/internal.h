@@ -135,6 +135,9 @@ int pick_tile_y(int ny, int nz, int requested);
 // calculator (needs a device), else two per CU are assumed.
 uint64_t lanczos_workspace_bytes(const rpa_setup_params& p, int B, int n_lanczos, int num_cu,
                                  bool query_occupancy);
+// Device bytes rpa_setup keeps for the problem `p` (with projectors an upper
+// bound: projectors that share a support store it once).
+uint64_t setup_bytes(const rpa_setup_params& p);
 
 // The persistent kernel of variant V (bit 0: nonlocal term, bit 1:
 // preconditioned) and LDS row pitch PITCH for tile mode m (0: the tile is the

@@ -181,6 +181,42 @@ int workspace(int nx, int ny, int nz, int n_occ, int n_pts, int m, int precision
   return used <= counted + counters && counted <= used + counters ? 0 : fail("the count is not what is allocated");
 }
 
+// --- resident: the server counts what a worker's setup keeps, and its own copy
+
+int resident(int nx, int ny, int nz, int n_occ, int precond, int n_proj) {
+  rpa_setup_params p = problem(nx, ny, nz, n_occ, RPA_FP32_REFINE, precond != 0);
+  // pairs of projectors on the same three points
+  std::vector<int64_t> ptr(n_proj + 1), idx(3 * n_proj);
+  std::vector<double> val(3 * n_proj, 0.5), gamma(n_proj, 1.0);
+  for (int q = 0; q <= n_proj; ++q) ptr[q] = 3 * q;
+  for (int e = 0; e < 3 * n_proj; ++e) idx[e] = 5 * (e / 6) + e % 3;
+  p.n_proj = n_proj;
+  p.proj_ptr = ptr.data();
+  p.proj_idx = idx.data();
+  p.proj_val = val.data();
+  p.proj_gamma = gamma.data();
+  rpa_handle h = nullptr;
+  if (rpa_setup(&p, nullptr, &h) != RPA_OK) return fail(rpa_last_error(nullptr));
+  const size_t kept = g_bytes;
+  rpa_destroy(h);
+  rpa_server_params sp;
+  std::memset(&sp, 0, sizeof(sp));
+  sp.n_workers = 2;
+  sp.fake_executor_us = 1;
+  rpa_server s = nullptr;
+  int32_t id = 0;
+  uint64_t high = 0;
+  if (rpa_server_create(&sp, &s) != RPA_OK || rpa_server_add_cell(s, &p, &id) != RPA_OK ||
+      rpa_server_status(s, nullptr, nullptr, nullptr, &high) != RPA_OK)
+    return fail("server");
+  rpa_server_destroy(s);
+  const uint64_t own = 8ULL * nx * ny * nz * (1 + n_occ);
+  std::printf("kept %zu counted %llu\n", kept, (unsigned long long)((high - own) / 2));
+  // a shared support is stored once and counted for each projector
+  const uint64_t shared = n_proj > 0 ? 40ULL * n_proj : 0;
+  return high >= own + 2 * kept && high <= own + 2 * (kept + shared) ? 0 : fail("the count is not what is kept");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -190,6 +226,7 @@ int main(int argc, char** argv) {
   int r = 2;
   if (what == "slots" && v.size() == 7) r = slots(v[0], v[1], v[2], v[3], v[4], v[5], v[6]);
   if (what == "workspace" && v.size() == 8) r = workspace(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]);
+  if (what == "resident" && v.size() == 6) r = resident(v[0], v[1], v[2], v[3], v[4], v[5]);
   if (r == 0) std::printf("ok\n");
   return r;
 }

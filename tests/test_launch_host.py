@@ -47,3 +47,12 @@ def test_sternheimer_workspaces_lie_inside_their_allocation(host, n, precision, 
 @pytest.mark.parametrize("precision", [FP64, FP32])
 def test_counted_workspace_is_what_a_job_allocates(host, precision, window, n_occ, n_pts):
     host("workspace", 24, 24, 20, n_occ, n_pts, 3, precision, int(window))
+
+
+# grids on and off the padding of the transform matrices, and one beyond them
+@pytest.mark.parametrize("precond,n_proj", [(False, 0), (True, 0), (False, 6)])
+@pytest.mark.parametrize("n", [(16, 16, 16), (24, 17, 18), (130, 8, 9)])
+def test_server_counts_what_a_worker_keeps(host, n, precond, n_proj):
+    if precond and max(n) > 64:
+        pytest.skip("the preconditioner needs dimensions of at most 64")
+    host("resident", *n, 3, int(precond), n_proj)
