@@ -166,17 +166,18 @@ __global__ void k_gram_finish(const double* __restrict__ part, int B, int n_occ,
 // x 64 grid points; the workgroups of a point range are dealt to one XCD.
 // Bound by the matrix cores at 512 x 128 states: 48^3, 16 start vectors,
 // 13.3 -> 10.2 ms (46 TFLOP/s) against vector FP64 tiles through LDS.
+constexpr int kExpandPoints = 64;        // grid points of a k_expand workgroup
 template <int TN>
 __global__ void __launch_bounds__(256, 2) k_expand(const double* __restrict__ psi,
                                                    const double2* __restrict__ G, int B, int n_occ, int ng,
-                                                   long long N, double2* __restrict__ x64) {
-  constexpr int TR = 4;
+                                                   long long N, long long c0, double2* __restrict__ x64) {
+  constexpr int TR = kExpandPoints / 16;
   const int ntn = (n_occ + 16 * TN - 1) / (16 * TN);
   const int jobs = B * ntn;
   int c, rank;
   xcd_chunk((jobs + 3) / 4, c, rank);
   const int job = rank * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const long long r0 = (long long)c * 16 * TR;
+  const long long r0 = (c0 + c) * kExpandPoints;
   if (r0 >= N || job >= jobs) return;
   const int b = job / ntn, n0 = job % ntn * 16 * TN;
   const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
@@ -508,13 +509,27 @@ hipError_t launch_gram_finish(const double* part, int B, int n_occ, int ng, int 
 hipError_t launch_expand(const double* psi, const double2* G, int B, int n_occ, int ng, long long N,
                          double2* x64, hipStream_t s) {
   const int tn = n_occ <= 16 ? 1 : 2;
-  const long long jobs = (long long)B * ((n_occ + 16 * tn - 1) / (16 * tn));
-  const dim3 grid(xcd_grid((int)((N + 63) / 64), (int)((jobs + 3) / 4)));
-  if (tn == 1)
-    hipLaunchKernelGGL((k_expand<1>), grid, dim3(256), 0, s, psi, G, B, n_occ, ng, N, x64);
-  else
-    hipLaunchKernelGGL((k_expand<2>), grid, dim3(256), 0, s, psi, G, B, n_occ, ng, N, x64);
-  return hipGetLastError();
+  const long long ntn = (n_occ + 16 * tn - 1) / (16 * tn), chunks = (N + kExpandPoints - 1) / kExpandPoints;
+  // a grid's threads are counted in 32 bits: ranges of start vectors, then of
+  // points in whole rounds of the XCDs, of at most kMost workgroups
+  constexpr long long kMost = 1LL << 23;
+  const int nb = (int)std::min<long long>(B, std::max(1LL, kMost / kXcds * 4 / ntn));
+  for (int b0 = 0; b0 < B; b0 += nb) {
+    const int bn = std::min(nb, B - b0);
+    const long long per_chunk = (bn * ntn + 3) / 4, span = std::max(1LL, kMost / kXcds / per_chunk) * kXcds;
+    const double2* Gb = G + (size_t)b0 * ng * n_occ;
+    double2* xb = x64 + (size_t)b0 * n_occ * N;
+    for (long long c0 = 0; c0 < chunks; c0 += span) {
+      const dim3 grid(xcd_grid((int)std::min(span, chunks - c0), (int)per_chunk));
+      if (tn == 1)
+        hipLaunchKernelGGL((k_expand<1>), grid, dim3(256), 0, s, psi, Gb, bn, n_occ, ng, N, c0, xb);
+      else
+        hipLaunchKernelGGL((k_expand<2>), grid, dim3(256), 0, s, psi, Gb, bn, n_occ, ng, N, c0, xb);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+  }
+  return hipSuccess;
 }
 hipError_t launch_accumulate(const double* psi, const double2* x64, int B, int n_occ, long long N,
                              const int* active, double* racc, hipStream_t s) {

@@ -217,6 +217,44 @@ int resident(int nx, int ny, int nz, int n_occ, int precond, int n_proj) {
   return high >= own + 2 * kept && high <= own + 2 * (kept + shared) ? 0 : fail("the count is not what is kept");
 }
 
+// --- expand: launches within the grid limit that together cover every start
+// vector and point once
+
+struct ExpandLaunch {
+  long long b0, bn, c0, threads, groups;
+};
+std::vector<ExpandLaunch> g_expand;
+long long g_expand_vec = 0;          // elements of a start vector's G
+
+int expand(long long N, int n_occ, int ng, int B) {
+  g_expand_vec = (long long)ng * n_occ;
+  g_on_launch = [](const Launch& l) {
+    // psi, G, B, n_occ, ng, N, first chunk, x
+    const double2* G = *static_cast<const double2**>(l.args[1]);
+    g_expand.push_back({(long long)(reinterpret_cast<uintptr_t>(G) / sizeof(double2)) / g_expand_vec,
+                        *static_cast<int*>(l.args[2]), *static_cast<long long*>(l.args[6]),
+                        (long long)l.grid.x * l.block.x, l.grid.x});
+  };
+  if (rpa::launch_expand(nullptr, nullptr, B, n_occ, ng, N, nullptr, nullptr) != hipSuccess) return fail("launch");
+  const long long tn = n_occ <= 16 ? 1 : 2, ntn = (n_occ + 16 * tn - 1) / (16 * tn), chunks = (N + 63) / 64;
+  long long b = 0, c = 0;            // next start vector, next chunk of its range
+  for (const ExpandLaunch& l : g_expand) {
+    if (l.threads >= 1LL << 32) return fail("grid of " + std::to_string(l.threads) + " threads");
+    if (l.b0 != b || l.c0 != c) return fail("gap");
+    // workgroups are dealt to the eight XCDs by chunk, four tiles each
+    const long long per_chunk = (l.bn * ntn + 3) / 4;
+    if (l.groups % (8 * per_chunk)) return fail("grid");
+    c += l.groups / per_chunk;
+    if (c >= chunks) {
+      if (c >= chunks + 8) return fail("overrun");
+      c = 0;
+      b += l.bn;
+    }
+  }
+  std::printf("%zu launches\n", g_expand.size());
+  return b == B && c == 0 ? 0 : fail("not all covered");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -227,6 +265,7 @@ int main(int argc, char** argv) {
   if (what == "slots" && v.size() == 7) r = slots(v[0], v[1], v[2], v[3], v[4], v[5], v[6]);
   if (what == "workspace" && v.size() == 8) r = workspace(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]);
   if (what == "resident" && v.size() == 6) r = resident(v[0], v[1], v[2], v[3], v[4], v[5]);
+  if (what == "expand" && v.size() == 4) r = expand(std::atoll(argv[2]), v[1], v[2], v[3]);
   if (r == 0) std::printf("ok\n");
   return r;
 }

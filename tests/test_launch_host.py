@@ -56,3 +56,11 @@ def test_server_counts_what_a_worker_keeps(host, n, precond, n_proj):
     if precond and max(n) > 64:
         pytest.skip("the preconditioner needs dimensions of at most 64")
     host("resident", *n, 3, int(precond), n_proj)
+
+
+# launches of one range; ranges of points (many start vectors of one orbital, a
+# long grid) and of start vectors
+@pytest.mark.parametrize("N,n_occ,ng,B", [(343, 1, 1, 1), (110592, 128, 512, 64), (110592, 1, 1, 39000), (110592, 33, 40, 50000),
+                                          ((1 << 32) + 77, 1, 3, 2), (343, 1, 1, 1 << 25), (520, 17, 17, 1 << 25)])
+def test_expansion_launches_stay_within_the_grid_limit(host, N, n_occ, ng, B):
+    host("expand", N, n_occ, ng, B)
