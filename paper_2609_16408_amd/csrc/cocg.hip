@@ -112,7 +112,7 @@ void cocg_pc_shape(Geom& g, int block, int n_proj) {
   // kPcBlock threads keep the memory pipes busy whatever the stencil tile is;
   // the tile's own workgroup only where the larger reduction buffer would not fit
   for (const int b : {kPcBlock, block}) {
-    const size_t rest = red_bytes(b) + (size_t)n_proj * sizeof(double2) + 256;
+    const size_t rest = red_bytes(b) + (size_t)n_proj * sizeof(double2);
     const size_t lds = 160 * 1024 > rest ? 160 * 1024 - rest : 0;
     g.pc_block = b;
     g.pc_planes32 = pc_planes<float>(g, b, lds);
@@ -185,7 +185,7 @@ hipError_t launch_cocg(const CocgArgs& a, bool fp32_refine, int grid, int block,
     // residual elements in the LDS that this many workgroups per compute unit
     // leave free, in whole trips of the streaming sweeps
     const int per_cu = std::max(1, (grid + num_cu - 1) / num_cu);
-    const long long free_lds = 160 * 1024 / per_cu - (long long)shmem - 256;
+    const long long free_lds = 160 * 1024 / per_cu - (long long)shmem;
     const long long trip = (long long)kSweep * block, elem = fp32_refine ? sizeof(float2) : sizeof(double2);
     const long long n = std::min(a.g.N, std::max(0LL, free_lds) / elem);
     b.r_lds = (int)(n / trip * trip);

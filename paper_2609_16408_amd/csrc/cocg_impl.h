@@ -1176,21 +1176,24 @@ __global__ void __launch_bounds__(kMaxBlock) k_cocg(CocgArgs a) {
   constexpr bool PC = (V & 2) != 0;
   constexpr bool FULL = M == 0;
   constexpr int HS = M == 2 ? 2 : 1;
-  // 16-byte accesses need the alignment: behind s_item the buffer would start
-  // at 8, where each ds_read_b128 took 54 cycles of the LDS instead of 8 (the
-  // FP64 stencil sweep of a 24^3 system 165 us instead of 30)
+  // All LDS is dynamic, so that what setup accepts is what a launch may use, and
+  // starts aligned: behind a static int the buffer began at 8, where each
+  // ds_read_b128 took 54 cycles of the LDS instead of 8 (the FP64 stencil sweep
+  // of a 24^3 system 165 us instead of 30)
   extern __shared__ __attribute__((aligned(256))) double smem_d[];
   char* smem = reinterpret_cast<char*>(smem_d);
   const Geom& g = a.g;
   double* red = reinterpret_cast<double*>(smem + lds_plane_bytes(g, PITCH, REFINE));
   char* nlc = smem + lds_plane_bytes(g, PITCH, REFINE) + red_bytes(blockDim.x);
-  __shared__ int s_item;
+  // the next system's index travels in the reduction buffer: block_reduce ends
+  // with a barrier after its last read, so between systems nothing is live there
+  int* s_item = reinterpret_cast<int*>(red);
   int item = 0;
   // the FP64 launch after an FP32 one takes the systems the latter handed over
   const int n_items = a.n_items_dev ? uni(*a.n_items_dev) : a.n_items;
-  if (threadIdx.x == 0) s_item = atomicAdd(a.counter, 1);
+  if (threadIdx.x == 0) *s_item = atomicAdd(a.counter, 1);
   __syncthreads();
-  item = uni(s_item);
+  item = uni(*s_item);
   __syncthreads();
   while (item < n_items) {
     const int s = uni(a.order[item]);
@@ -1204,9 +1207,9 @@ __global__ void __launch_bounds__(kMaxBlock) k_cocg(CocgArgs a) {
       a.out_cycles[s] = 0;
       a.out_status[s] = 0;
     }
-    if (threadIdx.x == 0) s_item = atomicAdd(a.counter, 1);
+    if (threadIdx.x == 0) *s_item = atomicAdd(a.counter, 1);
     __syncthreads();
-    item = uni(s_item);
+    item = uni(*s_item);
     __syncthreads();
   }
 }

@@ -118,6 +118,22 @@ rpa_setup_params problem(int nx, int ny, int nz, int n_occ, rpa_precision precis
   return p;
 }
 
+// n_proj projectors of three points, every two of them on the same ones.
+void add_projectors(rpa_setup_params& p, int n_proj) {
+  const long long N = (long long)p.n[0] * p.n[1] * p.n[2];
+  auto* ptr = new std::vector<int64_t>(n_proj + 1);
+  auto* idx = new std::vector<int64_t>(3 * n_proj);
+  auto* val = new std::vector<double>(3 * n_proj, 0.5);
+  auto* gamma = new std::vector<double>(n_proj, 1.0);
+  for (int q = 0; q <= n_proj; ++q) (*ptr)[q] = 3 * q;
+  for (int e = 0; e < 3 * n_proj; ++e) (*idx)[e] = (5 * (e / 6) + e % 3) % N;
+  p.n_proj = n_proj;
+  p.proj_ptr = ptr->data();
+  p.proj_idx = idx->data();
+  p.proj_val = val->data();
+  p.proj_gamma = gamma->data();
+}
+
 // --- slots: the workspaces of every Sternheimer launch lie inside their allocation
 
 bool g_slots_ok = true;
@@ -185,16 +201,7 @@ int workspace(int nx, int ny, int nz, int n_occ, int n_pts, int m, int precision
 
 int resident(int nx, int ny, int nz, int n_occ, int precond, int n_proj) {
   rpa_setup_params p = problem(nx, ny, nz, n_occ, RPA_FP32_REFINE, precond != 0);
-  // pairs of projectors on the same three points
-  std::vector<int64_t> ptr(n_proj + 1), idx(3 * n_proj);
-  std::vector<double> val(3 * n_proj, 0.5), gamma(n_proj, 1.0);
-  for (int q = 0; q <= n_proj; ++q) ptr[q] = 3 * q;
-  for (int e = 0; e < 3 * n_proj; ++e) idx[e] = 5 * (e / 6) + e % 3;
-  p.n_proj = n_proj;
-  p.proj_ptr = ptr.data();
-  p.proj_idx = idx.data();
-  p.proj_val = val.data();
-  p.proj_gamma = gamma.data();
+  add_projectors(p, n_proj);
   rpa_handle h = nullptr;
   if (rpa_setup(&p, nullptr, &h) != RPA_OK) return fail(rpa_last_error(nullptr));
   const size_t kept = g_bytes;
@@ -255,6 +262,33 @@ int expand(long long N, int n_occ, int ng, int B) {
   return b == B && c == 0 ? 0 : fail("not all covered");
 }
 
+// --- lds: the most projectors that setup accepts, and the largest dynamic LDS of
+// the Sternheimer launches then
+
+size_t g_lds = 0;
+
+int lds(int nx, int ny, int nz, int precision, int precond, int window) {
+  rpa_setup_params p = problem(nx, ny, nz, 2, (rpa_precision)precision, precond != 0);
+  if (window) p.precond_omega_min = 1.0;
+  g_on_launch = [](const Launch& l) {
+    if (is_cocg<1>(l.fn) || is_cocg<3>(l.fn)) g_lds = l.shmem > g_lds ? l.shmem : g_lds;
+  };
+  rpa_handle h = nullptr;
+  int n = rpa::kMaxProj;
+  for (; n > 0; --n) {
+    add_projectors(p, n);
+    if (rpa_setup(&p, nullptr, &h) == RPA_OK) break;
+  }
+  if (n == 0) return fail(rpa_last_error(nullptr));
+  const size_t N = (size_t)nx * ny * nz;
+  std::vector<double> u(9 * N), x(36 * N);
+  if (rpa_sternheimer_solve(h, 0.5, 9, u.data(), x.data(), nullptr, nullptr) != RPA_OK)
+    return fail(rpa_last_error(nullptr));
+  rpa_destroy(h);
+  std::printf("projectors %d lds %zu\n", n, g_lds);
+  return g_lds > 0 ? 0 : fail("no launch seen");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -266,6 +300,7 @@ int main(int argc, char** argv) {
   if (what == "workspace" && v.size() == 8) r = workspace(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]);
   if (what == "resident" && v.size() == 6) r = resident(v[0], v[1], v[2], v[3], v[4], v[5]);
   if (what == "expand" && v.size() == 4) r = expand(std::atoll(argv[2]), v[1], v[2], v[3]);
+  if (what == "lds" && v.size() == 6) r = lds(v[0], v[1], v[2], v[3], v[4], v[5]);
   if (r == 0) std::printf("ok\n");
   return r;
 }

@@ -2,6 +2,7 @@
 program runs the library over a stand-in for the HIP runtime (host_runtime.cpp)
 that records allocations and looks at every launch instead of running it."""
 import os
+import re
 import shutil
 import subprocess
 
@@ -64,3 +65,31 @@ def test_server_counts_what_a_worker_keeps(host, n, precond, n_proj):
                                           ((1 << 32) + 77, 1, 3, 2), (343, 1, 1, 1 << 25), (520, 17, 17, 1 << 25)])
 def test_expansion_launches_stay_within_the_grid_limit(host, N, n_occ, ng, B):
     host("expand", N, n_occ, ng, B)
+
+
+@pytest.fixture(scope="module")
+def fixed_lds(tmp_path_factory):
+    """Fixed LDS of every kernel of the built library, from its metadata."""
+    tools = [os.path.join("/opt/rocm/llvm/bin", t) for t in ("llvm-objdump", "llvm-readelf")]
+    if not all(map(os.path.exists, tools)):
+        pytest.skip("needs the LLVM tools of ROCm")
+    at = tmp_path_factory.mktemp("objects")
+    shutil.copy(os.path.join(PKG, "librpa_mi355x.so"), at)
+    subprocess.run([tools[0], "--offloading", "librpa_mi355x.so"], cwd=at, check=True, capture_output=True)
+    out = {}
+    for f in sorted(os.listdir(at)):
+        if "gfx950" in f:
+            notes = subprocess.run([tools[1], "--notes", f], cwd=at, check=True, capture_output=True, text=True).stdout
+            for size, name in re.findall(r"\.group_segment_fixed_size: (\d+).*?\n    \.name: +(\S+)", notes, re.S):
+                out[name] = int(size)
+    return out
+
+
+# whole planes and tiles on each LDS pitch, with the most projectors that setup accepts
+@pytest.mark.parametrize("precond,window", [(False, False), (True, False), (True, True)])
+@pytest.mark.parametrize("precision", [FP64, FP32])
+@pytest.mark.parametrize("n", [(7, 14, 53), (13, 27, 28), (9, 28, 48), (12, 28, 50)])
+def test_accepted_problems_fit_the_local_memory(host, fixed_lds, n, precision, precond, window):
+    fixed = max(v for k, v in fixed_lds.items() if "6k_cocgI" in k)
+    lds = int(host("lds", *n, precision, int(precond), int(window)).split("lds ")[1].split()[0])
+    assert lds + fixed <= 160 * 1024, (lds, fixed)
