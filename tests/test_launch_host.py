@@ -93,3 +93,9 @@ def test_accepted_problems_fit_the_local_memory(host, fixed_lds, n, precision, p
     fixed = max(v for k, v in fixed_lds.items() if "6k_cocgI" in k)
     lds = int(host("lds", *n, precision, int(precond), int(window)).split("lds ")[1].split()[0])
     assert lds + fixed <= 160 * 1024, (lds, fixed)
+
+
+@pytest.mark.parametrize("precision", [FP64, FP32])
+@pytest.mark.parametrize("n", [(24, 24, 24), (48, 48, 48), (17, 36, 20)])
+def test_plain_stencil_launches_the_same_on_a_preconditioned_handle(host, n, precision):
+    assert host("stencil", *n, precision, 1) == host("stencil", *n, precision, 0)
