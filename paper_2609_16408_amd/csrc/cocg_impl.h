@@ -992,8 +992,22 @@ __device__ __forceinline__ void solve_plain(const CocgArgs& a, int s, char* smem
 // transforms), at a reliable update in FP32.  FP64 takes 8: rounding in the
 // recurrence ends the longest solves early (24^3, tol 1e-10, right-hand sides
 // perturbed by 1e-15: 94 iterations at an unrecurred q and at 8, 91 in half of
-// the runs at 24 or without; true residuals are the same within a percent).
-// FP32 measures its true residual and takes 24.
+// the runs at 24 or without).  At 8, iterations and true residuals are those of
+// q formed by the stencil in each iteration on nine grids from 7x8x9 to 48^3,
+// omega 0.02 to 49, tol 1e-8 to 1e-13.  FP32 measures its true residual and
+// takes 24.
+//
+// Where a few iterations reach the FP32 rounding of A x (omega far above the
+// potential), the recursive residual has fallen below the true one when that is
+// measured.  beta then compares the new residual with one that the kept
+// direction no longer belongs to, and with q from the recurrence the solve
+// stalls or diverges: at omega 49.4, tol 1e-10 on nine grids 171 iterations in
+// the mean and 99 of 520 systems handed to FP64 (q by the stencil: 12 and 0; at
+// 187 all were handed over either way).  So a true residual kRestart times the
+// recursive one leaves the direction: 6 iterations there, none handed over up to
+// omega 2000.  Slow solves pass the test; kRestart 1.01 costs 2% more iterations
+// at omega 0.02 than 1.1, which at omega 30 lets single systems take 22 instead of 7.
+constexpr double kRestart = 1.03;
 
 template <bool REFINE, bool FULL, int HS, int PITCH, bool NL>
 __device__ __forceinline__ void solve_pc(const CocgArgs& a, int s, char* smem, double* red, char* nlc) {
@@ -1048,6 +1062,12 @@ __device__ __forceinline__ void solve_pc(const CocgArgs& a, int s, char* smem, d
       march<double, FULL, HS, PITCH>(g, a.c64, rp, reinterpret_cast<double2*>(smem), 0, g.ntiles, 0, g.nx);
       double w2[2] = {rp.rr, rp.bb};
       block_reduce<2>(w2, red);
+      if constexpr (REFINE) {
+        if (!start && !(uni(sqrt(w2[0])) <= kRestart * rnorm)) {
+          first = true;            // leave the search direction
+          last_q = its;
+        }
+      }
       rnorm = uni(sqrt(w2[0]));
       rmax = rnorm;
       if (start) {
