@@ -18,8 +18,10 @@ struct HapplyShifts {
 // most 80 registers, so that two workgroups of a 768-thread tile share a
 // compute unit and one loads while the other computes (512 vectors of 48^3:
 // 305 us with one workgroup, 270 with two; 193 at the rate of a copy).
+template <typename T>
+constexpr int kHapplyWaves = sizeof(T) == 4 ? 6 : 4;   // per SIMD: at most 80 and 128 registers
 template <typename T, int M, int PITCH>
-__global__ void __launch_bounds__(kMaxBlock, sizeof(T) == 4 ? 6 : 1) k_happly(Geom g, StencilCoef<T> cf, const T* v,
+__global__ void __launch_bounds__(kMaxBlock, kHapplyWaves<T>) k_happly(Geom g, StencilCoef<T> cf, const T* v,
                                                        const double* sr, const double* si,
                                                        const void* x, void* y, int seg, HapplyShifts sh) {
   extern __shared__ double smem_d[];
@@ -159,11 +161,26 @@ HapplyKernel<T> happly_kernel(int m) {
 
 template <typename T>
 hipError_t launch_ht(const Geom& g, const StencilCoef<T>& cf, const T* v, const double* sr, const double* si,
-                     const HapplyShifts& sh, const void* x, void* y, int nvec, int block, size_t shmem, hipStream_t s) {
-  constexpr int kFill = 512;         // workgroups that fill the chip (two per compute unit)
-  // few workgroups: split the march along x (each segment reads its own 12 halo planes)
-  const long long wgs = (long long)g.ntiles * nvec;
-  const int nseg = (int)std::max<long long>(1, std::min<long long>(g.nx, kFill / wgs));
+                     const HapplyShifts& sh, const void* x, void* y, int nvec, int block, size_t shmem, int num_cu,
+                     hipStream_t s) {
+  // few workgroups: split the march along x.  A segment reads its own 12 halo
+  // planes, so of the splits of at most two rounds of the workgroups that run at
+  // once the one with the fewest plane steps is taken (more rounds are bound by
+  // memory, where the halo costs): 64 FP64 vectors of 48^3, one 768-thread
+  // workgroup per compute unit, 67 us whole and 74 in halves; 65 of 60x30x40 93 us
+  // whole and 85 in thirds; 300 FP32 vectors of 128x8x8, four workgroups per
+  // compute unit, 103 us whole and 60 in thirds
+  const int fit = std::max(1, std::min(4 * kHapplyWaves<T> / (block / 64), (int)(160 * 1024 / shmem)));
+  const long long wgs = (long long)g.ntiles * nvec, cap = (long long)fit * num_cu;
+  int nseg = 1;
+  long long best = -1;
+  for (int k = 1; k <= g.nx && (k == 1 || k * wgs <= 2 * cap); ++k) {
+    const long long seg = (g.nx + k - 1) / k, steps = (k * wgs + cap - 1) / cap * (seg + 2 * R);
+    if (best < 0 || steps < best) {
+      best = steps;
+      nseg = k;
+    }
+  }
   const int seg = (g.nx + nseg - 1) / nseg;
   const int m = tile_mode(g, block);
   const int pitch = pitch_for(g);
@@ -198,7 +215,7 @@ hipError_t launch_cocg(const CocgArgs& a, bool fp32_refine, int grid, int block,
 hipError_t launch_happly(const Geom& g, const StencilCoef<double>& c64, const StencilCoef<float>& c32,
                          const double* v64, const float* v32, int nvec, const double* shift_re,
                          const double* shift_im, bool host_shifts, const void* x, void* y, bool fp32,
-                         int block, hipStream_t s) {
+                         int block, int num_cu, hipStream_t s) {
   // without the preconditioner's bases and planes, which this kernel does not
   // use: with them one workgroup of 48^3 filled a compute unit's LDS (137 KB against 57)
   Geom gp = g;
@@ -214,8 +231,8 @@ hipError_t launch_happly(const Geom& g, const StencilCoef<double>& c64, const St
     }
     shift_re = shift_im = nullptr;
   }
-  if (fp32) return launch_ht<float>(g, c32, v32, shift_re, shift_im, sh, x, y, nvec, block, shmem, s);
-  return launch_ht<double>(g, c64, v64, shift_re, shift_im, sh, x, y, nvec, block, shmem, s);
+  if (fp32) return launch_ht<float>(g, c32, v32, shift_re, shift_im, sh, x, y, nvec, block, shmem, num_cu, s);
+  return launch_ht<double>(g, c64, v64, shift_re, shift_im, sh, x, y, nvec, block, shmem, num_cu, s);
 }
 
 hipError_t launch_nl_apply(const NlArgs& nl, long long N, int nvec, const void* x, void* y,

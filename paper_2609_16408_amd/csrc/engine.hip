@@ -1240,7 +1240,7 @@ rpa_status rpa_hamiltonian_apply(rpa_handle h, int32_t nvec, const double* shift
   HIPCHK(h, launch_happly(h->geom, h->c64, h->c32, h->v64, h->v32, nvec,
                           host_shifts ? shift_re : P<double>(h->shifts),
                           host_shifts ? shift_im : P<double>(h->shifts) + nvec, host_shifts, x, y, precision == RPA_FP32_REFINE,
-                          h->block, s));
+                          h->block, h->num_cu, s));
   HIPCHK(h, hipEventRecord(h->ev1, s));
   if (h->nl.n_proj > 0) {
     ENSURE(h, h->nlcoef, (size_t)nvec * h->nl.n_proj * sizeof(double2));

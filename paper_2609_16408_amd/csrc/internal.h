@@ -171,7 +171,7 @@ int cocg_prec_regs_max();
 hipError_t launch_happly(const Geom& g, const StencilCoef<double>& c64, const StencilCoef<float>& c32,
                          const double* v64, const float* v32, int nvec, const double* shift_re,
                          const double* shift_im, bool host_shifts, const void* x, void* y, bool fp32,
-                         int block, hipStream_t s);
+                         int block, int num_cu, hipStream_t s);
 // y[v] += V_nl x[v] for nvec vectors of N points (complex, FP32 or FP64);
 // coef: workspace of nvec * n_proj complex values of that precision.
 hipError_t launch_nl_apply(const NlArgs& nl, long long N, int nvec, const void* x, void* y,

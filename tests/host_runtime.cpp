@@ -291,17 +291,16 @@ int lds(int nx, int ny, int nz, int precision, int precond, int window) {
 
 // --- stencil: the plain operator's launch of a handle
 
-int stencil(int nx, int ny, int nz, int precision, int precond) {
+int stencil(int nx, int ny, int nz, int precision, int precond, int nvec) {
   rpa_setup_params p = problem(nx, ny, nz, 2, RPA_FP32_REFINE, precond != 0);
   rpa_handle h = nullptr;
   if (rpa_setup(&p, nullptr, &h) != RPA_OK) return fail(rpa_last_error(nullptr));
   g_on_launch = [](const Launch& l) {
     std::printf("grid %u %u %u block %u lds %zu\n", l.grid.x, l.grid.y, l.grid.z, l.block.x, l.shmem);
   };
-  const double zero[3] = {0.0, 0.0, 0.0};
-  const size_t N = (size_t)nx * ny * nz;
-  std::vector<double> x(6 * N), y(6 * N);
-  if (rpa_hamiltonian_apply(h, 3, zero, zero, x.data(), y.data(), precision, nullptr) != RPA_OK)
+  const std::vector<double> zero(nvec, 0.0);
+  double x = 0.0, y = 0.0;           // the kernel does not run
+  if (rpa_hamiltonian_apply(h, nvec, zero.data(), zero.data(), &x, &y, precision, nullptr) != RPA_OK)
     return fail(rpa_last_error(nullptr));
   rpa_destroy(h);
   return 0;
@@ -319,7 +318,7 @@ int main(int argc, char** argv) {
   if (what == "resident" && v.size() == 6) r = resident(v[0], v[1], v[2], v[3], v[4], v[5]);
   if (what == "expand" && v.size() == 4) r = expand(std::atoll(argv[2]), v[1], v[2], v[3]);
   if (what == "lds" && v.size() == 6) r = lds(v[0], v[1], v[2], v[3], v[4], v[5]);
-  if (what == "stencil" && v.size() == 5) r = stencil(v[0], v[1], v[2], v[3], v[4]);
+  if (what == "stencil" && v.size() == 6) r = stencil(v[0], v[1], v[2], v[3], v[4], v[5]);
   if (r == 0) std::printf("ok\n");
   return r;
 }

@@ -98,4 +98,22 @@ def test_accepted_problems_fit_the_local_memory(host, fixed_lds, n, precision, p
 @pytest.mark.parametrize("precision", [FP64, FP32])
 @pytest.mark.parametrize("n", [(24, 24, 24), (48, 48, 48), (17, 36, 20)])
 def test_plain_stencil_launches_the_same_on_a_preconditioned_handle(host, n, precision):
-    assert host("stencil", *n, precision, 1) == host("stencil", *n, precision, 0)
+    assert host("stencil", *n, precision, 1, 3) == host("stencil", *n, precision, 0, 3)
+
+
+# few and many vectors of grids with small, large and several tiles
+@pytest.mark.parametrize("precision,waves_per_cu", [(FP64, 16), (FP32, 24)])
+@pytest.mark.parametrize("n,nvec", [((48, 48, 48), 65), ((48, 48, 48), 512), ((24, 24, 24), 65), ((128, 8, 8), 300), ((12, 12, 12), 64),
+                                    ((9, 24, 72), 5), ((72, 72, 72), 31), ((7, 7, 7), 1), ((60, 30, 40), 65), ((60, 30, 40), 200)])
+def test_stencil_split_takes_the_fewest_plane_steps(host, n, nvec, precision, waves_per_cu):
+    """A march split along x repeats 12 halo planes per segment: the launch takes
+    the fewest steps of rounds times planes among the splits of up to two rounds."""
+    f = host("stencil", *n, precision, 0, nvec).split()
+    x, y, z, block, lds = int(f[1]), int(f[2]), int(f[3]), int(f[5]), int(f[7])
+    fit = 256 * max(1, min(waves_per_cu // (block // 64), 160 * 1024 // lds))
+
+    def steps(k):
+        return -(-x * y * k // fit) * (-(-n[0] // k) + 12)
+
+    allowed = [k for k in range(1, n[0] + 1) if k == 1 or x * y * k <= 2 * fit]
+    assert z in allowed and steps(z) == min(map(steps, allowed))
