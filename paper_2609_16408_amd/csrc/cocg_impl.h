@@ -469,7 +469,7 @@ __device__ __forceinline__ void march(const Geom& g, const StencilCoef<T>& cf, P
 // Bytes of LDS used by the plane buffers of the march (padded pitch): the
 // FP32 form of one tile takes four buffers, the FP64 form two of twice the size.
 __host__ __device__ inline size_t lds_plane_bytes(const Geom& g, int pitch, bool fp32_iter) {
-  const size_t rows_pad = (size_t)(g.ty == g.ny ? g.ny : g.ty) + 2 * R;
+  const size_t rows_pad = (size_t)g.ty + 2 * R;
   size_t b = 2 * rows_pad * pitch * sizeof(double2);
   if (g.prec) {
     // the preconditioner's bases and planes (FP64 for the FP64 solver, which

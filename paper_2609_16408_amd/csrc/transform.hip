@@ -33,7 +33,7 @@ __device__ __forceinline__ d4 mma(double a, double b, d4 c) {
 // and L are stored k-major and zero-padded to multiples of 16.  Each wave
 // owns 16 columns j of every plane of the workgroup.
 //
-// Bound by the matrix cores' operand supply at cell sizes (a 48^3 plane: 54
+// Bound by the matrix cores' operand supply at cell sizes (a 48^3 plane: 72
 // instructions per wave and plane, each with one LDS or L1 operand), by
 // launch latency below.  Two planes per workgroup share every basis operand
 // read; one where that would leave compute units without a workgroup.
@@ -338,6 +338,10 @@ int grid_of(long long n) {
   return (int)(g > 65536 ? 65536 : (g < 1 ? 1 : g));
 }
 
+// Largest row tiles of the forms that work on two planes or column blocks at
+// once: beyond, their tiles need more registers than a wave has.
+constexpr int kPairTiles = 5;
+
 template <int PL, bool ENERGY>
 hipError_t plane_t(const double* in, double* out, long long planes, int na, int nb, int ni, int nj,
                    const double* R, const double* L, double scale, double* partials, hipStream_t s) {
@@ -358,9 +362,16 @@ hipError_t plane_t(const double* in, double* out, long long planes, int na, int 
     hipLaunchKernelGGL((k_plane<RA, PL, ENERGY>), grid, block, shmem, s, src, dst, np, na, nb, ni, nj, R, L, ld, \
                        scale, par);                                                                 \
     break;
-    switch (ra) {
-      RPA_PLANE(1) RPA_PLANE(2) RPA_PLANE(3) RPA_PLANE(4) RPA_PLANE(5) RPA_PLANE(6) RPA_PLANE(7) RPA_PLANE(8)
-      default: return hipErrorInvalidValue;
+    static_assert(kPairTiles == 5, "the first switch lists the row tiles of both forms");
+    if (ra <= kPairTiles) {
+      switch (ra) { RPA_PLANE(1) RPA_PLANE(2) RPA_PLANE(3) RPA_PLANE(4) RPA_PLANE(5) }
+    } else if constexpr (PL == 1) {
+      switch (ra) {
+        RPA_PLANE(6) RPA_PLANE(7) RPA_PLANE(8)
+        default: return hipErrorInvalidValue;
+      }
+    } else {
+      return hipErrorInvalidValue;
     }
 #undef RPA_PLANE
     const hipError_t e = hipGetLastError();
@@ -389,9 +400,16 @@ hipError_t cols_t(const double* in, double* out, int B, int n_in, int n_out, int
     hipLaunchKernelGGL((k_cols<RK, NC, MODE>), grid, block, 0, s, src, dst, n_in, n_out, ncol, A1, A2, diag, \
                        sr0, si0, fw);                                                               \
     break;
-    switch ((n_in + 15) / 16) {
-      RPA_COLS(1) RPA_COLS(2) RPA_COLS(3) RPA_COLS(4) RPA_COLS(5) RPA_COLS(6) RPA_COLS(7) RPA_COLS(8)
-      default: return hipErrorInvalidValue;
+    const int rk = (n_in + 15) / 16;
+    if (rk <= kPairTiles) {
+      switch (rk) { RPA_COLS(1) RPA_COLS(2) RPA_COLS(3) RPA_COLS(4) RPA_COLS(5) }
+    } else if constexpr (NC == 1 || MODE == COLS_KINETIC) {
+      switch (rk) {
+        RPA_COLS(6) RPA_COLS(7) RPA_COLS(8)
+        default: return hipErrorInvalidValue;
+      }
+    } else {
+      return hipErrorInvalidValue;
     }
 #undef RPA_COLS
     const hipError_t e = hipGetLastError();
@@ -408,9 +426,9 @@ bool transform_fits(int d0, int d1, int d2) {
 
 hipError_t launch_planes(const double* in, double* out, long long planes, int na, int nb, int ni, int nj,
                          const double* L, const double* R, hipStream_t s) {
-  // two planes per workgroup need their registers (at most five row tiles)
-  // and enough planes that every compute unit still gets several workgroups
-  if (na <= 80 && nb <= 80 && planes >= 2048)
+  // two planes per workgroup need their registers and LDS, and enough planes
+  // that every compute unit still gets several workgroups
+  if (na <= 16 * kPairTiles && nb <= 16 * kPairTiles && planes >= 2048)
     return plane_t<2, false>(in, out, planes, na, nb, ni, nj, R, L, 1.0, nullptr, s);
   return plane_t<1, false>(in, out, planes, na, nb, ni, nj, R, L, 1.0, nullptr, s);
 }
@@ -437,7 +455,7 @@ hipError_t launch_cols_fields(const double* in, double* out, int n_fields, const
 
 hipError_t launch_cols_scale(const double* in, double* out, int B, int n, int ncol, const double* fwd,
                              const double* inv, const double* diag, hipStream_t s) {
-  if (n <= 80 && (long long)B * ncol >= 32 * 2048)
+  if (n <= 16 * kPairTiles && (long long)B * ncol >= 32 * 2048)
     return cols_t<2, COLS_SCALE>(in, out, B, n, n, ncol, fwd, inv, diag, nullptr, nullptr, ColsArgs{}, s);
   return cols_t<1, COLS_SCALE>(in, out, B, n, n, ncol, fwd, inv, diag, nullptr, nullptr, ColsArgs{}, s);
 }
