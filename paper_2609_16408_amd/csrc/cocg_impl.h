@@ -1037,6 +1037,11 @@ __device__ __forceinline__ void solve_pc(const CocgArgs& a, int s, char* smem, d
   auto nlp = [&](long long i, T2& qv) {
     if constexpr (NL) nl_point<T>(pm_ptr, pm_proj, pm_v, coef, i, qv.x, qv.y);
   };
+  // the recursive residual across a reliable update: whole-plane tiles keep it
+  // above what reductions of two values use of their buffer (as a live scalar it
+  // cost their passes 1 to 5%), the others in rmax (in LDS it cost them 2%)
+  double* rec_lds = nullptr;
+  if constexpr (REFINE && FULL) rec_lds = red + 2 * ((blockDim.x >> 6) + 1);
   const int maxit = REFINE ? a.maxit32 : a.maxit;
 
   ResidPol<T, NL> rp;
@@ -1062,13 +1067,15 @@ __device__ __forceinline__ void solve_pc(const CocgArgs& a, int s, char* smem, d
       march<double, FULL, HS, PITCH>(g, a.c64, rp, reinterpret_cast<double2*>(smem), 0, g.ntiles, 0, g.nx);
       double w2[2] = {rp.rr, rp.bb};
       block_reduce<2>(w2, red);
+      rnorm = uni(sqrt(w2[0]));
       if constexpr (REFINE) {
-        if (!start && !(uni(sqrt(w2[0])) <= kRestart * rnorm)) {
+        double rec = rmax;         // the recursive residual, set at the update
+        if constexpr (FULL) rec = uni(*rec_lds);
+        if (!start && rnorm > kRestart * rec) {
           first = true;            // leave the search direction
           last_q = its;
         }
       }
-      rnorm = uni(sqrt(w2[0]));
       rmax = rnorm;
       if (start) {
         const double bnorm = sqrt(w2[1]);
@@ -1106,6 +1113,11 @@ __device__ __forceinline__ void solve_pc(const CocgArgs& a, int s, char* smem, d
         // apparent convergence, and at least every kMaxGap iterations
         if ((rnorm < a.inner_tol * rmax && its - last_upd >= kMinGap) || rnorm <= thr ||
             its - last_upd >= kMaxGap) {
+          if constexpr (FULL) {
+            if (threadIdx.x == 0) *rec_lds = rnorm;
+          } else {
+            rmax = rnorm;
+          }
           fold_pair<T>(N, x, d, !dfresh, p, uni((T)al_r), uni((T)al_i));
           __syncthreads();
           dfresh = true;
